@@ -23,6 +23,17 @@ namespace rfi {
 
 static thread_local hipError_t t_last_hip = hipSuccess;
 
+static thread_local int t_wg_per_cu = 0;
+
+void set_wg_per_cu(int n) { t_wg_per_cu = n; }
+
+int wg_per_cu() { return t_wg_per_cu; }
+
+int persistent_grid(int elem, int cls, int modes, bool fused)
+{
+    return elem == 1 ? i8_persistent_grid(cls, modes, fused) : i16_persistent_grid(cls, modes, fused);
+}
+
 int hip_fail(hipError_t e)
 {
     t_last_hip = e;
@@ -252,7 +263,9 @@ struct PlanLaunch {
     int modes;  // bit m: some stream of the launch uses mode m
     int64_t first, count;
     int grid;
-    int small = 0;  // generic: 64 / 128 if every window spans at most 256 / 512 chunks
+    // generic: threads per window if every window fits them (int8: 64 / 128,
+    // at most 256 / 512 chunks; int16: i16_window_threads), else 0
+    int small = 0;
 };
 
 struct GraphEntry {
@@ -328,8 +341,21 @@ static hipError_t run_launch(const rfi_plan* p, const PlanLaunch& l, const Launc
         return launch_i8_fused(l.modes, a, l.grid, s);
     }
     if (l.kind == 0) return launch_i16_tiles(l.cls, l.modes, a, l.grid, s);
-    if (l.kind == 1) return launch_i16_generic(a, l.grid, s);
+    if (l.kind == 1) return launch_i16_generic(a, l.modes, l.grid, s, l.small);
     return launch_i16_fused(a, l.grid, s);
+}
+
+// Threads of the int16 kernel that holds a stream's windows in registers,
+// four 16-byte chunks (32 samples) per thread: the fewest that span the
+// stream's longest window wherever its windows start (a window that is a
+// multiple of 8 samples starts on a chunk, others up to 7 samples into
+// one).  0: too long, the two-pass radix kernel.  Fewer threads per window
+// means more windows in flight and fewer idle lanes.
+static int i16_window_threads(int32_t W, int64_t L)
+{
+    const int64_t n = std::min<int64_t>(W, L);
+    const int64_t chunks = (n + (W % 8 ? 7 : 0) + 7) / 8;
+    return chunks <= 256 ? 64 : chunks <= 512 ? 128 : chunks <= 1024 ? 256 : chunks <= 2048 ? 512 : 0;
 }
 
 static void build_launches(rfi_plan* p)
@@ -368,13 +394,22 @@ static void build_launches(rfi_plan* p)
         while (b < gend[g]) {
             int64_t e = gend[g];
             int modes = gmodes[g];
+            int threads = 0;
             if (g > 0) {
                 const int m = p->M[p->hitems[b].stream];
                 e = b;
                 while (e < gend[g] && p->M[p->hitems[e].stream] == m) ++e;
                 modes = 1 << m;
+            } else if (elem == 2) {
+                // one launch per window size class of the int16 kernels
+                auto nt = [&](int64_t i) { return i16_window_threads(p->W[p->hitems[i].stream], p->L[p->hitems[i].stream]); };
+                threads = nt(b);
+                e = b;
+                modes = 0;
+                while (e < gend[g] && nt(e) == threads) modes |= 1 << p->M[p->hitems[e++].stream];
             }
             PlanLaunch l{g == 0 ? 1 : 0, 0, cls, modes, b, e - b, clamp_grid(e - b)};
+            l.small = threads;
             if (g == 0 && elem == 1) {
                 // longest window of the launch; n + 30 <= 16 * 4 * NT keeps
                 // it within 4 * NT chunks at any alignment
@@ -443,6 +478,7 @@ static void build_launches(rfi_plan* p)
             }
             if (b < 0) continue;
             PlanLaunch l{g == 0 ? 1 : 0, 0, g - 1, 1 << p->M[s], b, e - b, clamp_grid(e - b)};
+            if (g == 0 && elem == 2) l.small = i16_window_threads(p->W[s], p->L[s]);
             p->launches[RFI_SCHED_PER_STREAM].push_back(l);
         }
     }
@@ -520,6 +556,10 @@ int plan_build(int elem, int32_t n, const int64_t* L, const int32_t* W, const fl
         soff += align64(L[s]);
         woff += nw;
     }
+    if (elem == 2)  // one run of generic items per int16 window size class
+        std::stable_sort(groups[0].begin(), groups[0].end(), [&](const Item& a, const Item& b) {
+            return i16_window_threads(W[a.stream], L[a.stream]) < i16_window_threads(W[b.stream], L[b.stream]);
+        });
     for (auto& g : groups) p->hitems.insert(p->hitems.end(), g.begin(), g.end());
     for (int m = 0; m < 3; ++m) {  // the statistics-only mode has no fused launch
         for (const Item& it : groups[0])

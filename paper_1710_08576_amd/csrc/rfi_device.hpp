@@ -150,6 +150,10 @@ __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0
 // mask alive until the end of the chain.
 __device__ __forceinline__ void pin_sgpr(uint32_t& x) { asm volatile("" : "+s"(x)); }
 
+// The same for a per-lane running sum, whose addends would otherwise be kept
+// until the sum is used.
+__device__ __forceinline__ void pin_vgpr(uint32_t& x) { asm volatile("" : "+v"(x)); }
+
 // ------------------------------------------------------------------------
 // Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
 // 64x64->128 multiplies; the key is bumped by the two Weyl constants after
@@ -303,6 +307,25 @@ __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b)
 {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(ushort2v, a),
                                                                   __builtin_bit_cast(ushort2v, b)));
+}
+
+// a - b of the two int16 halves, saturated.
+__device__ __forceinline__ uint32_t pk_subsat_i16(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(short2v, a),
+                                                                      __builtin_bit_cast(short2v, b)));
+}
+
+// Arithmetic right shift of both int16 halves by s (0..15).
+__device__ __forceinline__ uint32_t pk_ashr_i16(uint32_t a, int s)
+{
+    return __builtin_bit_cast(uint32_t, (short2v)(__builtin_bit_cast(short2v, a) >> (short2v){(short)s, (short)s}));
+}
+
+// c + the products of the unsigned 16-bit halves of a and b.
+__device__ __forceinline__ uint32_t udot2_u16(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_udot2(__builtin_bit_cast(ushort2v, a), __builtin_bit_cast(ushort2v, b), c, false);
 }
 
 __device__ __forceinline__ uint32_t pk_shl2_u16(uint32_t a)

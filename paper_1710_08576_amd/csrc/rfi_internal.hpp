@@ -134,14 +134,19 @@ hipError_t launch_i8_tiles(int cls, int modes, int tpw, const LaunchArgs& a, int
 hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int small_nt = 0);
 hipError_t launch_i8_fused(int modes, const LaunchArgs& a, int grid, hipStream_t s);
 hipError_t launch_i16_tiles(int cls, int modes, const LaunchArgs& a, int grid, hipStream_t s);
-hipError_t launch_i16_generic(const LaunchArgs& a, int grid, hipStream_t s);
+// nt: threads per window (64, 128, 256 or 512) if every window of the launch
+// spans at most 4 * nt 16-byte chunks of a padded stream that starts at
+// absolute index 0, used when the grid covers every item; 0: 256-thread
+// workgroups for windows of any kind.
+hipError_t launch_i16_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int nt = 0);
 hipError_t launch_i16_fused(const LaunchArgs& a, int grid, hipStream_t s);
 // One workgroup of the all-modes fused kernel (int8) or of the int16 fused
 // kernel with no items.  A kernel that needs private (scratch) memory has
 // it set up by the runtime at its first dispatch on a hardware queue, which
 // can hold that queue for milliseconds; a server runs this once per lane
 // when it is created, so that no block's latency pays for it.
-hipError_t warm_fused(int elem_size, bool persist, hipStream_t s);
+hipError_t warm_i8_fused(bool persist, hipStream_t s);
+hipError_t warm_i16_fused(bool persist, hipStream_t s);
 
 // Several outputs from one read (int8 tile items): output o uses the
 // descriptors desc[o] (its k and mode; offsets as a.streams) and the bases
@@ -218,8 +223,11 @@ hipError_t launch_carry(const CarryItem* items, int n_items, hipStream_t s);
 
 // Occupancy cap for the launches issued by this thread (0: none).
 void set_wg_per_cu(int n);
+int wg_per_cu();
 
 // Occupancy-derived persistent grid size for a kernel choice.
 int persistent_grid(int elem_size, int cls, int modes, bool fused);
+int i8_persistent_grid(int cls, int modes, bool fused);
+int i16_persistent_grid(int cls, int modes, bool fused);
 
 }  // namespace rfi

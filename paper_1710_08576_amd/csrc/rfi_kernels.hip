@@ -12,11 +12,11 @@
 //   d with C[m+d] - C[m-d-1] >= r + 1, i.e. the |x - m| histogram folded out
 //   of the same counts, so the samples are histogrammed once.  The flag
 //   count is N - (C[hi] - C[lo-1]) and needs no extra pass.
-// int16 windows (W 8192 tiles): a 12-bit coarse histogram of x + 32768 and
-//   a 4-bit fine digit give the median; the MAD is bracketed to 16 values
-//   from the same cumulative coarse counts and resolved by one filtered pass
-//   over |x - m|.  Other int16 windows: an 8+8-bit radix select over global
-//   memory (generic path).
+// int16 windows of up to 16384 samples stay in registers: a histogram of one
+//   value (or 2^s values, by the samples' spread) per slot around a sampled
+//   estimate of the median gives the median and the MAD, with a pass over
+//   the samples for the last s bits of each.  Longer ones, and windows with
+//   a carried head: an 8+8-bit radix select over global memory.
 // Replacement: the per-sample test |x - m| > t equals x < m - floor(t) or
 //   x > m + floor(t) because |x - m| is an integer, so after one binary32
 //   threshold per window everything is integer; int8 samples are clamped
@@ -28,35 +28,9 @@
 // Also here: the several-outputs tile kernel, the median-of-MAD passes
 //   (MAD gather, block counts, search, history, replacement) and the serving
 //   carry copy.
-#include "rfi_device.hpp"
-#include "rfi_internal.hpp"
+#include "rfi_item.hpp"
 
 namespace rfi {
-
-__constant__ int16_t c_q8[4096] = {
-#include "q8_table.inc"
-};
-
-struct WinParams {
-    int32_t lo;   // lowest unflagged value, m - floor(t) saturated
-    int32_t hi;   // highest unflagged value, m + floor(t) saturated
-    int32_t m;    // median
-    int32_t sq8;  // (int)(1.4826f * D * 256), Q8 robust sigma for noise
-};
-
-__device__ __forceinline__ uint64_t pick4(const Philox4x64& r, int i)
-{
-    const uint64_t a = (i & 1) ? r.w[1] : r.w[0];
-    const uint64_t b = (i & 1) ? r.w[3] : r.w[2];
-    return (i & 2) ? b : a;
-}
-
-// Robust sigma, threshold and the integer bounds of one window (Eq. (1)).
-__device__ __forceinline__ float threshold_of(int D, float k, float& sig)
-{
-    sig = __fmul_rn(1.4826f, (float)D);
-    return __fmul_rn(k, sig);
-}
 
 // ---------------------------------------------------------------------------
 // int8: selection from a 256-bin histogram owned by an aligned group of G
@@ -261,185 +235,6 @@ __device__ __forceinline__ void wide_params(const uint32_t* pc, int mb, int D, f
     s.mad = D;
     s.n_flagged = (uint32_t)n - inside;
     s.threshold = t;
-}
-
-// ---------------------------------------------------------------------------
-// Noise.  One Philox4x64-10 block (counter j >> 2) serves 4 consecutive
-// samples: sample j takes word j & 3 and indexes the Q8 table with its 12
-// most significant bits.
-// ---------------------------------------------------------------------------
-// 4 int8 noise samples starting at absolute index j0 (a multiple of 4):
-// byte c is sample j0 + c.
-__device__ __forceinline__ uint32_t noise_quad_i8(uint64_t j0, uint64_t seed, uint32_t key, int m,
-                                                  int sq8)
-{
-    const Philox4x64 r = philox4x64_10(j0 >> 2, seed, key);
-    uint32_t nb = 0;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int g = c_q8[(uint32_t)(r.w[c] >> 52)];
-        const int q = (sq8 * g + 32768) >> 16;  // |sq8 * g| < 2^31 for int8
-        nb |= ((uint32_t)min(max(m + q, -128), 127) & 0xFFu) << (8 * c);
-    }
-    return nb;
-}
-
-// The flagged 4-sample parts (one Philox block each) of a workgroup's tile
-// are pooled into one list, and one thread turns each entry into its
-// merged part (noise in the flagged samples), so the draws of a workgroup
-// occupy as few waves as the list needs and an isolated flagged sample
-// costs one block.  A lane holds 4 load slots of P parts (4 / P dwords
-// each); cf bit (slot * P + part) marks a part holding a flagged sample;
-// merged(wave, lane, slot, part, x) returns the merged part from the input
-// part x.  The list (1 KiB) and the parts (<= 2 KiB) live in LDS that the tile no
-// longer needs once its windows' parameters are known (its histograms):
-// nothing is written there before the first barrier below, which every
-// wave reaches only after its selection.  The per-wave counts have storage
-// of their own, as they are written before that barrier.
-struct NoiseScratch {
-    uint32_t* counts;  // [4]
-    uint32_t* list;    // [256]
-    uint4* data;       // [256], 16-byte aligned
-};
-constexpr int kNoiseAliasWords = 256 + 4 * 256;
-
-template <int P> struct NoisePart;
-template <> struct NoisePart<4> { using T = uint32_t; };
-template <> struct NoisePart<2> { using T = uint2; };
-
-// NT: threads of the workgroup (a multiple of 64, at most 256); the list
-// holds NT parts a round.
-template <int P, int NT = kBlock, class PartFn>
-__device__ __forceinline__ void pool_noise(uint32_t (&v)[16], uint32_t cf, const NoiseScratch& ns,
-                                           PartFn merged)
-{
-    using PartT = typename NoisePart<P>::T;
-    constexpr int WPP = 4 / P;  // dwords per part
-    constexpr int C = NT;       // parts per round
-    PartT* data = reinterpret_cast<PartT*>(ns.data);
-    const int lane = lane_id();
-    const int wave = (int)(threadIdx.x >> 6);
-    const uint32_t cnt = __popc(cf);
-    const uint32_t incl = group_incl_scan<64>(cnt);
-    if (lane == 63) ns.counts[wave] = incl;
-    __syncthreads();
-    int wbase = 0, F = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-        const int c = (int)ns.counts[w];
-        wbase += w < wave ? c : 0;
-        F += c;
-    }
-    const int base = wbase + (int)(incl - cnt);
-    // With no entries the loop below has no barrier: close the counts reads
-    // here so no wave reuses the scratch while another still reads it.
-    if (F == 0) __syncthreads();
-    for (int r0 = 0; r0 < F; r0 += C) {
-        int e = base - r0;
-#pragma unroll
-        for (int q = 0; q < 4 * P; ++q) {
-            if ((cf >> q) & 1u) {
-                if (e >= 0 && e < C) {
-                    ns.list[e] = (uint32_t)(wave << 8 | lane << 2 | (q / P)) | (uint32_t)(q % P) << 16;
-                    if constexpr (P == 4) data[e] = v[q];
-                    else data[e] = make_uint2(v[WPP * q], v[WPP * q + 1]);
-                }
-                ++e;
-            }
-        }
-        __syncthreads();
-        const int k = (int)threadIdx.x;
-        if (k < min(C, F - r0)) {
-            const uint32_t ent = ns.list[k];
-            data[k] = merged((int)((ent >> 8) & 3u), (int)((ent >> 2) & 63u), (int)(ent & 3u),
-                             (int)(ent >> 16), data[k]);
-        }
-        __syncthreads();
-        e = base - r0;
-#pragma unroll
-        for (int q = 0; q < 4 * P; ++q) {
-            if ((cf >> q) & 1u) {
-                if (e >= 0 && e < C) {
-                    if constexpr (P == 4) {
-                        v[q] = data[e];
-                    } else {
-                        const uint2 t = data[e];
-                        v[WPP * q] = t.x;
-                        v[WPP * q + 1] = t.y;
-                    }
-                }
-                ++e;
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// pool_noise without its first barrier: each wave reserves its slots with
-// one LDS atomic add on ns.counts[0], which the caller has zeroed before a
-// workgroup barrier that precedes the call (the waves' slots then follow
-// in the order of their adds).  The total is read after the barrier that
-// closes the list writes.  A wave writes its list entries and parts as soon
-// as it arrives, so the list and the parts must have storage of their own:
-// unlike pool_noise's, they cannot alias memory that another wave of the
-// workgroup may still be reading.
-template <int P, class PartFn>
-__device__ __forceinline__ void pool_noise_reserved(uint32_t (&v)[16], uint32_t cf, const NoiseScratch& ns,
-                                                    PartFn merged)
-{
-    using PartT = typename NoisePart<P>::T;
-    constexpr int WPP = 4 / P;
-    constexpr int C = kBlock;
-    PartT* data = reinterpret_cast<PartT*>(ns.data);
-    const int lane = lane_id();
-    const int wave = (int)(threadIdx.x >> 6);
-    const uint32_t cnt = __popc(cf);
-    const uint32_t incl = group_incl_scan<64>(cnt);
-    uint32_t wb = 0;
-    if (lane == 63 && incl) wb = atomicAdd(&ns.counts[0], incl);
-    wb = (uint32_t)__builtin_amdgcn_readlane((int)wb, 63);
-    const int base = (int)(wb + incl - cnt);
-    for (int r0 = 0;; r0 += C) {
-        int e = base - r0;
-#pragma unroll
-        for (int q = 0; q < 4 * P; ++q) {
-            if ((cf >> q) & 1u) {
-                if (e >= 0 && e < C) {
-                    ns.list[e] = (uint32_t)(wave << 8 | lane << 2 | (q / P)) | (uint32_t)(q % P) << 16;
-                    if constexpr (P == 4) data[e] = v[q];
-                    else data[e] = make_uint2(v[WPP * q], v[WPP * q + 1]);
-                }
-                ++e;
-            }
-        }
-        __syncthreads();
-        const int F = (int)ns.counts[0];  // every wave has added its count
-        const int k = (int)threadIdx.x;
-        if (k < min(C, F - r0)) {
-            const uint32_t ent = ns.list[k];
-            data[k] = merged((int)((ent >> 8) & 3u), (int)((ent >> 2) & 63u), (int)(ent & 3u),
-                             (int)(ent >> 16), data[k]);
-        }
-        __syncthreads();
-        e = base - r0;
-#pragma unroll
-        for (int q = 0; q < 4 * P; ++q) {
-            if ((cf >> q) & 1u) {
-                if (e >= 0 && e < C) {
-                    if constexpr (P == 4) {
-                        v[q] = data[e];
-                    } else {
-                        const uint2 t = data[e];
-                        v[WPP * q] = t.x;
-                        v[WPP * q + 1] = t.y;
-                    }
-                }
-                ++e;
-            }
-        }
-        __syncthreads();
-        if (r0 + C >= F) break;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -766,33 +561,13 @@ __device__ __forceinline__ TileStats i8_tile_any(const StreamView& d, int64_t fi
 // ---------------------------------------------------------------------------
 struct GenericSmem {
     union {
-        uint32_t hist[4 * 256];                            // int16 radix: four digit histograms
-        __align__(16) uint32_t whist[4 * kWaveHistWords];  // int8 register path: per-wave replicas
+        uint32_t hist[256];                                // two-pass path
+        __align__(16) uint32_t whist[4 * kWaveHistWords];  // register path: per-wave replicas
     };
     __align__(16) uint32_t tot[256];
     __align__(16) uint32_t pc[kPadC];
     WinParams prm;
-    int32_t sel[4];
-    uint32_t flagged;
 };
-
-template <typename T>
-__device__ __forceinline__ int load_logical(const StreamView& d, int64_t i)
-{
-    return i < d.head_len ? (int)gload(static_cast<const T*>(d.x_head) + i)
-                          : (int)gload(static_cast<const T*>(d.x) + (i - d.head_len));
-}
-
-// Noise sample for absolute index j (one Philox block per 4 samples).
-__device__ __forceinline__ int noise_sample(int64_t j, uint64_t seed, uint32_t key, int m, int sq8,
-                                            int vmin, int vmax)
-{
-    const Philox4x64 r = philox4x64_10((uint64_t)j >> 2, seed, key);
-    const uint64_t word = pick4(r, (int)(j & 3));
-    const int g = c_q8[(uint32_t)(word >> 52)];
-    const int64_t q = ((int64_t)sq8 * g + 32768) >> 16;
-    return (int)min(max((int64_t)m + q, (int64_t)vmin), (int64_t)vmax);
-}
 
 // Register path for a generic int8 window (zero, clip, statistics only,
 // and noise where the instance allows it) with no head segment, 16-byte
@@ -1024,626 +799,9 @@ struct GenericSmemN {
 };
 
 // ---------------------------------------------------------------------------
-// int16: radix select over two 8-bit digits.
-// ---------------------------------------------------------------------------
-// Find the bucket of rank `need` (1-based) in a 256-bin histogram whose bins
-// are spread over R replicas (bin b, replica r at b * R + r).  Every lane of
-// the wave gets the bucket and the count below it.  hw is left unchanged.
-template <int R>
-__device__ __forceinline__ void bucket_of(const uint32_t* hw, uint32_t need, int& bucket,
-                                          uint32_t& below)
-{
-    const int lane = lane_id();
-    uint32_t c[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t* src = hw + (lane * 4 + j) * R;
-        uint32_t s = 0;
-        if constexpr (R >= 4) {
-#pragma unroll
-            for (int r = 0; r < R; r += 4) {
-                const uint4 t = *reinterpret_cast<const uint4*>(src + r);
-                s += t.x + t.y + t.z + t.w;
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < R; ++r) s += src[r];
-        }
-        c[j] = s;
-    }
-#pragma unroll
-    for (int j = 1; j < 4; ++j) c[j] += c[j - 1];
-    const uint32_t incl = group_incl_scan<64>(c[3]);
-    const uint32_t excl = incl - c[3];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) c[j] += excl;
-    // Bins run in lane order and C is non-decreasing: the bucket holding
-    // rank `need` is the number of bins with C < need.
-    int nb = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) nb += group_count<64>(c[j] < need);
-    bucket = min(nb, 255);  // 255 only if the histogram held fewer than `need`
-    const int prev = bucket - 1;
-    const int pj = prev & 3;
-    const uint32_t mine = pj == 0 ? c[0] : pj == 1 ? c[1] : pj == 2 ? c[2] : c[3];
-    const uint32_t got = (uint32_t)__builtin_amdgcn_readlane((int)mine, max(prev, 0) >> 2);
-    below = prev >= 0 ? got : 0u;
-}
-
-__device__ __forceinline__ void zero_words(uint32_t* p, int words, int tid, int nthreads)
-{
-    for (int i = tid * 4; i < words; i += nthreads * 4)
-        *reinterpret_cast<uint4*>(p + i) = make_uint4(0, 0, 0, 0);
-}
-
-// 4 int16 noise samples starting at absolute index j0 (a multiple of 4):
-// dword k holds samples j0 + 2k (low half) and j0 + 2k + 1.
-__device__ __forceinline__ uint2 noise_quad_i16(uint64_t j0, uint64_t seed, uint32_t key, int m,
-                                                int sq8)
-{
-    const Philox4x64 r = philox4x64_10(j0 >> 2, seed, key);
-    uint32_t o[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        uint32_t nb = 0;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int g = c_q8[(uint32_t)(r.w[2 * k + b] >> 52)];
-            const int64_t q = ((int64_t)sq8 * g + 32768) >> 16;
-            const int val = (int)min(max((int64_t)m + q, (int64_t)-32768), (int64_t)32767);
-            nb |= ((uint32_t)val & 0xFFFFu) << (16 * b);
-        }
-        o[k] = nb;
-    }
-    return make_uint2(o[0], o[1]);
-}
-
-// int16 tile: radix selection with a 12-bit coarse digit and a 4-bit fine
-// digit.  Sample values of a noise-dominated window sit within a few
-// hundred of the median, so a coarse pass over the top 8 bits would send
-// almost every sample to a handful of bins and serialise the LDS atomics;
-// 4096 coarse bins (16 values each) spread them over hundreds.
-// One copy of the coarse histogram: with the swizzle below the atomics of a
-// Gaussian-like window spread over the banks well enough, and the smaller
-// footprint (16 KiB) leaves room for more workgroups per CU than two
-// copies did.
-constexpr int kI16Reps = 1;  // replicas of the coarse histogram (replica = lane % R)
-
-// Values of the full-resolution band of the fast path (one bin each).
-constexpr int kI16Band = 4096;
-
-struct I16TileSmem {
-    // radix path: coarse counts h[bin * R + rep]; band path: one bin per
-    // value of the band, then the bin of the samples above it
-    __align__(16) uint32_t h[kI16Band + 16];
-    uint32_t fine[2][16];  // fine digit inside the selected coarse bin
-    uint32_t part[4];      // per-wave totals of the block scan
-    int sel[2];            // selected coarse bin, count below it
-    uint32_t flagged;
-    uint32_t mad_below;    // samples with |x - m| below the MAD bracket
-    uint32_t est[4];       // band path: the waves' median estimates
-    uint32_t below;        // band path: samples below the band
-    // The noise pool (pool_noise_reserved) writes its list while other
-    // waves may still be searching the band's counts in h, so it has
-    // storage of its own (3 KiB; 8 workgroups per CU still fit).
-    uint32_t noise_counts[4];
-    __align__(16) uint32_t noise_list[256];
-    __align__(16) uint2 noise_data[256];
-    __device__ NoiseScratch noise()
-    {
-        return NoiseScratch{noise_counts, noise_list, reinterpret_cast<uint4*>(noise_data)};
-    }
-};
-
-// Physical word of histogram word w = bin * R + replica: the 16-byte
-// chunks of each 64-word block are permuted by XOR with bits 6..9 of w, so
-// that the selection's 16-byte row reads (lane t reads words 16Rt ..
-// 16R(t+1) - 1) fall in distinct banks for 16 consecutive lanes; without it
-// lanes 64 or 128 bytes apart meet in the same few banks.
-__device__ __forceinline__ uint32_t i16_hidx(uint32_t w) { return w ^ (((w >> 6) & 15u) << 2); }
-
-// Coarse bin holding rank `need` (1-based) of the 4096-bin histogram h, and
-// the count of samples in lower bins, for the whole workgroup.  Thread t
-// sums bins 16t .. 16t+15 over the replicas; ends with a barrier after
-// which every thread may read sm.sel, and h holds the inclusive cumulative
-// counts (h[bin] = samples in bins 0..bin; each thread rewrites only the
-// bins it read).
-__device__ __forceinline__ void i16_coarse_select(I16TileSmem& sm, uint32_t need)
-{
-    static_assert(kI16Reps == 1, "the cumulative counts are written one word per bin");
-    constexpr int R = kI16Reps;
-    const int tid = (int)threadIdx.x;
-    const int lane = lane_id(), wave = tid >> 6;
-    uint32_t c[16];
-#pragma unroll
-    for (int j = 0; j < 16 * R; j += 4) {
-        const uint4 t = *reinterpret_cast<const uint4*>(sm.h + i16_hidx((uint32_t)(tid * 16 * R + j)));
-        const uint32_t w[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int bin = (j + q) / R;
-            if ((j + q) % R == 0) c[bin] = w[q];
-            else c[bin] += w[q];
-        }
-    }
-#pragma unroll
-    for (int j = 1; j < 16; ++j) c[j] += c[j - 1];
-    const uint32_t incl = group_incl_scan<64>(c[15]);
-    if (lane == 63) sm.part[wave] = incl;
-    __syncthreads();
-    uint32_t off = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) off += w < wave ? sm.part[w] : 0u;
-    const uint32_t excl = off + incl - c[15];
-    if (excl < need && need <= excl + c[15]) {
-        int cnt = 0;
-        uint32_t below = excl;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const uint32_t C = excl + c[j];
-            cnt += C < need ? 1 : 0;
-            below = C < need ? C : below;
-        }
-        sm.sel[0] = tid * 16 + cnt;
-        sm.sel[1] = (int)below;
-    }
-#pragma unroll
-    for (int j = 0; j < 16; j += 4)
-        *reinterpret_cast<uint4*>(sm.h + i16_hidx((uint32_t)(tid * 16 + j))) =
-            make_uint4(excl + c[j], excl + c[j + 1], excl + c[j + 2], excl + c[j + 3]);
-    __syncthreads();
-}
-
-// Lower end of the MAD bracket from the cumulative coarse counts of x + 32768
-// (h after i16_coarse_select).  N(d) = #{|x - m| <= d} lies between the
-// counts of the coarse bins inside and touching [M - d, M + d] (M = m +
-// 32768); the smallest d whose touching count reaches `need` bounds the MAD
-// from below, and the MAD is at most 15 above it (every bin touching
-// [M - d, M + d] lies inside [M - d - 15, M + d + 15]).  A 64-way search by
-// each wave over d in [0, 65535] (three rounds); reads only, no barrier.
-__device__ __forceinline__ int i16_mad_lower(const I16TileSmem& sm, int M, uint32_t need)
-{
-    const int lane = lane_id();
-    int lo = 0, span = 65536;
-    while (span > 1) {
-        const int step = (span + 63) >> 6;
-        // sub-range `lane` is [lo + lane * step, lo + (lane + 1) * step - 1]
-        const int right = min(lo + (lane + 1) * step - 1, lo + span - 1);
-        bool ok = false;
-        if (lo + lane * step < lo + span) {
-            const int a = max(M - right, 0), c = min(M + right, 65535);
-            const uint32_t hiC = sm.h[i16_hidx((uint32_t)(c >> 4))];
-            const uint32_t loC = (a >> 4) > 0 ? sm.h[i16_hidx((uint32_t)((a >> 4) - 1))] : 0u;
-            ok = hiC - loC >= need;
-        }
-        const uint64_t b = __ballot(ok);  // the last sub-range always qualifies
-        const int f = (int)__builtin_ctzll(b);
-        const int nlo = lo + f * step;
-        span = min(step, lo + span - nlo);
-        lo = nlo;
-    }
-    return lo;
-}
-
-// Fine digit (0..15) holding rank `need` of the 16-bin histogram f; every
-// wave computes it (no barrier).
-__device__ __forceinline__ int i16_fine_select(const uint32_t* f, uint32_t need)
-{
-    const int lane = lane_id();
-    const uint32_t c = group_incl_scan<16>(lane < 16 ? f[lane & 15] : 0u);
-    const uint64_t lt = __ballot(lane < 16 && c < need);
-    return (int)__popcll(lt & 0xFFFFull);
-}
-
-__device__ __forceinline__ int lo16(uint32_t v) { return (int)(int16_t)(v & 0xFFFFu); }
-__device__ __forceinline__ int hi16(uint32_t v) { return (int)(int16_t)(v >> 16); }
-
-// int16 median and MAD by radix digits (the general path): a 12-bit coarse
-// digit histogram, the coarse bin of the median, a 4-bit fine digit inside
-// it, and the MAD from a 16-value bracket read off the coarse counts plus
-// one filtered pass over |x - m|.  v: the tile's samples (16 dwords per
-// lane); starts with a barrier (the scratch may still be read).
-__device__ void i16_select_radix(const uint32_t (&v)[16], I16TileSmem& sm, int& m_out, int& D_out)
-{
-    constexpr int W = 8192;
-    constexpr int R = kI16Reps;
-    const int lane = lane_id();
-    const int tid = (int)threadIdx.x;
-    __syncthreads();
-    zero_words(sm.h, 4096 * R, tid, kBlock);
-    if (tid < 8) reinterpret_cast<uint4*>(&sm.fine[0][0])[tid] = make_uint4(0, 0, 0, 0);
-    if (tid == 0) sm.mad_below = 0;
-    __syncthreads();
-
-    const uint32_t rep = (uint32_t)(lane & (R - 1));
-    // Coarse digit of x + 32768: bits 4..15.
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const uint32_t u = v[q] ^ 0x80008000u;
-        atomicAdd(sm.h + i16_hidx(((u >> 4) & 0xFFFu) * R + rep), 1u);
-        atomicAdd(sm.h + i16_hidx((u >> 20) * R + rep), 1u);
-        sched_fence();
-    }
-    __syncthreads();
-    constexpr uint32_t need = (W - 1) / 2 + 1;
-    i16_coarse_select(sm, need);
-    const int b1 = sm.sel[0];
-    const uint32_t below1 = (uint32_t)sm.sel[1];
-    // Fine digit inside coarse bin b1.  Words whose samples all lie outside
-    // the bin in every lane are skipped with one wave-uniform test.
-    const uint32_t B1 = ((uint32_t)b1 << 4) | ((uint32_t)b1 << 20);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const uint32_t u = v[q] ^ 0x80008000u;
-        const uint32_t t = u ^ B1;
-        const bool in0 = (t & 0xFFF0u) == 0, in1 = (t & 0xFFF00000u) == 0;
-        if (__ballot(in0 || in1) != 0) {
-            if (in0) atomicAdd(&sm.fine[0][u & 0xFu], 1u);
-            if (in1) atomicAdd(&sm.fine[0][(u >> 16) & 0xFu], 1u);
-        }
-    }
-    __syncthreads();
-    const int m = ((b1 << 4) | i16_fine_select(sm.fine[0], need - below1)) - 32768;
-    // MAD: bracket [dlo, dlo + 15] from the coarse counts of x, then the
-    // exact rank inside it from |x - m| of the samples (no second histogram
-    // over 4096 bins).  The samples below the bracket are counted from
-    // ballots (wave-uniform sums).
-    const int dlo = i16_mad_lower(sm, m + 32768, need);
-    const uint32_t m2 = rep_i16(m);
-    const uint32_t dlo2 = rep_i16(dlo);
-    uint32_t nbelow = 0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const uint32_t dq = pk_absdiff_i16(v[q], m2);
-        nbelow += (uint32_t)__popcll(__ballot((dq & 0xFFFFu) < (uint32_t)dlo)) +
-                  (uint32_t)__popcll(__ballot(dq < ((uint32_t)dlo << 16)));
-        pin_sgpr(nbelow);
-        const uint32_t r = pk_sub_u16(dq, dlo2);  // wraps when below
-        const bool in0 = (r & 0xFFFFu) < 16u, in1 = r < (16u << 16);
-        if (__ballot(in0 || in1) != 0) {
-            if (in0) atomicAdd(&sm.fine[1][r & 0xFu], 1u);
-            if (in1) atomicAdd(&sm.fine[1][(r >> 16) & 0xFu], 1u);
-        }
-    }
-    if (lane == 0) atomicAdd(&sm.mad_below, nbelow);
-    __syncthreads();
-    m_out = m;
-    D_out = dlo + i16_fine_select(sm.fine[1], need - sm.mad_below);
-}
-
-// int16 median and MAD from one full-resolution histogram (the fast path).
-// The band of kI16Band consecutive values of u = x + 32768 centred on an
-// estimate of the median (the lower median of the four waves' sample
-// medians, each over 64 of its samples) is counted at one bin per value,
-// samples above it in one extra bin, samples below it by ballots.  The
-// median is then read off the cumulative counts, and the MAD by a search
-// over d of N(d) = #{m - d <= u <= m + d}, also read off them.  Returns
-// false (every thread alike) when the median lies outside the band or the
-// MAD reaches past it; the caller then selects by radix digits.  Exact
-// either way: only where the counts are, not what they are, depends on
-// the estimate.
-__device__ bool i16_select_band(const uint32_t (&v)[16], I16TileSmem& sm, int& m_out, int& D_out)
-{
-    constexpr uint32_t need = 4096;  // rank floor((8192 - 1) / 2), 1-based
-    const int lane = lane_id();
-    const int tid = (int)threadIdx.x, wave = tid >> 6;
-    // This wave's estimate: the lower median of 64 of its samples (low
-    // halves of dwords 0, 5, 10, 15 in lane groups of 16), by a bitwise
-    // search on ballot counts.
-    const uint32_t pick = lane < 16 ? v[0] : lane < 32 ? v[5] : lane < 48 ? v[10] : v[15];
-    const uint32_t us = (pick ^ 0x8000u) & 0xFFFFu;
-    uint32_t est = 0;
-#pragma unroll
-    for (int b = 15; b >= 8; --b) {
-        const uint32_t t = est | (1u << b);
-        est = __popcll(__ballot(us < t)) < 32 ? t : est;
-    }
-    est += 128;  // the middle of the 256-value bucket holding the estimate
-    __syncthreads();  // the previous tile is done with the scratch
-    zero_words(sm.h, kI16Band + 16, tid, kBlock);
-    if (lane == 0) sm.est[wave] = est;
-    if (tid == 0) {
-        sm.below = 0;
-        sm.flagged = 0;  // added to once the tile is replaced
-        sm.noise_counts[0] = 0;  // the noise pool's slot reservations
-    }
-    __syncthreads();
-    uint32_t e[4] = {sm.est[0], sm.est[1], sm.est[2], sm.est[3]};
-    // lower median of the four estimates: the second smallest
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3 - i; ++j) {
-            const uint32_t lo = min(e[j], e[j + 1]), hi = max(e[j], e[j + 1]);
-            e[j] = lo;
-            e[j + 1] = hi;
-        }
-    const int base = min(max((int)e[1] - kI16Band / 2, 0), 65536 - kI16Band);
-    // u - base in each 16-bit half is x - (base - 32768) modulo 2^16.
-    const uint32_t xb = (uint32_t)(base ^ 0x8000) & 0xFFFFu;
-    const uint32_t xb2 = xb | (xb << 16);
-    const int xs = base - 32768;  // the band's first sample value
-    uint32_t below = 0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const uint32_t x = v[q];
-        // byte offset of each half's bin: (u - base) clamped to the extra
-        // bin kI16Band, times 4
-        const uint32_t t = pk_shl2_u16(pk_min_u16(pk_sub_u16(x, xb2), (uint32_t)kI16Band * 0x10001u));
-        atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(sm.h) + (t & 0xFFFFu)), 1u);
-        atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(sm.h) + (t >> 16)), 1u);
-        below += (uint32_t)__popcll(__ballot((int)(int16_t)(x & 0xFFFFu) < xs)) +
-                 (uint32_t)__popcll(__ballot((int32_t)x < xs * 65536));
-        pin_sgpr(below);
-        sched_fence();
-    }
-    if (lane == 0) atomicAdd(&sm.below, below);
-    __syncthreads();
-    const uint32_t bl = sm.below;
-    // Thread t scans bins 16t .. 16t + 15, and rewrites them as inclusive
-    // cumulative counts of the band (without the samples below it).
-    uint32_t c[16];
-#pragma unroll
-    for (int j = 0; j < 16; j += 4) {
-        const uint4 w = *reinterpret_cast<const uint4*>(sm.h + tid * 16 + j);
-        c[j] = w.x;
-        c[j + 1] = w.y;
-        c[j + 2] = w.z;
-        c[j + 3] = w.w;
-    }
-#pragma unroll
-    for (int j = 1; j < 16; ++j) c[j] += c[j - 1];
-    const uint32_t incl = group_incl_scan<64>(c[15]);
-    if (lane == 63) sm.part[wave] = incl;
-    __syncthreads();
-    uint32_t off = 0, inside = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        off += w < wave ? sm.part[w] : 0u;
-        inside += sm.part[w];
-    }
-    const uint32_t excl = bl + off + incl - c[15];
-    if (excl < need && need <= excl + c[15]) {
-        int cnt = 0;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) cnt += excl + c[j] < need ? 1 : 0;
-        sm.sel[0] = tid * 16 + cnt;
-    }
-#pragma unroll
-    for (int j = 0; j < 16; j += 4)
-        *reinterpret_cast<uint4*>(sm.h + tid * 16 + j) =
-            make_uint4(excl + c[j], excl + c[j + 1], excl + c[j + 2], excl + c[j + 3]);
-    __syncthreads();
-    if (bl >= need || bl + inside < need) return false;  // the median is outside the band
-    const int m = base + sm.sel[0];
-    // C(u') = #{u <= u'} for u' in [base - 1, base + kI16Band - 1]
-    auto C = [&](int u) -> uint32_t { return u < base ? bl : sm.h[u - base]; };
-    const int dwin = min(base + kI16Band - 1 - m, m - base);
-    if (C(m + dwin) - C(m - dwin - 1) < need) return false;  // the MAD reaches past the band
-    // smallest d in [0, dwin] with N(d) >= need: 64-way search, each lane
-    // testing the right end of its sub-range
-    int lo = 0, span = dwin + 1;
-    while (span > 1) {
-        const int step = (span + 63) >> 6;
-        const int right = min(lo + (lane + 1) * step - 1, lo + span - 1);
-        const bool ok = lo + lane * step < lo + span && C(m + right) - C(m - right - 1) >= need;
-        const int f = (int)__builtin_ctzll(__ballot(ok));  // the last sub-range always qualifies
-        const int nlo = lo + f * step;
-        span = min(step, lo + span - nlo);
-        lo = nlo;
-    }
-    m_out = m - 32768;
-    D_out = lo;
-    return true;
-}
-
-// W = 8192 int16 samples = 16 KiB = one window per workgroup tile.
-// MODES: bit m set if the launch has windows in mode m (one bit: the mode
-// is fixed at compile time).
-template <int MODES>
-__device__ void i16_tile_8192(const StreamView& d, int64_t first, uint64_t seed, I16TileSmem& sm)
-{
-    constexpr int W = 8192;
-    const int lane = lane_id();
-    const int tid = (int)threadIdx.x;
-    const int wbase = (tid >> 6) * 4096;  // bytes
-    const uint8_t* xt = reinterpret_cast<const uint8_t*>(static_cast<const int16_t*>(d.x) + first) + wbase + lane * 16;
-
-    uint32_t v[16];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint4 t = gload16_nt(xt + i * 1024);
-        v[4 * i] = t.x;
-        v[4 * i + 1] = t.y;
-        v[4 * i + 2] = t.z;
-        v[4 * i + 3] = t.w;
-    }
-    int m, D;
-    if (!i16_select_band(v, sm, m, D)) i16_select_radix(v, sm, m, D);
-
-    float sig;
-    const float t = threshold_of(D, d.k, sig);
-    const int T = (int)floorf(t);
-    const int lo = max(m - T, -32768), hi = min(m + T, 32767);
-    const uint32_t lo2 = rep_i16(lo), hi2 = rep_i16(hi);
-    const int sq8 = (int)__fmul_rn(sig, 256.0f);
-    const int mode = MODES == 1 ? RFI_MODE_ZERO : MODES == 2 ? RFI_MODE_CLIP : MODES == 4 ? RFI_MODE_NOISE : d.mode;
-    uint32_t nflag = 0;  // wave-uniform (ballot counts)
-    uint32_t cf = 0;     // bit 2i + h: dwords 2h, 2h + 1 of slot i hold a flagged sample
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            uint32_t any = 0;
-#pragma unroll
-            for (int j = 2 * h; j < 2 * h + 2; ++j) {
-                const int q = 4 * i + j;
-                const uint32_t x = v[q];
-                const uint32_t c = pk_clamp_i16(x, lo2, hi2);
-                const uint32_t diff = c ^ x;  // non-zero halves: flagged samples
-                nflag += (uint32_t)__popcll(__ballot((diff & 0xFFFFu) != 0)) +
-                         (uint32_t)__popcll(__ballot(diff > 0xFFFFu));
-                pin_sgpr(nflag);
-                if (mode == RFI_MODE_CLIP) v[q] = c;
-                else if (mode == RFI_MODE_ZERO) v[q] = x & ~pk_mask_nonzero_u16(diff);
-                else any |= diff;
-            }
-            if (mode == RFI_MODE_NOISE) cf |= (any != 0 ? 1u : 0u) << (2 * i + h);
-        }
-    }
-    if (mode == RFI_MODE_NOISE) {
-        const int64_t abs0 = d.abs_base + first;
-        const uint32_t key1 = d.key;
-        auto merged = [&](int wv, int ln, int slot, int part, uint2 x) -> uint2 {
-            // samples: 2048 per wave, 512 per load slot, 8 per lane, 4 per part
-            const int off = wv * 2048 + slot * 512 + ln * 8 + part * 4;
-            const uint2 nz = noise_quad_i16((uint64_t)(abs0 + off), seed, key1, m, sq8);
-            const uint32_t m0 = nonzero_half_mask(pk_clamp_i16(x.x, lo2, hi2) ^ x.x);
-            const uint32_t m1 = nonzero_half_mask(pk_clamp_i16(x.y, lo2, hi2) ^ x.y);
-            return make_uint2((x.x & ~m0) | (nz.x & m0), (x.y & ~m1) | (nz.y & m1));
-        };
-        pool_noise_reserved<2>(v, cf, sm.noise(), merged);
-    }
-    // The store address is formed here from a fresh copy of the thread
-    // index: kept live from the loads, its lane and wave offsets were spilled
-    // to private memory and reloaded right before the stores.
-    uint32_t t2 = (uint32_t)tid;
-    asm volatile("" : "+v"(t2));
-    uint8_t* yt = reinterpret_cast<uint8_t*>(static_cast<int16_t*>(d.y) + first) + (t2 >> 6) * 4096 + (t2 & 63) * 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        gstore16_nt(yt + i * 1024, make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]));
-    if (lane == 0) atomicAdd(&sm.flagged, nflag);
-    __syncthreads();
-    if (tid == 0 && d.stats) {
-        rfi_window_stats s;
-        s.median = m;
-        s.mad = D;
-        s.n_flagged = sm.flagged;
-        s.threshold = t;
-        d.stats[first / W] = s;
-    }
-}
-
-// Generic int16 window: radix passes over global memory.
-__device__ void i16_generic(const StreamView& d, int64_t w, uint64_t seed, GenericSmem& sm)
-{
-    const int W = d.window;
-    const int64_t a = w * (int64_t)W;
-    const int n = (int)min((int64_t)W, d.length - a);
-    const int tid = (int)threadIdx.x;
-    int16_t* y = static_cast<int16_t*>(d.y);
-    uint32_t* h = sm.hist;
-    const uint32_t need = (uint32_t)((n - 1) / 2 + 1);
-    __syncthreads();
-    for (int i = tid; i < 4 * 256; i += kBlock) h[i] = 0;
-    if (tid == 0) sm.flagged = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += kBlock)
-        atomicAdd(&h[(uint32_t)(load_logical<int16_t>(d, a + i) + 32768) >> 8], 1u);
-    __syncthreads();
-    if (tid < 64) {
-        int b;
-        uint32_t below;
-        bucket_of<1>(h, need, b, below);
-        if (tid == 0) {
-            sm.sel[0] = b;
-            sm.sel[1] = (int)below;
-        }
-    }
-    __syncthreads();
-    const int b1 = sm.sel[0];
-    const uint32_t below1 = (uint32_t)sm.sel[1];
-    for (int i = tid; i < n; i += kBlock) {
-        const uint32_t u = (uint32_t)(load_logical<int16_t>(d, a + i) + 32768);
-        if ((int)(u >> 8) == b1) atomicAdd(&h[256 + (u & 0xFFu)], 1u);
-    }
-    __syncthreads();
-    if (tid < 64) {
-        int b;
-        uint32_t below;
-        bucket_of<1>(h + 256, need - below1, b, below);
-        if (tid == 0) sm.sel[2] = ((b1 << 8) | b) - 32768;
-    }
-    __syncthreads();
-    const int m = sm.sel[2];
-    for (int i = tid; i < n; i += kBlock) {
-        const uint32_t dv = (uint32_t)abs(load_logical<int16_t>(d, a + i) - m);
-        atomicAdd(&h[512 + (dv >> 8)], 1u);
-    }
-    __syncthreads();
-    if (tid < 64) {
-        int b;
-        uint32_t below;
-        bucket_of<1>(h + 512, need, b, below);
-        if (tid == 0) {
-            sm.sel[0] = b;
-            sm.sel[1] = (int)below;
-        }
-    }
-    __syncthreads();
-    const int b3 = sm.sel[0];
-    const uint32_t below3 = (uint32_t)sm.sel[1];
-    for (int i = tid; i < n; i += kBlock) {
-        const uint32_t dv = (uint32_t)abs(load_logical<int16_t>(d, a + i) - m);
-        if ((int)(dv >> 8) == b3) atomicAdd(&h[768 + (dv & 0xFFu)], 1u);
-    }
-    __syncthreads();
-    if (tid < 64) {
-        int b;
-        uint32_t below;
-        bucket_of<1>(h + 768, need - below3, b, below);
-        if (tid == 0) sm.sel[3] = (b3 << 8) | b;
-    }
-    __syncthreads();
-    const int D = sm.sel[3];
-    float sig;
-    const float t = threshold_of(D, d.k, sig);
-    const int T = (int)floorf(t);
-    const int lo = max(m - T, -32768), hi = min(m + T, 32767);
-    const int sq8 = (int)__fmul_rn(sig, 256.0f);
-    uint32_t nflag = 0;
-    for (int i = tid; i < n; i += kBlock) {
-        const int x = load_logical<int16_t>(d, a + i);
-        int yv = x;
-        if (x < lo || x > hi) {
-            ++nflag;
-            if (d.mode == RFI_MODE_ZERO) yv = 0;
-            else if (d.mode == RFI_MODE_CLIP) yv = min(max(x, lo), hi);
-            else yv = noise_sample(d.abs_base + a + i, seed, d.key, m, sq8, -32768, 32767);
-        }
-        gstore(y + a + i, (int16_t)yv);
-    }
-    nflag = group_sum<64>(nflag);
-    if (lane_id() == 0) atomicAdd(&sm.flagged, nflag);
-    __syncthreads();
-    if (tid == 0 && d.stats) {
-        rfi_window_stats s;
-        s.median = m;
-        s.mad = D;
-        s.n_flagged = sm.flagged;
-        s.threshold = t;
-        d.stats[w] = s;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Kernels.  All loop over items with a grid stride, so the same kernel
 // serves one-workgroup-per-item launches and persistent launches.
 // ---------------------------------------------------------------------------
-// Runs body(item_index) for this workgroup's items.  PERSIST: grid-stride
-// loop; otherwise exactly one item per workgroup (no loop, so nothing is
-// kept live across items).
-template <bool PERSIST, class Body>
-__device__ __forceinline__ void for_items(const LaunchArgs& a, Body body)
-{
-    if constexpr (PERSIST) {
-        for (int64_t it = blockIdx.x; it < a.n_items; it += gridDim.x) body(it);
-    } else {
-        if ((int64_t)blockIdx.x < a.n_items) body((int64_t)blockIdx.x);
-    }
-}
-
 // One or two tiles per workgroup.  With two, the second tile's loads are
 // issued before the first tile is processed, so they are in flight while
 // the first tile's histogram, selection and replacement run.
@@ -1787,51 +945,6 @@ __global__ __launch_bounds__(kBlock, MODES == 7 ? 4 : 0) void k_i8_fused(LaunchA
             case 4: write_stats(i8_tile_any<8192, NS, MODES>(d, item.first, a.seed, sm.c4, v)); break;
             default: write_stats(i8_tile_any<16384, NS, MODES>(d, item.first, a.seed, sm.c5, v)); break;
         }
-    });
-}
-
-// One tile per workgroup: eight workgroups per CU (the noise variant holds
-// 63 VGPRs, against 68 and seven workgroups unbounded; 2.8 % faster in
-// noise mode, zero and clip unchanged).  The persistent loop keeps more
-// live (90-107 VGPRs): bounded the same way it spilled 88-120 bytes per
-// lane and ran 27-31 % slower, so it keeps the unbounded budget.  (The int8
-// tiles, bounded to 72 VGPRs, measured 2-3 % slower in noise mode.)
-template <bool PERSIST, int MODES>
-__global__ __launch_bounds__(kBlock, PERSIST ? 0 : 8) void k_i16_tiles(LaunchArgs a)
-{
-    __shared__ I16TileSmem sm;
-    for_items<PERSIST>(a, [&](int64_t it) {
-        const Item item = a.items[it];
-        const StreamView d = resolve(a.streams[item.stream], a);
-        i16_tile_8192<MODES>(d, item.first, a.seed, sm);
-    });
-}
-
-template <bool PERSIST>
-__global__ __launch_bounds__(kBlock) void k_i16_generic(LaunchArgs a)
-{
-    __shared__ GenericSmem sm;
-    for_items<PERSIST>(a, [&](int64_t it) {
-        const Item item = a.items[it];
-        const StreamView d = resolve(a.streams[item.stream], a);
-        i16_generic(d, item.first, a.seed, sm);
-    });
-}
-
-union I16FusedSmem {
-    I16TileSmem t;
-    GenericSmem g;
-};
-
-template <bool PERSIST>
-__global__ __launch_bounds__(kBlock) void k_i16_fused(LaunchArgs a)
-{
-    __shared__ I16FusedSmem sm;
-    for_items<PERSIST>(a, [&](int64_t it) {
-        const Item item = a.items[it];
-        const StreamView d = resolve(a.streams[item.stream], a);
-        if (item.kind == kItemGeneric) i16_generic(d, item.first, a.seed, sm.g);
-        else i16_tile_8192<7>(d, item.first, a.seed, sm.t);
     });
 }
 
@@ -2231,31 +1344,6 @@ __global__ __launch_bounds__(kBlock) void k_carry(const CarryItem* __restrict__ 
 // ---------------------------------------------------------------------------
 // Host launch wrappers.
 // ---------------------------------------------------------------------------
-// wg_per_cu > 0 caps the workgroups resident on one CU by padding each
-// workgroup's LDS allocation (160 KiB per CU), an occupancy limit the
-// autotuner can choose.
-static thread_local int t_wg_per_cu = 0;
-
-void set_wg_per_cu(int n) { t_wg_per_cu = n; }
-
-static hipError_t launch(void (*k)(LaunchArgs), const LaunchArgs& a, int grid, hipStream_t s)
-{
-    if (a.n_items <= 0) return hipSuccess;
-    if (grid < 1) grid = 1;
-    size_t dyn = 0;
-    if (t_wg_per_cu > 0) {
-        hipFuncAttributes fa;
-        if (hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(k)) == hipSuccess) {
-            const size_t want = (160u * 1024u) / (size_t)t_wg_per_cu;
-            if (want > fa.sharedSizeBytes) dyn = ((want - fa.sharedSizeBytes) + 255) & ~(size_t)255;
-            if (dyn + fa.sharedSizeBytes > 160u * 1024u) dyn = 0;
-        }
-    }
-    LaunchArgs args = a;
-    void* kargs[] = {&args};
-    return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3(grid), dim3(kBlock), kargs, dyn, s);
-}
-
 template <int MODES, bool PERSIST, int T>
 static void (*i8_tile_kernel_t(int cls))(LaunchArgs)
 {
@@ -2307,7 +1395,6 @@ hipError_t launch_i8_tiles(int cls, int modes, int tpw, const LaunchArgs& a, int
     if (!k) return hipErrorInvalidValue;
     return launch(k, a, persist ? grid : (int)((a.n_items + tpw - 1) / tpw), s);
 }
-#define RFI_PICK(K, a, grid) ((grid) < (a).n_items ? K<true> : K<false>)
 hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int small_nt)
 {
     const bool persist = grid < a.n_items;
@@ -2338,40 +1425,6 @@ static void (*i8_fused_kernel(int modes))(LaunchArgs)
 hipError_t launch_i8_fused(int modes, const LaunchArgs& a, int grid, hipStream_t s)
 {
     return launch(grid < a.n_items ? i8_fused_kernel<true>(modes) : i8_fused_kernel<false>(modes), a, grid, s);
-}
-template <bool PERSIST>
-static void (*i16_tile_kernel(int modes))(LaunchArgs)
-{
-    switch (modes) {
-        case 1: return k_i16_tiles<PERSIST, 1>;
-        case 2: return k_i16_tiles<PERSIST, 2>;
-        case 4: return k_i16_tiles<PERSIST, 4>;
-        default: return k_i16_tiles<PERSIST, 7>;
-    }
-}
-
-hipError_t launch_i16_tiles(int cls, int modes, const LaunchArgs& a, int grid, hipStream_t s)
-{
-    if (cls != 0) return hipErrorInvalidValue;
-    return launch(grid < a.n_items ? i16_tile_kernel<true>(modes) : i16_tile_kernel<false>(modes), a, grid, s);
-}
-hipError_t launch_i16_generic(const LaunchArgs& a, int grid, hipStream_t s)
-{
-    return launch(RFI_PICK(k_i16_generic, a, grid), a, grid, s);
-}
-hipError_t launch_i16_fused(const LaunchArgs& a, int grid, hipStream_t s)
-{
-    return launch(RFI_PICK(k_i16_fused, a, grid), a, grid, s);
-}
-#undef RFI_PICK
-
-hipError_t warm_fused(int elem_size, bool persist, hipStream_t s)
-{
-    LaunchArgs a{};  // no items: the workgroup returns at once
-    void (*k)(LaunchArgs) = elem_size == 1 ? (persist ? i8_fused_kernel<true>(7) : i8_fused_kernel<false>(7))
-                                           : (persist ? k_i16_fused<true> : k_i16_fused<false>);
-    void* kargs[] = {&a};
-    return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3(1), dim3(kBlock), kargs, 0, s);
 }
 
 __global__ __launch_bounds__(kBlock) void k_mom_apply(LaunchArgs a, const MomItem* __restrict__ items,
@@ -2476,26 +1529,19 @@ hipError_t launch_carry(const CarryItem* items, int n_items, hipStream_t s)
     return hipGetLastError();
 }
 
-int persistent_grid(int elem_size, int cls, int modes, bool fused)
+hipError_t warm_i8_fused(bool persist, hipStream_t s)
 {
-    void (*k)(LaunchArgs) = nullptr;
-    if (elem_size == 1) {
-        if (fused) k = i8_fused_kernel<true>(modes);
-        else if (cls < 0) k = (modes & 4) ? k_i8_generic<true, true> : k_i8_generic<true, false>;
-        else k = i8_tile_kernel(cls, modes, true, 1);
-    } else {
-        if (fused) k = k_i16_fused<true>;
-        else if (cls < 0) k = k_i16_generic<true>;
-        else k = i16_tile_kernel<true>(modes);
-    }
-    int per_cu = 0;
-    if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kBlock, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
-    return per_cu * cus;
+    LaunchArgs a{};  // no items: the workgroup returns at once
+    void (*k)(LaunchArgs) = persist ? i8_fused_kernel<true>(7) : i8_fused_kernel<false>(7);
+    void* kargs[] = {&a};
+    return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3(1), dim3(kBlock), kargs, 0, s);
+}
+
+int i8_persistent_grid(int cls, int modes, bool fused)
+{
+    if (fused) return resident_grid(i8_fused_kernel<true>(modes));
+    if (cls < 0) return resident_grid((modes & 4) ? k_i8_generic<true, true> : k_i8_generic<true, false>);
+    return resident_grid(i8_tile_kernel(cls, modes, true, 1));
 }
 
 }  // namespace rfi

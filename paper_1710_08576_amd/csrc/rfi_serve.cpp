@@ -578,9 +578,9 @@ int rfi_server_create(const rfi_server_config* cfg, rfi_server** out)
             if (e == hipSuccess) rc = ensure_slot(L.slots[s], kSlotPrealloc);
         }
         // The batch kernels this lane will launch, once, with no items.
-        if (e == hipSuccess && rc == RFI_OK) e = warm_fused(cfg->elem_size, false, L.s);
+        if (e == hipSuccess && rc == RFI_OK) e = (cfg->elem_size == 1 ? warm_i8_fused(false, L.s) : warm_i16_fused(false, L.s));
         if (e == hipSuccess && rc == RFI_OK && cfg->schedule == RFI_SCHED_FUSED_PERSIST)
-            e = warm_fused(cfg->elem_size, true, L.s);
+            e = (cfg->elem_size == 1 ? warm_i8_fused(true, L.s) : warm_i16_fused(true, L.s));
         if (e == hipSuccess && rc == RFI_OK) e = hipStreamSynchronize(L.s);
         if (e != hipSuccess || rc != RFI_OK) {
             rfi_server_destroy(srv);
@@ -715,7 +715,7 @@ int rfi_server_flush(rfi_server* srv, uint32_t stream_id, void* out_dev, rfi_win
     a.n_items = 1;
     a.seed = srv->cfg.seed;
     set_wg_per_cu(0);
-    hipError_t e = srv->cfg.elem_size == 1 ? launch_i8_generic(a, 1 << st.mode, 1, L.s) : launch_i16_generic(a, 1, L.s);
+    hipError_t e = srv->cfg.elem_size == 1 ? launch_i8_generic(a, 1 << st.mode, 1, L.s) : launch_i16_generic(a, 1 << st.mode, 1, L.s);
     ++srv->n_launches;
     if (e == hipSuccess) e = hipStreamSynchronize(L.s);
     if (e != hipSuccess) return hip_fail(e);

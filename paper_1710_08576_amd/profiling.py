@@ -35,7 +35,7 @@ import os
 import statistics
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ["csrc/rfi_kernels.hip", "csrc/rfi_device.hpp", "csrc/rfi_internal.hpp",
+KERNEL_SOURCES = ["csrc/rfi_kernels.hip", "csrc/rfi_i16.hip", "csrc/rfi_item.hpp", "csrc/rfi_device.hpp", "csrc/rfi_internal.hpp",
                   "csrc/q8_table.inc"]
 
 
