@@ -253,7 +253,9 @@ int rfi_mad_filter_noalloc(const int8_t* x, int8_t* y, int32_t n_streams, const 
 typedef struct rfi_plan rfi_plan;
 
 typedef enum {
-    RFI_SCHED_AUTO = 0,        /* autotuned table, else RFI_SCHED_SPLIT         */
+    RFI_SCHED_AUTO = 0,        /* autotuned table, else RFI_SCHED_SPLIT, merged
+                                  into one launch of every item where that
+                                  is faster                               */
     RFI_SCHED_SPLIT = 1,       /* one launch per window class, one WG per tile  */
     RFI_SCHED_SPLIT_PERSIST = 2, /* one persistent launch per window class     */
     RFI_SCHED_FUSED = 3,       /* one launch for every class, one WG per item   */

@@ -72,7 +72,9 @@ struct TuneEntry {
 // or above the uncapped rate for every int8 window class and mode (fewer
 // resident workgroups contend less for LDS banks and the L2).
 constexpr int kDefaultWgPerCu = 8;
-constexpr TuneEntry kUntuned = {RFI_SCHED_SPLIT, 1, kDefaultWgPerCu, 0.0f};
+// RFI_SCHED_AUTO here: nothing is tuned, AUTO plans use their own launch list
+// (see untuned_launches).
+constexpr TuneEntry kUntuned = {RFI_SCHED_AUTO, 1, kDefaultWgPerCu, 0.0f};
 
 static std::mutex g_tune_mu;
 static std::map<std::string, TuneEntry> g_tune;  // key: "<arch>/<signature hex>"
@@ -358,6 +360,27 @@ static int i16_window_threads(int32_t W, int64_t L)
     return chunks <= 256 ? 64 : chunks <= 512 ? 128 : chunks <= 1024 ? 256 : chunks <= 2048 ? 512 : 0;
 }
 
+// Whose launches a plan takes that nothing was tuned for: SPLIT's, unless
+// those are several and one launch of the fused kernel beats them.  A launch
+// more costs 3 us of a small batch and 5 us of a large one, which drains
+// before the next; the fused kernel's occupancy costs less than that at
+// every size measured (int8, microseconds, SPLIT against one launch: one
+// stream of 20000 samples 10.3 / 7.7; 60 of 10^6, W 4096 with tails, clip
+// 28.7 / 24.1, noise 38.1 / 31.7; 60 of 4 x 10^6 83.3 / 79.2 and 102.9 /
+// 99.9, every class and mode mixed 178.6 / 103.1).  Not with windows that
+// are no tile class: SPLIT has kernels of fewer threads for them (60 of
+// 10^6, W 5000, noise 44.7 / 164).  int16 tiles run at the copy rate by
+// themselves: one launch up to 8192 items (60 of 10^6 49.1 / 46.1, noise
+// 55.7 / 55.0; 60 of 2 x 10^6, noise 96.8 / 101.9).
+static int untuned_launches(const rfi_plan* p)
+{
+    if (p->launches[RFI_SCHED_SPLIT].size() < 2) return RFI_SCHED_SPLIT;
+    for (int s = 0; s < p->n; ++s)
+        if (tile_class(p->elem, p->W[s]) < 0) return RFI_SCHED_SPLIT;
+    if (p->elem == 2 && p->hitems.size() > 8192) return RFI_SCHED_SPLIT;
+    return RFI_SCHED_ONE_LAUNCH;
+}
+
 static void build_launches(rfi_plan* p)
 {
     const int elem = p->elem;
@@ -501,7 +524,7 @@ static void build_launches(rfi_plan* p)
         for (size_t i = 0; i < fs.size(); ++i) fs[i].queue = (int)(i % 4);
         p->launches[RFI_SCHED_FUSED_CONCURRENT] = fs;
     }
-    p->launches[RFI_SCHED_AUTO] = p->launches[RFI_SCHED_SPLIT];
+    p->launches[RFI_SCHED_AUTO] = p->launches[untuned_launches(p)];
 }
 
 int plan_build(int elem, int32_t n, const int64_t* L, const int32_t* W, const float* K,
@@ -645,6 +668,15 @@ void plan_free(rfi_plan* p)
 static int effective_schedule(const rfi_plan* p)
 {
     if (p->schedule != RFI_SCHED_AUTO) return p->schedule;
+    const int s = tuned(p->tune_key).sched;
+    return s == RFI_SCHED_AUTO ? RFI_SCHED_SPLIT : s;
+}
+
+// The launch list that an execute takes: the effective schedule's, or an
+// untuned plan's own.
+static int launch_list(const rfi_plan* p)
+{
+    if (p->schedule != RFI_SCHED_AUTO) return p->schedule;
     return tuned(p->tune_key).sched;
 }
 
@@ -685,7 +717,7 @@ static hipError_t run_schedule(rfi_plan* p, const std::vector<PlanLaunch>& ls, c
 int plan_execute(rfi_plan* p, const void* x, void* y, rfi_window_stats* st, hipStream_t s,
                  int sched_override)
 {
-    const int sched = sched_override >= 0 ? sched_override : effective_schedule(p);
+    const int sched = sched_override >= 0 ? sched_override : launch_list(p);
     LaunchArgs base;
     std::memset(&base, 0, sizeof(base));
     base.streams = p->ddesc;
@@ -860,7 +892,7 @@ int rfi_plan_info(const rfi_plan* plan, int32_t* n_launches, int64_t* n_windows,
                   int64_t* n_generic)
 {
     if (!plan) return RFI_ERR_INVALID;
-    if (n_launches) *n_launches = (int32_t)plan->launches[effective_schedule(plan)].size();
+    if (n_launches) *n_launches = (int32_t)plan->launches[launch_list(plan)].size();
     if (n_windows) *n_windows = plan->n_windows;
     if (n_tiles) *n_tiles = plan->n_tiles;
     if (n_generic) *n_generic = plan->n_generic;

@@ -731,7 +731,7 @@ __device__ __forceinline__ void i16_generic_any(const StreamView& d, int64_t w, 
 }
 
 template <bool PERSIST>
-__global__ __launch_bounds__(kBlock) void k_i16_generic(LaunchArgs a)
+__global__ __launch_bounds__(kBlock, PERSIST ? 0 : 7) void k_i16_generic(LaunchArgs a)
 {
     __shared__ I16FusedSmem sm;
     for_items<PERSIST>(a, [&](int64_t it) {
@@ -742,18 +742,14 @@ __global__ __launch_bounds__(kBlock) void k_i16_generic(LaunchArgs a)
 }
 
 template <bool PERSIST>
-__global__ __launch_bounds__(kBlock) void k_i16_fused(LaunchArgs a)
+__global__ __launch_bounds__(kBlock, PERSIST ? 0 : 7) void k_i16_fused(LaunchArgs a)
 {
     __shared__ I16FusedSmem sm;
     for_items<PERSIST>(a, [&](int64_t it) {
         const Item item = a.items[it];
         const StreamView d = resolve(a.streams[item.stream], a);
-        if (item.kind == kItemGeneric) {
-            i16_generic_any(d, item.first, a.seed, sm);
-        } else {
-            i16_window<kBlock, 7, true>(d, item.first / 8192, item.first, 8192, a.seed, (int)threadIdx.x, sm.t);
-            if constexpr (PERSIST) __syncthreads();
-        }
+        // a tile is one window: the same code serves both kinds
+        i16_generic_any(d, item.kind == kItemGeneric ? item.first : item.first / 8192, a.seed, sm);
     });
 }
 
