@@ -747,6 +747,10 @@ __global__ __launch_bounds__(kBlock, PERSIST ? 0 : 7) void k_i16_fused(LaunchArg
     __shared__ I16FusedSmem sm;
     for_items<PERSIST>(a, [&](int64_t it) {
         const Item item = a.items[it];
+        if (item.kind == kItemCarry) {
+            carry_copy(a.carries[item.stream]);
+            return;
+        }
         const StreamView d = resolve(a.streams[item.stream], a);
         // a tile is one window: the same code serves both kinds
         i16_generic_any(d, item.kind == kItemGeneric ? item.first : item.first / 8192, a.seed, sm);

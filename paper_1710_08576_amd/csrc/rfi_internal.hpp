@@ -62,8 +62,11 @@ struct Item {
     int32_t kind;
     int64_t first;
 };
+//   kind == kItemCarry:   a serving carry update (fused kernels); `stream` =
+//                         its index in LaunchArgs::carries.
 constexpr int32_t kItemTile = 0;
 constexpr int32_t kItemGeneric = 1;
+constexpr int32_t kItemCarry = 2;
 
 // Window classes with a register-resident tile path.
 //   int8:  512, 1024, 2048, 4096 (one wave per window or less),
@@ -90,6 +93,19 @@ constexpr int kI16Classes = 1;
 // the median-of-MAD path's first pass.
 constexpr int32_t kModeStats = 3;
 
+// Serving carry update: copies logical elements [from, from + count) of the
+// concatenation (head[0 .. head_len), body[...]) to dst.  Addresses are
+// absolute device addresses.
+struct CarryItem {
+    uint64_t head;
+    uint64_t body;
+    uint64_t dst;
+    int32_t head_len;
+    int32_t from;
+    int32_t count;
+    int32_t elem;  // 1 or 2 bytes
+};
+
 // Kernel launch requests issued by the host runtime.
 struct LaunchArgs {
     const StreamDesc* streams;
@@ -101,6 +117,7 @@ struct LaunchArgs {
     uint64_t stats_base;  // added to StreamDesc::stats_off
     int32_t no_stats;     // 1: write no statistics at all
     int32_t pad;
+    const CarryItem* carries;  // of kItemCarry items
 };
 
 __host__ __device__ inline StreamView resolve(const StreamDesc& d, const LaunchArgs& a)
@@ -207,19 +224,8 @@ hipError_t launch_mom_apply(const LaunchArgs& a, const MomItem* items, int64_t n
 hipError_t launch_mom_gather(const rfi_window_stats* stats, int64_t total_windows, uint8_t* mad,
                              hipStream_t s);
 
-// Serving carry update: copies logical elements [from, from + count) of the
-// concatenation (head[0 .. head_len), body[...]) to dst.  Addresses are
-// absolute device addresses.
-struct CarryItem {
-    uint64_t head;
-    uint64_t body;
-    uint64_t dst;
-    int32_t head_len;
-    int32_t from;
-    int32_t count;
-    int32_t elem;  // 1 or 2 bytes
-};
-hipError_t launch_carry(const CarryItem* items, int n_items, hipStream_t s);
+// Copies n16 16-byte units from pinned host memory to device memory.
+hipError_t launch_stage(void* dst, const void* src_host, int64_t n16, hipStream_t s);
 
 // Occupancy cap for the launches issued by this thread (0: none).
 void set_wg_per_cu(int n);

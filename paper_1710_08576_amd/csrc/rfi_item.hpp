@@ -245,6 +245,28 @@ __device__ __forceinline__ int noise_sample(int64_t j, uint64_t seed, uint32_t k
     return (int)min(max((int64_t)m + q, (int64_t)vmin), (int64_t)vmax);
 }
 
+// A carry update by one workgroup.  The usual carry is one run of whole
+// 16-byte units (a block's tail).
+__device__ __forceinline__ void carry_copy(const CarryItem& c)
+{
+    const uint64_t bytes = (uint64_t)c.count * (uint64_t)c.elem;
+    if (c.from == 0 && c.count <= c.head_len && ((c.head | c.dst | bytes) & 15u) == 0) {
+        for (uint64_t i = threadIdx.x; i < bytes / 16; i += kBlock)
+            gstore16(reinterpret_cast<void*>(c.dst + 16 * i), gload16(reinterpret_cast<const void*>(c.head + 16 * i)));
+        return;
+    }
+    for (int i = (int)threadIdx.x; i < c.count; i += kBlock) {
+        const int j = c.from + i;
+        const uint64_t src = j < c.head_len ? c.head + (uint64_t)j * c.elem
+                                            : c.body + (uint64_t)(j - c.head_len) * c.elem;
+        const uint64_t dst = c.dst + (uint64_t)i * c.elem;
+        if (c.elem == 1)
+            gstore(reinterpret_cast<uint8_t*>(dst), gload(reinterpret_cast<const uint8_t*>(src)));
+        else
+            gstore(reinterpret_cast<uint16_t*>(dst), gload(reinterpret_cast<const uint16_t*>(src)));
+    }
+}
+
 // Runs body(item_index) for this workgroup's items.  PERSIST: grid-stride
 // loop; otherwise exactly one item per workgroup (no loop, so nothing is
 // kept live across items).

@@ -583,10 +583,13 @@ constexpr int kGenericRegMin = 512;
 // NOISE: noise-mode windows qualify too, when each dword of the stream holds
 // one Philox block (absolute index of the stream's first sample a multiple
 // of 4).
-template <bool NOISE, int NT = kBlock>
+// HEAD: so do windows with a head segment of whole chunks (a serving
+// stream's carry, whose blocks start and end on 16 samples).
+template <bool NOISE, int NT, bool HEAD>
 __device__ __forceinline__ bool i8_generic_reg_ok(const StreamView& d, int64_t a, int n)
 {
-    if (d.head_len != 0 || n < kGenericRegMin) return false;
+    if (n < kGenericRegMin) return false;
+    if (d.head_len != 0 && (!HEAD || ((d.head_len | (uint32_t)(uintptr_t)d.x_head) & 15u) != 0)) return false;
     if (d.mode == RFI_MODE_NOISE && (!NOISE || (d.abs_base & 3) != 0)) return false;
     if (((uintptr_t)d.x | (uintptr_t)d.y) & 15u) return false;
     // the last chunk may reach up to 15 bytes past the window: inside the
@@ -599,7 +602,7 @@ __device__ __forceinline__ uint32_t byte_of(uint32_t v, int b) { return (v >> (8
 
 // NT: threads of the workgroup (256, or 64 / 128 for launches whose windows
 // span at most 256 / 512 chunks, so that more windows are in flight per CU).
-template <bool NOISE, int NT, class Smem>
+template <bool NOISE, int NT, bool HEAD, class Smem>
 __device__ void i8_generic_reg(const StreamView& d, int64_t w, int64_t a, int n, uint64_t seed, Smem& sm)
 {
     const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
@@ -612,7 +615,11 @@ __device__ void i8_generic_reg(const StreamView& d, int64_t w, int64_t a, int n,
     for (int k = 0; k < 4; ++k) {
         const int64_t c = tid + k * NT;
         uint4 t = make_uint4(0, 0, 0, 0);
-        if (c < nch) t = gload16_nt(xb + (c0 + c) * 16);
+        if (c < nch) {
+            const int64_t at = (c0 + c) * 16;
+            t = gload16_nt(HEAD ? (at < d.head_len ? static_cast<const uint8_t*>(d.x_head) + at : xb + (at - d.head_len))
+                                : xb + at);
+        }
         v[4 * k] = t.x;
         v[4 * k + 1] = t.y;
         v[4 * k + 2] = t.z;
@@ -740,14 +747,15 @@ __device__ void i8_generic_reg(const StreamView& d, int64_t w, int64_t a, int n,
 // REG: zero/clip windows may take the register path; REG_NOISE: noise
 // windows too (kept out of the fused kernels, whose register budget the
 // inlined draw would raise).
-template <bool REG = true, bool REG_NOISE = false, int NT = kBlock, class Smem = GenericSmem>
+// HEAD: the launch may hold windows with a head segment.
+template <bool REG = true, bool REG_NOISE = false, int NT = kBlock, bool HEAD = NT == kBlock, class Smem = GenericSmem>
 __device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, Smem& sm)
 {
     const int W = d.window;
     const int64_t a = w * (int64_t)W;
     const int n = (int)min((int64_t)W, d.length - a);
-    if (REG && i8_generic_reg_ok<REG_NOISE, NT>(d, a, n)) {
-        i8_generic_reg<REG_NOISE, NT>(d, w, a, n, seed, sm);
+    if (REG && i8_generic_reg_ok<REG_NOISE, NT, HEAD>(d, a, n)) {
+        i8_generic_reg<REG_NOISE, NT, HEAD>(d, w, a, n, seed, sm);
         return;
     }
     const int tid = (int)threadIdx.x;
@@ -920,6 +928,10 @@ __global__ __launch_bounds__(kBlock, MODES == 7 ? 4 : 0) void k_i8_fused(LaunchA
     __shared__ I8FusedSmem<NS> sm;
     for_items<PERSIST>(a, [&](int64_t it) {
         const Item item = a.items[it];
+        if (item.kind == kItemCarry) {
+            carry_copy(a.carries[item.stream]);
+            return;
+        }
         if constexpr (MODES == 7) {
             if (item.kind == kItemGeneric) {
                 i8_generic_item<true>(a.streams + item.stream, a.x_base, a.y_base, a.stats_base, a.no_stats,
@@ -1326,19 +1338,14 @@ __device__ __forceinline__ void mom_apply_item(const LaunchArgs& a, const MomIte
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_carry(const CarryItem* __restrict__ items)
+// One 16-byte unit per thread from pinned host memory: tables of a few tens
+// of KiB reach the device in about 3 us, ordered before the next kernel of
+// the stream without the signals a DMA copy waits for (7 us and a gap of 17
+// before the kernel that follows it).
+__global__ __launch_bounds__(kBlock) void k_stage(void* dst, const void* src, int64_t n16)
 {
-    const CarryItem c = items[blockIdx.x];
-    for (int i = (int)threadIdx.x; i < c.count; i += kBlock) {
-        const int j = c.from + i;
-        const uint64_t src = j < c.head_len ? c.head + (uint64_t)j * c.elem
-                                            : c.body + (uint64_t)(j - c.head_len) * c.elem;
-        const uint64_t dst = c.dst + (uint64_t)i * c.elem;
-        if (c.elem == 1)
-            gstore(reinterpret_cast<uint8_t*>(dst), gload(reinterpret_cast<const uint8_t*>(src)));
-        else
-            gstore(reinterpret_cast<uint16_t*>(dst), gload(reinterpret_cast<const uint16_t*>(src)));
-    }
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n16) gstore16(static_cast<uint8_t*>(dst) + 16 * i, gload16(static_cast<const uint8_t*>(src) + 16 * i));
 }
 
 // ---------------------------------------------------------------------------
@@ -1522,10 +1529,10 @@ hipError_t launch_mom_apply(const LaunchArgs& a, const MomItem* items, int64_t n
     return hipGetLastError();
 }
 
-hipError_t launch_carry(const CarryItem* items, int n_items, hipStream_t s)
+hipError_t launch_stage(void* dst, const void* src_host, int64_t n16, hipStream_t s)
 {
-    if (n_items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_carry, dim3(n_items), dim3(kBlock), 0, s, items);
+    if (n16 <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_stage, dim3((unsigned)((n16 + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, dst, src_host, n16);
     return hipGetLastError();
 }
 

@@ -9,10 +9,11 @@
 // Each stream is bound to one "lane" (a HIP stream).  A lane dispatches
 // batches: admitted blocks of its streams, taken round-robin in each
 // stream's order, up to max_batch blocks, as one fused kernel launch over a
-// work table plus one carry-update launch.  Within a batch, the head window
-// of a stream's next block reads its carry straight from the previous
-// block's buffer; the carry left at the end of the batch is copied to the
-// stream's device carry buffer by the carry-update launch, so the carry
+// work table (which a small kernel copies from pinned memory first).  Within
+// a batch, the head window of a stream's next block reads its carry straight
+// from the previous block's buffer; the carry left at the end of the batch is
+// copied to the stream's device carry buffer by an item of the same launch
+// (to the buffer that the batch does not read), so the carry
 // chain across batches follows HIP stream order.  A lane keeps
 // up to kSlotsPerLane batches in flight; blocks that arrive meanwhile wait
 // for the next batch of their lane (continuous batching), so the work of
@@ -106,7 +107,7 @@ size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 // stream's device carry buffer (at batch start) or at the end of a block
 // already in the batch.  `open` turns false once a block leaves a carry
 // that spans the old carry and that whole block; that carry goes through
-// the carry-update launch, so later blocks of the stream wait for the next
+// a carry item, so later blocks of the stream wait for the next
 // batch.
 struct Chain {
     uint64_t src = 0;
@@ -131,8 +132,14 @@ struct Lane {
     std::vector<uint32_t> members;
     // Work tables of the batch being built (kept to reuse their storage).
     std::vector<StreamDesc> descs;
-    std::vector<Item> items;
+    // Items by kind: windows of the generic path, then tiles, noise tiles
+    // first and narrow classes first in each, so that the launch, which
+    // hands them out in order, starts its longest items first.
+    std::vector<Item> generic;
+    std::vector<Item> tiles[2][kI8Classes];
+    std::vector<Item> items;  // all of them, carry updates among them
     std::vector<CarryItem> carries;
+    int modes = 0;            // bit m: some block of the batch has mode m
     std::vector<uint64_t> batch;
     std::vector<Chain> chains;
     std::vector<SavedState> saved;  // members' state before the batch
@@ -203,14 +210,14 @@ int upload(Slot& sl, const std::vector<StreamDesc>& descs, const std::vector<Ite
 {
     const size_t bd = descs.size() * sizeof(StreamDesc), bi = items.size() * sizeof(Item),
                  bc = carries.size() * sizeof(CarryItem);
-    const size_t oi = align256(bd), oc = oi + align256(bi), total = oc + bc;
+    const size_t oi = align256(bd), oc = oi + align256(bi), total = oc + align256(bc);
     int rc = ensure_slot(sl, total);
     if (rc != RFI_OK) return rc;
     if (bd) std::memcpy(sl.h_stage, descs.data(), bd);
     if (bi) std::memcpy(sl.h_stage + oi, items.data(), bi);
     if (bc) std::memcpy(sl.h_stage + oc, carries.data(), bc);
     if (total) {
-        hipError_t e = hipMemcpyAsync(sl.d_buf, sl.h_stage, total, hipMemcpyHostToDevice, s);
+        hipError_t e = launch_stage(sl.d_buf, sl.h_stage, (int64_t)(total / 16), s);
         if (e != hipSuccess) return hip_fail(e);
     }
     *dd = reinterpret_cast<StreamDesc*>(sl.d_buf);
@@ -240,6 +247,7 @@ void plan_block(rfi_server* srv, SrvStream& st, uint32_t sid, TicketRec& t, Chai
         return d;
     };
     if (nw > 0) {
+        L.modes |= 1 << st.mode;
         const int64_t h = c > 0 ? 1 : 0;
         if (h) {
             StreamDesc d = base_desc();
@@ -250,7 +258,7 @@ void plan_block(rfi_server* srv, SrvStream& st, uint32_t sid, TicketRec& t, Chai
             d.y_off = (uint64_t)(uintptr_t)t.out;
             d.stats_off = (uint64_t)(uintptr_t)t.stats;
             d.abs_base = st.next_abs;
-            L.items.push_back(Item{(int32_t)L.descs.size(), kItemGeneric, 0});
+            L.generic.push_back(Item{(int32_t)L.descs.size(), kItemGeneric, 0});
             L.descs.push_back(d);
         }
         const int64_t nb = nw - h;
@@ -272,10 +280,11 @@ void plan_block(rfi_server* srv, SrvStream& st, uint32_t sid, TicketRec& t, Chai
             // the tile's first sample on, so that sample must start a block.
             if (cls >= 0 && (x % 16) == 0 && (y % 16) == 0 && (d.abs_base % 4) == 0) {
                 const int64_t nt = (nb * W) / tile_samples;
-                for (int64_t i = 0; i < nt; ++i) L.items.push_back(Item{ds, kItemTile, i * tile_samples});
+                std::vector<Item>& tiles = L.tiles[st.mode == RFI_MODE_NOISE ? 0 : 1][cls];
+                for (int64_t i = 0; i < nt; ++i) tiles.push_back(Item{ds, kItemTile, i * tile_samples});
                 first_generic = nt * (tile_samples / W);
             }
-            for (int64_t w = first_generic; w < nb; ++w) L.items.push_back(Item{ds, kItemGeneric, w});
+            for (int64_t w = first_generic; w < nb; ++w) L.generic.push_back(Item{ds, kItemGeneric, w});
         }
     }
     if (newc > 0 && nw == 0 && c > 0) {
@@ -312,7 +321,7 @@ void plan_block(rfi_server* srv, SrvStream& st, uint32_t sid, TicketRec& t, Chai
 }
 
 // End of a stream's part of a batch: a carry left inside a block is copied
-// to the stream's other carry buffer (after the batch's filter launch).
+// to the stream's other carry buffer.
 void close_chain(rfi_server* srv, SrvStream& st, Chain& ch, Lane& L)
 {
     if (ch.len > 0 && !ch.in_buffer) {
@@ -343,7 +352,11 @@ int dispatch_lane(rfi_server* srv, int li)
     if (srv->fault != hipSuccess) return hip_fail(srv->fault);
     L.descs.clear();
     L.items.clear();
+    L.generic.clear();
+    for (auto& m : L.tiles)
+        for (auto& v : m) v.clear();
     L.carries.clear();
+    L.modes = 0;
     L.batch.clear();
     const int nm = (int)L.members.size();
     L.chains.assign(nm, Chain());
@@ -376,6 +389,12 @@ int dispatch_lane(rfi_server* srv, int li)
     if (L.batch.empty()) return RFI_OK;
     for (int j = 0; j < nm; ++j) close_chain(srv, srv->streams[L.members[j]], L.chains[j], L);
     L.rr = (L.rr + 1) % nm;
+    // A carry update reads what no item of the batch writes (input blocks and
+    // the stream's other carry buffer), so it is an item like the others.
+    L.items.insert(L.items.end(), L.generic.begin(), L.generic.end());
+    for (size_t i = 0; i < L.carries.size(); ++i) L.items.push_back(Item{(int32_t)i, kItemCarry, 0});
+    for (auto& m : L.tiles)
+        for (auto& v : m) L.items.insert(L.items.end(), v.begin(), v.end());
     Slot& sl = L.slots[si];
     StreamDesc* dd = nullptr;
     Item* di = nullptr;
@@ -402,23 +421,19 @@ int dispatch_lane(rfi_server* srv, int li)
     }
     hipError_t e = hipSuccess;
     const std::vector<Item>& items = L.items;
-    const std::vector<CarryItem>& carries = L.carries;
     if (!items.empty()) {
         LaunchArgs a;
         std::memset(&a, 0, sizeof(a));
         a.streams = dd;
         a.items = di;
+        a.carries = dc;
         a.n_items = (int64_t)items.size();
         a.seed = srv->cfg.seed;
         set_wg_per_cu(0);
         int64_t grid = a.n_items;
         if (srv->cfg.schedule == RFI_SCHED_FUSED_PERSIST) grid = std::min<int64_t>(grid, srv->persist_grid);
-        e = srv->cfg.elem_size == 1 ? launch_i8_fused(7, a, (int)grid, L.s)
+        e = srv->cfg.elem_size == 1 ? launch_i8_fused(L.modes, a, (int)grid, L.s)
                                     : launch_i16_fused(a, (int)grid, L.s);
-        ++srv->n_launches;
-    }
-    if (e == hipSuccess && !carries.empty()) {
-        e = launch_carry(dc, (int)carries.size(), L.s);
         ++srv->n_launches;
     }
     if (e == hipSuccess) e = hipEventRecord(sl.ev, L.s);
