@@ -715,7 +715,7 @@ static hipError_t run_schedule(rfi_plan* p, const std::vector<PlanLaunch>& ls, c
 }
 
 int plan_execute(rfi_plan* p, const void* x, void* y, rfi_window_stats* st, hipStream_t s,
-                 int sched_override)
+                 int sched_override, uint8_t* mads)
 {
     const int sched = sched_override >= 0 ? sched_override : launch_list(p);
     LaunchArgs base;
@@ -726,6 +726,7 @@ int plan_execute(rfi_plan* p, const void* x, void* y, rfi_window_stats* st, hipS
     base.y_base = (uint64_t)(uintptr_t)y;
     base.stats_base = (uint64_t)(uintptr_t)st;
     base.no_stats = st ? 0 : 1;
+    base.mad_base = (uint64_t)(uintptr_t)mads;
     const auto& ls = p->launches[sched];
     if (p->use_graph && s != nullptr && !ls.empty()) {
         const TuneEntry te = tuned(p->tune_key);

@@ -150,7 +150,23 @@ __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0
 // mask alive until the end of the chain.
 __device__ __forceinline__ void pin_sgpr(uint32_t& x) { asm volatile("" : "+s"(x)); }
 
-// The same for a per-lane running sum, whose addends would otherwise be kept
+// A draw's key (the same in every lane), made opaque where it is drawn: the
+// ten rounds' keys are otherwise computed ahead of the loops over draws and
+// kept in 40 scalar registers, most of which spill in the int16 kernels (W
+// 8192 noise, 60 x 2^21 samples, 113 -> 105 us; the int8 kernels hold them,
+// and making them at each draw cost 5-10 % there).
+__device__ __forceinline__ void make_opaque(uint64_t& seed, uint32_t& key)
+{
+    uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)seed);
+    uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(seed >> 32));
+    key = (uint32_t)__builtin_amdgcn_readfirstlane((int)key);
+    pin_sgpr(lo);
+    pin_sgpr(hi);
+    pin_sgpr(key);
+    seed = (uint64_t)hi << 32 | lo;
+}
+
+// Pins a per-lane running sum, whose addends would otherwise be kept
 // until the sum is used.
 __device__ __forceinline__ void pin_vgpr(uint32_t& x) { asm volatile("" : "+v"(x)); }
 

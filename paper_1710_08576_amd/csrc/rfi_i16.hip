@@ -73,6 +73,7 @@ __device__ __forceinline__ void zero_words(uint32_t* p, int words, int tid, int 
 __device__ __forceinline__ uint2 noise_quad_i16(uint64_t j0, uint64_t seed, uint32_t key, int m,
                                                 int sq8)
 {
+    make_opaque(seed, key);
     const Philox4x64 r = philox4x64_10(j0 >> 2, seed, key);
     uint32_t o[2];
 #pragma unroll
@@ -501,15 +502,7 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
             const uint32_t key1 = d.key;
             auto merged = [&](int wv, int ln, int slot, int part, uint2 x) -> uint2 {
                 const int64_t off = (int64_t)(slot * NT + wv * 64 + ln) * 8 + part * 4;
-                // opaque here, so that the ten rounds' keys are not kept in
-                // scalar registers (and spilled) from before the pool
-                uint32_t k0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)seed);
-                uint32_t k1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(seed >> 32));
-                uint32_t k2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)key1);
-                pin_sgpr(k0);
-                pin_sgpr(k1);
-                pin_sgpr(k2);
-                const uint2 nz = noise_quad_i16((uint64_t)(abs0 + off), (uint64_t)k1 << 32 | k0, k2, m, sq8);
+                const uint2 nz = noise_quad_i16((uint64_t)(abs0 + off), seed, key1, m, sq8);
                 const uint32_t m0 = nonzero_half_mask(pk_clamp_i16(x.x, lo2, hi2) ^ x.x);
                 const uint32_t m1 = nonzero_half_mask(pk_clamp_i16(x.y, lo2, hi2) ^ x.y);
                 return make_uint2((x.x & ~m0) | (nz.x & m0), (x.y & ~m1) | (nz.y & m1));

@@ -41,6 +41,7 @@ struct StreamView {
     const void* x;
     void* y;
     rfi_window_stats* stats;  // NULL: no statistics
+    uint8_t* mads;            // statistics-only launches: MADs, or NULL
     const void* x_head;
     int64_t length;
     int64_t abs_base;
@@ -118,6 +119,9 @@ struct LaunchArgs {
     int32_t no_stats;     // 1: write no statistics at all
     int32_t pad;
     const CarryItem* carries;  // of kItemCarry items
+    // statistics-only launches: byte g receives window g's MAD (g in the
+    // packed stats order); 0: none
+    uint64_t mad_base;
 };
 
 __host__ __device__ inline StreamView resolve(const StreamDesc& d, const LaunchArgs& a)
@@ -128,6 +132,9 @@ __host__ __device__ inline StreamView resolve(const StreamDesc& d, const LaunchA
     v.stats = (a.no_stats || (d.flags & kNoStats))
                   ? nullptr
                   : reinterpret_cast<rfi_window_stats*>(static_cast<uintptr_t>(a.stats_base + d.stats_off));
+    v.mads = a.mad_base ? reinterpret_cast<uint8_t*>(static_cast<uintptr_t>(
+                              a.mad_base + d.stats_off / sizeof(rfi_window_stats)))
+                        : nullptr;
     v.x_head = reinterpret_cast<const void*>(static_cast<uintptr_t>(a.x_base + d.head_off));
     v.length = d.length;
     v.abs_base = d.abs_base;
@@ -180,35 +187,27 @@ struct MultiArgs {
 hipError_t launch_i8_multi(int cls, const MultiArgs& ma, int grid, hipStream_t s);
 
 // Median of MAD (int8).  Windows of all streams are numbered globally in
-// the packed stats order; mad[g] is window g's own MAD, dm[g] receives the
-// lower median of the MADs of its stream's last K windows.  Each stream's
-// MAD sequence (emad, from eoff) is `pre` history slots (the MADs of earlier
-// calls, right-aligned, hist_len[s] of them valid) followed by its windows;
-// pre = 0 when there is no history, and emad is mad itself.
+// the packed stats order; mad[g] is window g's own MAD (written by the
+// statistics pass), dm[g] receives the lower median of the MADs of its
+// stream's last K windows.  Each stream's MAD sequence is `pre` history
+// slots (hist[s * pre ..]: the MADs of earlier calls, right-aligned,
+// hist_len[s] of them valid) followed by its windows; pre = 0 when there is
+// no history.
 struct MomStream {
-    int64_t woff;   // first window of the stream in the stats order
-    int64_t nw;     // windows of the stream in this call
-    int64_t eoff;   // first entry of the stream's MAD sequence
-    int64_t pre;    // history slots before its first window (0 or K - 1)
-    int64_t hoff;   // first row of the stream's block-count table
+    int64_t woff;  // first window of the stream in the stats order
+    int64_t nw;    // windows of the stream in this call
+    int64_t pre;   // history slots before its first window (0 or K - 1)
 };
-constexpr int kMomBlock = 64;  // entries per row of the block-count table
-// hcnt[(hoff + b) * 256 + v] = #{j < 64 b : emad_j <= v} over the stream's
-// sequence (pre + nw entries).  max_blocks: the largest ceil((pre + nw) / 64).
-hipError_t launch_mom_counts(const MomStream* streams, int n_streams, int64_t max_blocks,
-                             const uint8_t* emad, uint32_t* hcnt, hipStream_t s);
-// hist_len: NULL when no stream has history slots.
-hipError_t launch_mom_select(const MomStream* streams, int n_streams, int64_t total_windows,
-                             int32_t mom_k, const uint8_t* emad, const uint32_t* hcnt,
-                             const int32_t* hist_len, int32_t* dm, hipStream_t s);
-// emad of streams with history slots: hist[s * pre + i] for the slots, then
-// mad[woff + w] (total_ext = sum of pre + nw).
-hipError_t launch_mom_extend(const MomStream* streams, int n_streams, int64_t total_ext,
-                             const uint8_t* mad, const uint8_t* hist, uint8_t* emad, hipStream_t s);
-// New history: the last min(pre, hist_len + nw) entries of each stream's
-// sequence, right-aligned in hist[s * pre ..], and hist_len updated.
-hipError_t launch_mom_history(const MomStream* streams, int n_streams, const uint8_t* emad, uint8_t* hist,
-                              int32_t* hist_len, hipStream_t s);
+// One wave's windows of the median search: `first` .. first + n - 1 of a
+// stream.
+struct MomSeg {
+    int32_t stream;
+    int32_t n;
+    int64_t first;
+};
+hipError_t launch_mom_select(const MomStream* streams, const MomSeg* segs, int64_t n_segs, int32_t mom_k,
+                             const uint8_t* mad, const uint8_t* hist, const int32_t* hist_len, int32_t* dm,
+                             hipStream_t s);
 // Replacement pass: items of up to 256 windows (<= 16 KiB) of one stream;
 // window params from stats (median) and dm; rewrites n_flagged and threshold.
 struct MomItem {
@@ -217,13 +216,19 @@ struct MomItem {
     int64_t first_window;  // within the stream
 };
 // abs_add: NULL, or per stream an offset added to its absolute sample index.
+// n_hist streams (0 without a carried history): one workgroup each writes the
+// new history, the last min(pre, hist_len + nw) entries of the stream's MAD
+// sequence, right-aligned in hist[s * pre ..], and hist_len.
+struct MomHistory {
+    const MomStream* streams;
+    const uint8_t* mad;
+    uint8_t* hist;
+    int32_t* hist_len;
+    int32_t n_hist;
+};
 hipError_t launch_mom_apply(const LaunchArgs& a, const MomItem* items, int64_t n_items,
                             const int32_t* dm, const int64_t* stream_woff, const int64_t* abs_add,
-                            rfi_window_stats* stats, hipStream_t s);
-// Copies the MAD of every window out of the stats array (int8 MADs fit a byte).
-hipError_t launch_mom_gather(const rfi_window_stats* stats, int64_t total_windows, uint8_t* mad,
-                             hipStream_t s);
-
+                            rfi_window_stats* stats, const MomHistory& h, hipStream_t s);
 // Copies n16 16-byte units from pinned host memory to device memory.
 hipError_t launch_stage(void* dst, const void* src_host, int64_t n16, hipStream_t s);
 

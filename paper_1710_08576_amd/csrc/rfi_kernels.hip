@@ -424,7 +424,10 @@ __device__ __forceinline__ TileStats i8_tile(const StreamView& d, int64_t first,
         if (wave % WPW == 0) {
             if (lane == 0) {
                 sm.prm[wl] = p;
-                if constexpr (MODE == kModeStats) sm.mad[wl] = D;
+                if constexpr (MODE == kModeStats) {
+                    sm.mad[wl] = D;
+                    if (d.mads) gstore(d.mads + first / W + wl, (uint8_t)D);
+                }
             }
             ts.s = ws;
             ts.dst = (lane == 0 && d.stats) ? d.stats + first / W + wl : nullptr;
@@ -508,7 +511,10 @@ __device__ __forceinline__ TileStats i8_tile(const StreamView& d, int64_t first,
             // Lane r of the window's group keeps the statistics of round r.
             if ((lane & (G - 1)) == r) {
                 sm.prm[wl] = p;
-                if constexpr (MODE == kModeStats) sm.mad[wl] = D;
+                if constexpr (MODE == kModeStats) {
+                    sm.mad[wl] = D;
+                    if (d.mads) gstore(d.mads + first / W + wl, (uint8_t)D);
+                }
                 ts.s = ws;
                 ts.dst = d.stats ? d.stats + first / W + wl : nullptr;
             }
@@ -670,6 +676,7 @@ __device__ void i8_generic_reg(const StreamView& d, int64_t w, int64_t a, int n,
         if (lane == 0) {
             sm.prm = p;
             if (d.stats) d.stats[w] = s;
+            if (d.mode == kModeStats && d.mads) gstore(d.mads + w, (uint8_t)D);
         }
     }
     __syncthreads();
@@ -774,6 +781,7 @@ __device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, Smem& 
         if (tid == 0) {
             sm.prm = p;
             if (d.stats) d.stats[w] = s;
+            if (d.mode == kModeStats && d.mads) gstore(d.mads + w, (uint8_t)D);
         }
     }
     __syncthreads();
@@ -1053,170 +1061,154 @@ __global__ __launch_bounds__(kBlock) void k_i8_multi(MultiArgs ma)
 }
 
 // ---------------------------------------------------------------------------
-// Median of MAD (Eq. (3)), int8: the MADs of the first pass are gathered,
-// counted per stream in blocks of 64 windows, and each window's lower
-// median of the MADs of its K-window history is found by a binary search
-// over the 256 possible MAD values on those counts; a last pass applies
-// Eqs. (1)-(2) with it.
+// Median of MAD (Eq. (3)), int8: the statistics pass leaves each window's
+// MAD as a byte; each window's lower median of the MADs of its K-window
+// history is found 64 windows at a time; a last pass applies Eqs. (1)-(2)
+// with it.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_mom_gather(const rfi_window_stats* __restrict__ stats,
-                                                       int64_t total, uint8_t* __restrict__ mad)
-{
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g < total) mad[g] = (uint8_t)stats[g].mad;
-}
+// One wave per segment, one lane per window, 64 windows at a time.  The MADs
+// [a0, p0) that precede the group's first window in its history are counted
+// into a 256-value histogram; window i of the group then differs from that
+// by its predecessors' and its own MAD added and by the entries from a0 on
+// that its history no longer holds (for K < 64 the group's own among them), which for one value v are two ballots and their popcounts for all
+// 64 windows at once.  The medians are found by trying the values in order
+// from the first that any window can reach; MADs of neighbouring windows
+// differ little, so a few values do.  From group to group the histogram
+// takes up 64 entries and drops as many.
+//
+// The counts have 16 replicas (lane & 15): MADs cluster on a few values, on
+// which the atomics of a wave would meet.  Latency-bound: 60 streams of 256
+// windows with 4095 MADs of history 34 us before, as five kernels (gather,
+// concatenate, count in blocks of 64, add up, search), 6 us now.
+constexpr int kMomReps = 16;
 
-// Two steps build row b of a stream's table, #{j < 64 b : mad_j <= v} for
-// b = 0 .. ceil(nw / 64): per block of 64 windows (blockIdx.x = block b of
-// stream blockIdx.y, thread v) the block's own count goes to row b + 1, then
-// one workgroup per stream turns the rows into running sums.
-__global__ __launch_bounds__(256) void k_mom_block_counts(const MomStream* __restrict__ streams,
-                                                          const uint8_t* __restrict__ mad,
-                                                          uint32_t* __restrict__ hcnt)
+__global__ __launch_bounds__(64) void k_mom_select(const MomStream* __restrict__ streams,
+                                                   const MomSeg* __restrict__ segs, int32_t K,
+                                                   const uint8_t* __restrict__ mad,
+                                                   const uint8_t* __restrict__ hist,
+                                                   const int32_t* __restrict__ hist_len, int32_t* __restrict__ dm)
 {
-    const MomStream st = streams[blockIdx.y];
-    const int64_t n = st.pre + st.nw;
-    const int64_t j0 = (int64_t)blockIdx.x * kMomBlock;
-    if (j0 >= n) return;
-    __shared__ uint8_t m[kMomBlock];
-    const int64_t j1 = min(j0 + kMomBlock, n);
-    if ((int64_t)threadIdx.x < j1 - j0) m[threadIdx.x] = mad[st.eoff + j0 + threadIdx.x];
-    __syncthreads();
-    const uint32_t v = threadIdx.x;
-    uint32_t c = 0;
-    for (int j = 0; j < (int)(j1 - j0); ++j) c += m[j] <= v ? 1u : 0u;
-    hcnt[(st.hoff + blockIdx.x + 1) * 256 + v] = c;
-}
-
-__global__ __launch_bounds__(256) void k_mom_counts(const MomStream* __restrict__ streams,
-                                                    uint32_t* __restrict__ hcnt)
-{
-    const MomStream st = streams[blockIdx.x];
-    uint32_t* row = hcnt + st.hoff * 256 + threadIdx.x;
-    const int64_t nb = (st.pre + st.nw + kMomBlock - 1) / kMomBlock;
-    uint32_t run = 0;
-    row[0] = 0;
-    // 16 rows per batch: their loads are in flight together
-    for (int64_t b0 = 1; b0 <= nb; b0 += 16) {
-        uint32_t t[16];
+    __shared__ __align__(16) uint32_t rep[256 * kMomReps];  // value v, replica r at v * 16 + r
+    __shared__ __align__(16) uint32_t cum[256];             // #{entries <= v}
+    const MomSeg sg = segs[blockIdx.x];
+    const MomStream st = streams[sg.stream];
+    const int lane = lane_id();
+    const uint8_t* hs = hist ? hist + sg.stream * st.pre : nullptr;
+    const uint8_t* ms = mad + st.woff;
+    auto entry = [&](int64_t p) -> uint32_t { return p < st.pre ? hs[p] : ms[p - st.pre]; };
+    // sequence position of the first valid entry
+    const int64_t H = st.pre > 0 ? min(max((int64_t)hist_len[sg.stream], (int64_t)0), st.pre) : 0;
+    const int64_t lb = st.pre - H;
+    int64_t p0 = st.pre + sg.first;  // sequence position of the group's first window
+    int64_t a0 = max(lb, p0 + 1 - (int64_t)K);
+    for (int i = lane; i < 256 * kMomReps / 4; i += 64) reinterpret_cast<uint4*>(rep)[i] = make_uint4(0, 0, 0, 0);
+    wave_sync();
+    uint32_t* mine = rep + (lane & (kMomReps - 1));
+    // 32 loads of a lane in flight: a history of 4096 takes two round trips
+    for (int64_t p = a0 + lane; p < p0; p += 32 * 64) {
+        uint32_t e[32];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) t[i] = b0 + i <= nb ? row[(b0 + i) * 256] : 0u;
+        for (int u = 0; u < 32; ++u) e[u] = p + 64 * u < p0 ? entry(p + 64 * u) : 256u;
 #pragma unroll
+        for (int u = 0; u < 32; ++u)
+            if (e[u] < 256u) atomicAdd(mine + e[u] * kMomReps, 1u);
+    }
+    for (int done = 0; done < sg.n; done += 64) {
+        const int n = min(64, sg.n - done);
+        const bool has = lane < n;
+        const int64_t p = p0 + lane;  // this lane's window
+        const int64_t a = max(lb, p + 1 - (int64_t)K);
+        const int gone = has ? (int)(a - a0) : 0;  // entries from a0 on that it has dropped, at most lane
+        const uint32_t mine_e = has ? entry(p) : 255u;
+        // lane r holds the r-th entry to be dropped
+        const int dropped = __builtin_amdgcn_readlane(gone, n - 1);
+        const uint32_t old_e = lane < dropped ? entry(a0 + lane) : 255u;
+        const uint32_t need = (uint32_t)((p - a) / 2 + 1);  // rank floor((N - 1) / 2) of N = p + 1 - a, 1-based
+        // Sums of the replicas: 4 lanes per value, 16 values at a time, then
+        // cumulative counts, four values per lane.
+        wave_sync();
+#pragma unroll 4
         for (int i = 0; i < 16; ++i) {
-            run += t[i];
-            if (b0 + i <= nb) row[(b0 + i) * 256] = run;
+            const uint4 t = reinterpret_cast<const uint4*>(rep)[i * 64 + lane];
+            uint32_t c = t.x + t.y + t.z + t.w;
+            c += dpp0<0xB1>(c);  // quad_perm [1, 0, 3, 2]
+            c += dpp0<0x4E>(c);  // quad_perm [2, 3, 0, 1]
+            if ((lane & 3) == 0) cum[i * 16 + (lane >> 2)] = c;
+        }
+        wave_sync();
+        uint4 t = reinterpret_cast<const uint4*>(cum)[lane];
+        t.y += t.x;
+        t.z += t.y;
+        t.w += t.z;
+        const uint32_t excl = group_incl_scan<64>(t.w) - t.w;
+        t.x += excl;
+        t.y += excl;
+        t.z += excl;
+        t.w += excl;
+        reinterpret_cast<uint4*>(cum)[lane] = t;
+        // No window can reach its rank at values whose count is more than 64
+        // below the smallest rank (ranks grow with the window index).
+        const uint32_t least = (uint32_t)__builtin_amdgcn_readfirstlane((int)need);
+        int v = group_count<64>(t.x + 64 < least) + group_count<64>(t.y + 64 < least) +
+                group_count<64>(t.z + 64 < least) + group_count<64>(t.w + 64 < least);
+        wave_sync();
+        const uint64_t upto = lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1;  // windows 0 .. lane
+        const uint64_t first = (1ull << gone) - 1;                            // gone <= lane <= 63
+        int res = 255;
+        bool found = !has;
+        for (; v < 255; ++v) {
+            const uint64_t in = __ballot(mine_e <= (uint32_t)v), out = __ballot(old_e <= (uint32_t)v);
+            const uint32_t N = cum[v] + (uint32_t)__popcll(in & upto) - (uint32_t)__popcll(out & first);
+            if (!found && N >= need) {
+                found = true;
+                res = v;
+            }
+            if (__ballot(!found) == 0) break;
+        }
+        if (has) dm[st.woff + (p - st.pre)] = res;
+        if (done + 64 < sg.n) {
+            // the next group: this one's entries join, those before its start leave
+            wave_sync();
+            atomicAdd(mine + mine_e * kMomReps, 1u);
+            const int64_t na = max(lb, p0 + 64 + 1 - (int64_t)K);
+            for (int64_t q = a0 + lane; q < na; q += 64) atomicSub(mine + entry(q) * kMomReps, 1u);
+            p0 += 64;
+            a0 = na;
         }
     }
 }
 
-// The partial block of prefix p: entries [kMomBlock * (p / kMomBlock), p)
-// of a MAD sequence, four to a dword (entry 4i + c in byte c of w[i]), the
-// bytes from p on set to 255.  Only dwords holding an entry are read.
-__device__ __forceinline__ void mom_partial(const uint8_t* m, int64_t p, uint32_t (&w)[16])
+// The new right-aligned history of a stream, in place, then its length, by
+// one workgroup.  Slot i takes sequence entry nw + i, so the slots move
+// towards the front: a pass reads its entries before any of its slots is
+// written, and later passes read only from later slots on.
+__device__ __forceinline__ void mom_history(const MomHistory& h, int s)
 {
-    const int64_t j0 = p / kMomBlock * kMomBlock;
-    const int n = (int)(p - j0);  // 0 .. kMomBlock - 1
-    const uintptr_t a = (uintptr_t)(m + j0);
-    const uint32_t* base = reinterpret_cast<const uint32_t*>(a & ~(uintptr_t)3);
-    const int off = (int)(a & 3);
-    uint32_t r[17];
-#pragma unroll
-    for (int i = 0; i < 17; ++i) r[i] = 4 * i < off + n ? base[i] : 0u;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const uint32_t x = __builtin_amdgcn_alignbyte(r[i + 1], r[i], (uint32_t)off);
-        const int valid = n - 4 * i;  // entries in this dword
-        w[i] = valid >= 4 ? x : valid <= 0 ? ~0u : x | (~0u << (8 * valid));
-    }
-}
-
-// Number of bytes <= v (v < 255) in w: each byte is subtracted from v in
-// a 16-bit lane with bit 15 preset, which stays set exactly when the byte
-// is at most v.
-__device__ __forceinline__ uint32_t count_le(const uint32_t (&w)[16], int v)
-{
-    const uint32_t V = (uint32_t)v * 0x00010001u | 0x80008000u;
-    uint32_t c = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        c += __popc((V - (w[i] & 0x00FF00FFu)) & 0x80008000u);
-        c += __popc((V - ((w[i] >> 8) & 0x00FF00FFu)) & 0x80008000u);
-    }
-    return c;
-}
-
-__global__ __launch_bounds__(kBlock) void k_mom_select(const MomStream* __restrict__ streams, int n_streams,
-                                                       int64_t total, int32_t K,
-                                                       const uint8_t* __restrict__ mad,
-                                                       const uint32_t* __restrict__ hcnt,
-                                                       const int32_t* __restrict__ hist_len,
-                                                       int32_t* __restrict__ dm)
-{
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g >= total) return;
-    int lo_s = 0, hi_s = n_streams - 1;  // last stream with woff <= g
-    while (lo_s < hi_s) {
-        const int mid = (lo_s + hi_s + 1) / 2;
-        if (streams[mid].woff <= g) lo_s = mid;
-        else hi_s = mid - 1;
-    }
-    const MomStream st = streams[lo_s];
-    const int64_t w = g - st.woff;
-    // sequence position of window w; the valid history starts pre - H back
-    const int64_t p = st.pre + w;
-    const int64_t H = st.pre > 0 ? min(max((int64_t)hist_len[lo_s], (int64_t)0), st.pre) : 0;
-    const int64_t a = max(st.pre - H, p + 1 - (int64_t)K), b = p + 1;
-    const uint32_t need = (uint32_t)((b - a - 1) / 2 + 1);
-    const uint8_t* m = mad + st.eoff;
-    const uint32_t* ha = hcnt + (st.hoff + a / kMomBlock) * 256;
-    const uint32_t* hb = hcnt + (st.hoff + b / kMomBlock) * 256;
-    // #{j < p : mad_j <= v} = block table row p / kMomBlock + partial block
-    uint32_t wa[16], wb[16];
-    mom_partial(m, a, wa);
-    mom_partial(m, b, wb);
-    int lo = 0, hi = 255;  // smallest v with #{a <= j < b : mad_j <= v} >= need
-    while (lo < hi) {
-        const int mid = (lo + hi) / 2;  // < 255
-        if ((hb[mid] + count_le(wb, mid)) - (ha[mid] + count_le(wa, mid)) >= need) hi = mid;
-        else lo = mid + 1;
-    }
-    dm[g] = lo;
-}
-
-// emad of streams with history slots (see launch_mom_extend).
-__global__ __launch_bounds__(kBlock) void k_mom_extend(const MomStream* __restrict__ streams, int n_streams,
-                                                       int64_t total_ext, const uint8_t* __restrict__ mad,
-                                                       const uint8_t* __restrict__ hist,
-                                                       uint8_t* __restrict__ emad)
-{
-    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (q >= total_ext) return;
-    int lo_s = 0, hi_s = n_streams - 1;  // last stream with eoff <= q
-    while (lo_s < hi_s) {
-        const int mid = (lo_s + hi_s + 1) / 2;
-        if (streams[mid].eoff <= q) lo_s = mid;
-        else hi_s = mid - 1;
-    }
-    const MomStream st = streams[lo_s];
-    const int64_t i = q - st.eoff;
-    emad[q] = i < st.pre ? hist[lo_s * st.pre + i] : mad[st.woff + (i - st.pre)];
-}
-
-// One workgroup per stream: the new right-aligned history, then its length.
-__global__ __launch_bounds__(kBlock) void k_mom_history(const MomStream* __restrict__ streams,
-                                                        const uint8_t* __restrict__ emad,
-                                                        uint8_t* __restrict__ hist,
-                                                        int32_t* __restrict__ hist_len)
-{
-    const MomStream st = streams[blockIdx.x];
+    const MomStream st = h.streams[s];
     if (st.pre == 0) return;
-    const int64_t H = min(max((int64_t)hist_len[blockIdx.x], (int64_t)0), st.pre);
+    uint8_t* hs = h.hist + s * st.pre;
+    const uint8_t* ms = h.mad + st.woff;
+    const int64_t H = min(max((int64_t)h.hist_len[s], (int64_t)0), st.pre);
     const int64_t Hn = min(st.pre, H + st.nw);
-    // slot i (i >= pre - Hn) takes sequence entry nw + i
-    for (int64_t i = st.pre - Hn + threadIdx.x; i < st.pre; i += kBlock)
-        hist[blockIdx.x * st.pre + i] = emad[st.eoff + st.nw + i];
+    constexpr int U = 16;
+    for (int64_t i0 = st.pre - Hn; i0 < st.pre; i0 += U * kBlock) {
+        uint8_t e[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + u * kBlock + threadIdx.x;
+            const int64_t p = st.nw + i;
+            e[u] = i >= st.pre ? 0 : p < st.pre ? hs[p] : ms[p - st.pre];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + u * kBlock + threadIdx.x;
+            if (i < st.pre) hs[i] = e[u];
+        }
+        __syncthreads();
+    }
     __syncthreads();  // every thread has read hist_len
-    if (threadIdx.x == 0) hist_len[blockIdx.x] = (int32_t)Hn;
+    if (threadIdx.x == 0) h.hist_len[s] = (int32_t)Hn;
 }
 
 struct MomSmem {
@@ -1314,8 +1306,106 @@ __device__ __forceinline__ void mom_apply_item(const LaunchArgs& a, const MomIte
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             gstore16_nt(y + base + i * 1024, make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]));
+    } else if (W >= 16 && (MODE != RFI_MODE_NOISE || (d.abs_base & 3) == 0)) {
+        // Other items (irregular W, stream tails): 16-byte chunks of the
+        // stream, 16 KiB a pass.  A chunk holds samples of at most two of the
+        // item's windows, the second from its byte t on; the edge chunks hold
+        // other items' samples too, which are neither counted nor stored.
+        // (The last chunk may read into the packed layout's padding.)
+        const int lead = (int)(s0 & 15);
+        const int64_t base = s0 - lead;
+        const int len = (int)(s1 - s0);
+        const float rW = __builtin_amdgcn_rcpf((float)W);
+        auto window_of = [&](int rel) {  // rel / W
+            int w = (int)((float)rel * rW);
+            w -= w * W > rel ? 1 : 0;
+            return w + ((w + 1) * W <= rel ? 1 : 0);
+        };
+        auto below = [](int t) -> uint32_t { return t >= 4 ? ~0u : t <= 0 ? 0u : (1u << (8 * t)) - 1u; };  // bytes < t
+        const int last = it.n_windows - 1;
+#pragma unroll 1
+        for (int p = 0; p < lead + len; p += 16384) {
+            uint32_t v[16];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int at = p + i * 4096 + tid * 16;
+                uint4 t = make_uint4(0, 0, 0, 0);
+                if (at < lead + len) t = gload16_nt(x + base + at);
+                v[4 * i] = t.x;
+                v[4 * i + 1] = t.y;
+                v[4 * i + 2] = t.z;
+                v[4 * i + 3] = t.w;
+            }
+            uint32_t cf = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int rel = p + i * 4096 + tid * 16 - lead;  // first sample of the chunk, from s0
+                if (rel < len) {
+                    const int w0 = min(window_of(max(rel, 0)), last);
+                    const int w1 = min(w0 + 1, last);
+                    const int t = (w0 + 1) * W - rel;
+                    auto apply = [&](int w, bool second) {
+                        const WinParams pw = sm.prm[w];
+                        const uint32_t lo = rep_i16(pw.lo * 256), hi = rep_i16(pw.hi * 256);
+                        const uint32_t lo_u = rep_i16((pw.lo + 128) * 256), hi_u = rep_i16((pw.hi + 128) * 256);
+                        uint32_t nf = 0;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const uint32_t xw = v[4 * i + q];
+                            uint32_t mask = below(t - 4 * q);
+                            if (second) mask = ~mask;
+                            const uint32_t clipped = clamp_i8x4(xw, lo, hi);
+                            const uint32_t diff = (clipped ^ xw) & mask & below(len - rel - 4 * q) & ~below(-rel - 4 * q);
+                            nf += __popc(nonzero_byte_mask(diff)) >> 3;
+                            cf |= (diff != 0 ? 1u : 0u) << (4 * i + q);
+                            if constexpr (MODE == RFI_MODE_CLIP) v[4 * i + q] = bit_select(mask, clipped, xw);
+                            else if constexpr (MODE == RFI_MODE_ZERO)
+                                v[4 * i + q] = bit_select(mask, byte_perm(0u, xw, flag_sel_i8x4(xw, lo_u, hi_u)), xw);
+                        }
+                        if (nf) atomicAdd(&sm.flagged[w], nf);
+                    };
+                    apply(w0, false);
+                    if (t < 16 && w1 != w0) apply(w1, true);
+                }
+            }
+            if constexpr (MODE == RFI_MODE_NOISE) {
+                const int64_t j0 = d.abs_base + base + p;
+                auto merged = [&](int wv, int ln, int slot, int part, uint32_t xw) -> uint32_t {
+                    const int off = slot * 4096 + (wv * 64 + ln) * 16 + part * 4;
+                    const int rel = p + off - lead;
+                    const int w0 = min(window_of(max(rel, 0)), last);
+                    const int w1 = min(w0 + 1, last);
+                    uint32_t r = xw;
+                    // the two windows of a part share its Philox block, not
+                    // their parameters
+                    for (int w = w0; w <= ((w0 + 1) * W - rel < 4 ? w1 : w0); ++w) {
+                        const WinParams pw = sm.prm[w];
+                        const uint32_t mask = w == w0 ? below((w0 + 1) * W - rel) : ~below((w0 + 1) * W - rel);
+                        const uint32_t lo_u = rep_i16((pw.lo + 128) * 256), hi_u = rep_i16((pw.hi + 128) * 256);
+                        const uint32_t nz = noise_quad_i8((uint64_t)(j0 + off), a.seed, d.key, pw.m, pw.sq8);
+                        r = bit_select(mask, byte_perm(nz, xw, flag_sel_i8x4(xw, lo_u, hi_u)), r);
+                    }
+                    return r;
+                };
+                pool_noise<4>(v, cf, sm.noise(), merged);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int rel = p + i * 4096 + tid * 16 - lead;
+                if (rel >= len) continue;
+                if (rel >= 0 && rel + 16 <= len) {
+                    gstore16_nt(y + s0 + rel, make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]));
+                } else {
+#pragma unroll
+                    for (int b = 0; b < 16; ++b)
+                        if (rel + b >= 0 && rel + b < len)
+                            gstore(reinterpret_cast<uint8_t*>(y) + s0 + rel + b, (uint8_t)byte_of(v[4 * i + b / 4], b % 4));
+                }
+            }
+        }
     } else {
-        // Other items (irregular W, stream tails): sample by sample.
+        // Windows of a few samples, and noise on streams whose dwords are not
+        // whole Philox blocks: sample by sample.
 #pragma unroll 1
         for (int64_t j = s0 + tid; j < s1; j += kBlock) {
             const int wl = (int)(j - s0) / W;
@@ -1434,14 +1524,21 @@ hipError_t launch_i8_fused(int modes, const LaunchArgs& a, int grid, hipStream_t
     return launch(grid < a.n_items ? i8_fused_kernel<true>(modes) : i8_fused_kernel<false>(modes), a, grid, s);
 }
 
-__global__ __launch_bounds__(kBlock) void k_mom_apply(LaunchArgs a, const MomItem* __restrict__ items,
+// Six waves per SIMD (80 VGPRs; unbounded 97 and five: 60 x 2^22 samples, W
+// 5000, 258 against 239 us for the whole call, W 4096 unchanged).
+__global__ __launch_bounds__(kBlock, 6) void k_mom_apply(LaunchArgs a, const MomItem* __restrict__ items,
                                                       const int32_t* __restrict__ dm,
                                                       const int64_t* __restrict__ stream_woff,
                                                       const int64_t* __restrict__ abs_add,
-                                                      rfi_window_stats* __restrict__ stats)
+                                                      rfi_window_stats* __restrict__ stats, MomHistory h)
 {
     __shared__ MomSmem sm;
-    const MomItem it = items[blockIdx.x];
+    // the first workgroups carry the streams' histories on
+    if ((int)blockIdx.x < h.n_hist) {
+        mom_history(h, (int)blockIdx.x);
+        return;
+    }
+    const MomItem it = items[blockIdx.x - h.n_hist];
     StreamView d = resolve(a.streams[it.stream], a);
     if (abs_add) d.abs_base += abs_add[it.stream];
     if (d.mode == RFI_MODE_CLIP) mom_apply_item<RFI_MODE_CLIP>(a, it, d, dm, stream_woff, stats, sm);
@@ -1467,65 +1564,25 @@ hipError_t launch_i8_multi(int cls, const MultiArgs& ma, int grid, hipStream_t s
     return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3(grid), dim3(kBlock), kargs, 0, s);
 }
 
-hipError_t launch_mom_gather(const rfi_window_stats* stats, int64_t total, uint8_t* mad, hipStream_t s)
-{
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mom_gather, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                       stats, total, mad);
-    return hipGetLastError();
-}
-
-hipError_t launch_mom_counts(const MomStream* streams, int n_streams, int64_t max_blocks, const uint8_t* mad,
-                             uint32_t* hcnt, hipStream_t s)
-{
-    if (n_streams <= 0) return hipSuccess;
-    if (max_blocks > 0) {
-        if (max_blocks > (1 << 30) || n_streams > 65535) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_mom_block_counts, dim3((unsigned)max_blocks, (unsigned)n_streams), dim3(256), 0, s,
-                           streams, mad, hcnt);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_mom_counts, dim3(n_streams), dim3(256), 0, s, streams, hcnt);
-    return hipGetLastError();
-}
-
-hipError_t launch_mom_select(const MomStream* streams, int n_streams, int64_t total, int32_t K,
-                             const uint8_t* mad, const uint32_t* hcnt, const int32_t* hist_len, int32_t* dm,
+hipError_t launch_mom_select(const MomStream* streams, const MomSeg* segs, int64_t n_segs, int32_t mom_k,
+                             const uint8_t* mad, const uint8_t* hist, const int32_t* hist_len, int32_t* dm,
                              hipStream_t s)
 {
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mom_select, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                       streams, n_streams, total, K, mad, hcnt, hist_len, dm);
-    return hipGetLastError();
-}
-
-hipError_t launch_mom_extend(const MomStream* streams, int n_streams, int64_t total_ext, const uint8_t* mad,
-                             const uint8_t* hist, uint8_t* emad, hipStream_t s)
-{
-    if (total_ext <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mom_extend, dim3((unsigned)((total_ext + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                       streams, n_streams, total_ext, mad, hist, emad);
-    return hipGetLastError();
-}
-
-hipError_t launch_mom_history(const MomStream* streams, int n_streams, const uint8_t* emad, uint8_t* hist,
-                              int32_t* hist_len, hipStream_t s)
-{
-    if (n_streams <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mom_history, dim3((unsigned)n_streams), dim3(kBlock), 0, s, streams, emad, hist,
-                       hist_len);
+    if (n_segs <= 0) return hipSuccess;
+    if (n_segs > (1 << 30)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_mom_select, dim3((unsigned)n_segs), dim3(64), 0, s, streams, segs, mom_k, mad, hist,
+                       hist_len, dm);
     return hipGetLastError();
 }
 
 hipError_t launch_mom_apply(const LaunchArgs& a, const MomItem* items, int64_t n_items, const int32_t* dm,
                             const int64_t* stream_woff, const int64_t* abs_add, rfi_window_stats* stats,
-                            hipStream_t s)
+                            const MomHistory& h, hipStream_t s)
 {
-    if (n_items <= 0) return hipSuccess;
+    if (n_items + h.n_hist <= 0) return hipSuccess;
     if (n_items > (1 << 30)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mom_apply, dim3((unsigned)n_items), dim3(kBlock), 0, s, a, items, dm, stream_woff,
-                       abs_add, stats);
+    hipLaunchKernelGGL(k_mom_apply, dim3((unsigned)(n_items + h.n_hist)), dim3(kBlock), 0, s, a, items, dm,
+                       stream_woff, abs_add, stats, h);
     return hipGetLastError();
 }
 

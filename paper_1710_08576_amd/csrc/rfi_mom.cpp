@@ -4,9 +4,9 @@
 //   1. window statistics (median, own MAD) by the tile/generic kernels in
 //      their statistics-only mode (a plan whose streams all use it);
 //   2. per stream, the lower median of the MADs of each window's K-window
-//      history (block counts + binary search over the 256 MAD values);
+//      history;
 //   3. Eqs. (1)-(2) with that value, which also rewrites each window's flag
-//      count and threshold.
+//      count and threshold and carries the MAD histories on.
 // Work tables and temporaries are kept per argument signature and stream
 // (calls on one stream are ordered; calls on different streams use
 // different temporaries).
@@ -36,6 +36,7 @@ struct MomKey {
     int device;
     uintptr_t stream;  // temporaries are per stream: calls on one stream are ordered
     int64_t pre;       // history slots per stream (0, or K - 1 with a carried history)
+    int32_t per_wave;  // groups of 64 windows per wave of pass 2
     uint64_t seed;
     std::vector<int64_t> L;
     std::vector<int32_t> W;
@@ -46,6 +47,7 @@ struct MomKey {
         if (device != o.device) return device < o.device;
         if (stream != o.stream) return stream < o.stream;
         if (pre != o.pre) return pre < o.pre;
+        if (per_wave != o.per_wave) return per_wave < o.per_wave;
         if (seed != o.seed) return seed < o.seed;
         if (L != o.L) return L < o.L;
         if (W != o.W) return W < o.W;
@@ -63,13 +65,12 @@ struct MomChunk {
     MomStream* d_streams = nullptr;
     MomItem* d_items = nullptr;
     int64_t* d_woff = nullptr;
+    MomSeg* d_segs = nullptr;
     uint8_t* d_mad = nullptr;
-    uint8_t* d_emad = nullptr;  // history slots + MADs (pre > 0)
     int32_t* d_dm = nullptr;
-    uint32_t* d_hcnt = nullptr;
     int32_t s0 = 0, n_streams = 0;
     int64_t byte0 = 0, win0 = 0;
-    int64_t total_ext = 0, n_items = 0, total_windows = 0, max_blocks = 0;
+    int64_t n_items = 0, n_segs = 0, total_windows = 0;
 };
 
 struct MomPlan {
@@ -97,10 +98,9 @@ void mom_free(MomPlan* p)
         (void)hipFree(c.d_streams);
         (void)hipFree(c.d_items);
         (void)hipFree(c.d_woff);
+        (void)hipFree(c.d_segs);
         (void)hipFree(c.d_mad);
-        (void)hipFree(c.d_emad);
         (void)hipFree(c.d_dm);
-        (void)hipFree(c.d_hcnt);
     }
     (void)hipFree(p->d_stats);
     for (hipEvent_t e : p->ready) (void)hipEventDestroy(e);
@@ -132,7 +132,7 @@ int alloc(T** dst, int64_t n)
 
 // Tables of streams s0 .. s0 + n - 1 (L, W, K, M point at stream s0).
 int chunk_build(MomChunk& c, int32_t s0, int32_t n, const int64_t* L, const int32_t* W, const float* K,
-                const int32_t* M, uint64_t seed, int64_t pre)
+                const int32_t* M, uint64_t seed, int64_t pre, int32_t per_wave)
 {
     c.s0 = s0;
     c.n_streams = n;
@@ -142,8 +142,9 @@ int chunk_build(MomChunk& c, int32_t s0, int32_t n, const int64_t* L, const int3
     std::vector<StreamDesc> desc(n);
     std::vector<MomStream> ms(n);
     std::vector<MomItem> items;
+    std::vector<MomSeg> segs;
     std::vector<int64_t> woff(n);
-    int64_t soff = 0, wo = 0, eo = 0, rows = 0;
+    int64_t soff = 0, wo = 0;
     for (int s = 0; s < n && rc == RFI_OK; ++s) {
         StreamDesc& d = desc[s];
         std::memset(&d, 0, sizeof(d));
@@ -157,16 +158,12 @@ int chunk_build(MomChunk& c, int32_t s0, int32_t n, const int64_t* L, const int3
         d.key = (uint32_t)(s0 + s);  // the stream's index in the call: the noise key
         d.flags = kPadded;
         const int64_t nw = (L[s] + W[s] - 1) / W[s];
-        const int64_t ne = pre + nw;  // the stream's MAD sequence: history slots, then windows
         ms[s].woff = wo;
         ms[s].nw = nw;
-        ms[s].eoff = pre > 0 ? eo : wo;
         ms[s].pre = pre;
-        ms[s].hoff = rows;
-        c.max_blocks = std::max<int64_t>(c.max_blocks, (ne + kMomBlock - 1) / kMomBlock);
-        rows += ne / kMomBlock + 1 + (ne % kMomBlock ? 1 : 0);
-        eo += ne;
         woff[s] = wo;
+        for (int64_t w = 0; w < nw; w += 64 * (int64_t)per_wave)
+            segs.push_back(MomSeg{s, (int32_t)std::min<int64_t>(64 * (int64_t)per_wave, nw - w), w});
         const int64_t per = std::max<int64_t>(1, std::min<int64_t>(256, 16384 / W[s]));
         for (int64_t w = 0; w < nw; w += per)
             items.push_back(MomItem{s, (int32_t)std::min<int64_t>(per, nw - w), w});
@@ -174,18 +171,15 @@ int chunk_build(MomChunk& c, int32_t s0, int32_t n, const int64_t* L, const int3
         wo += nw;
     }
     c.total_windows = wo;
-    c.total_ext = pre > 0 ? eo : 0;
     c.n_items = (int64_t)items.size();
+    c.n_segs = (int64_t)segs.size();
     if (rc == RFI_OK) rc = upload(&c.d_desc, desc);
     if (rc == RFI_OK) rc = upload(&c.d_streams, ms);
     if (rc == RFI_OK) rc = upload(&c.d_items, items);
     if (rc == RFI_OK) rc = upload(&c.d_woff, woff);
-    // The selection reads a stream's MAD sequence in whole aligned dwords:
-    // 4 bytes past the end keep the last one inside the allocation.
-    if (rc == RFI_OK) rc = alloc(&c.d_mad, wo + 4);
-    if (rc == RFI_OK && c.total_ext > 0) rc = alloc(&c.d_emad, c.total_ext + 4);
+    if (rc == RFI_OK) rc = upload(&c.d_segs, segs);
+    if (rc == RFI_OK) rc = alloc(&c.d_mad, wo);
     if (rc == RFI_OK) rc = alloc(&c.d_dm, wo);
-    if (rc == RFI_OK) rc = alloc(&c.d_hcnt, rows * 256);
     return rc;
 }
 
@@ -195,7 +189,7 @@ constexpr int64_t kMomChunkMinSamples = int64_t(1) << 26;
 constexpr int kMomChunks = 4;
 
 int mom_build(int32_t n, const int64_t* L, const int32_t* W, const float* K, const int32_t* M,
-              uint64_t seed, int64_t pre, MomPlan** out)
+              uint64_t seed, int64_t pre, int32_t per_wave, MomPlan** out)
 {
     MomPlan* p = new MomPlan;
     if (hipGetDevice(&p->device) != hipSuccess) p->device = 0;
@@ -219,7 +213,7 @@ int mom_build(int32_t n, const int64_t* L, const int32_t* W, const float* K, con
     for (size_t ci = 0; ci + 1 < first.size() && rc == RFI_OK; ++ci) {
         MomChunk& c = p->chunks[ci];
         const int32_t s0 = first[ci], cn = first[ci + 1] - first[ci];
-        rc = chunk_build(c, s0, cn, L + s0, W + s0, K + s0, M + s0, seed, pre);
+        rc = chunk_build(c, s0, cn, L + s0, W + s0, K + s0, M + s0, seed, pre, per_wave);
         c.byte0 = byte0;
         c.win0 = win0;
         for (int s = s0; s < s0 + cn; ++s) {
@@ -247,31 +241,24 @@ int mom_build(int32_t n, const int64_t* L, const int32_t* W, const float* K, con
 
 // Passes 1 and 2 of a chunk on s.
 int chunk_select(MomChunk& c, int64_t pre, const uint8_t* x, uint8_t* y, rfi_window_stats* st, int32_t mom_k,
-                 uint8_t* hist, int32_t* hist_len, hipStream_t s)
+                 const uint8_t* hist, const int32_t* hist_len, hipStream_t s)
 {
     rfi_window_stats* cst = st + c.win0;
-    int rc = plan_execute(c.stats_plan, x + c.byte0, y + c.byte0, cst, s, RFI_SCHED_SPLIT);
+    int rc = plan_execute(c.stats_plan, x + c.byte0, y + c.byte0, cst, s, RFI_SCHED_SPLIT, c.d_mad);
     if (rc != RFI_OK) return rc;
-    hipError_t e = launch_mom_gather(cst, c.total_windows, c.d_mad, s);
-    const uint8_t* emad = c.d_mad;
-    uint8_t* ch = hist ? hist + (int64_t)c.s0 * pre : nullptr;
-    int32_t* chl = hist_len ? hist_len + c.s0 : nullptr;
-    if (e == hipSuccess && pre > 0) {
-        e = launch_mom_extend(c.d_streams, c.n_streams, c.total_ext, c.d_mad, ch, c.d_emad, s);
-        emad = c.d_emad;
-    }
-    if (e == hipSuccess) e = launch_mom_counts(c.d_streams, c.n_streams, c.max_blocks, emad, c.d_hcnt, s);
-    if (e == hipSuccess)
-        e = launch_mom_select(c.d_streams, c.n_streams, c.total_windows, mom_k, emad, c.d_hcnt,
-                              pre > 0 ? chl : nullptr, c.d_dm, s);
-    if (e == hipSuccess && pre > 0) e = launch_mom_history(c.d_streams, c.n_streams, emad, ch, chl, s);
+    const uint8_t* ch = pre > 0 ? hist + (int64_t)c.s0 * pre : nullptr;
+    const int32_t* chl = pre > 0 ? hist_len + c.s0 : nullptr;
+    const hipError_t e = launch_mom_select(c.d_streams, c.d_segs, c.n_segs, mom_k, c.d_mad, ch, chl, c.d_dm, s);
     return e == hipSuccess ? RFI_OK : hip_fail(e);
 }
 
 // Pass 3 of a chunk on s.
-hipError_t chunk_apply(MomChunk& c, uint64_t seed, const uint8_t* x, uint8_t* y, rfi_window_stats* st,
-                       const int64_t* abs_add, hipStream_t s)
+hipError_t chunk_apply(MomChunk& c, int64_t pre, uint64_t seed, const uint8_t* x, uint8_t* y, rfi_window_stats* st,
+                       const int64_t* abs_add, uint8_t* hist, int32_t* hist_len, hipStream_t s)
 {
+    MomHistory h;
+    std::memset(&h, 0, sizeof(h));
+    if (pre > 0) h = MomHistory{c.d_streams, c.d_mad, hist + (int64_t)c.s0 * pre, hist_len + c.s0, c.n_streams};
     LaunchArgs a;
     std::memset(&a, 0, sizeof(a));
     a.streams = c.d_desc;
@@ -280,7 +267,7 @@ hipError_t chunk_apply(MomChunk& c, uint64_t seed, const uint8_t* x, uint8_t* y,
     a.x_base = (uint64_t)(uintptr_t)(x + c.byte0);
     a.y_base = (uint64_t)(uintptr_t)(y + c.byte0);
     return launch_mom_apply(a, c.d_items, c.n_items, c.d_dm, c.d_woff, abs_add ? abs_add + c.s0 : nullptr,
-                            st + c.win0, s);
+                            st + c.win0, h, s);
 }
 
 int mom_execute(MomPlan* p, const void* xv, void* yv, rfi_window_stats* st, int32_t mom_k, const int64_t* abs_add,
@@ -299,7 +286,7 @@ int mom_execute(MomPlan* p, const void* xv, void* yv, rfi_window_stats* st, int3
     if (nc == 1) {
         int rc = chunk_select(p->chunks[0], p->pre, x, y, st, mom_k, hist, hist_len, s);
         if (rc != RFI_OK) return rc;
-        hipError_t e = chunk_apply(p->chunks[0], p->seed, x, y, st, abs_add, s);
+        hipError_t e = chunk_apply(p->chunks[0], p->pre, p->seed, x, y, st, abs_add, hist, hist_len, s);
         return e == hipSuccess ? RFI_OK : hip_fail(e);
     }
     // Pass 3 of chunk c on aux beside passes 1-2 of chunk c + 1 on s.
@@ -311,7 +298,7 @@ int mom_execute(MomPlan* p, const void* xv, void* yv, rfi_window_stats* st, int3
         if (rc != RFI_OK) break;
         e = hipEventRecord(p->ready[c], s);
         if (e == hipSuccess) e = hipStreamWaitEvent(p->aux, p->ready[c], 0);
-        if (e == hipSuccess) e = chunk_apply(p->chunks[c], p->seed, x, y, st, abs_add, p->aux);
+        if (e == hipSuccess) e = chunk_apply(p->chunks[c], p->pre, p->seed, x, y, st, abs_add, hist, hist_len, p->aux);
     }
     // join the auxiliary stream, also after an error, so it never stays forked
     hipError_t j = hipEventRecord(p->join, p->aux);
@@ -319,6 +306,18 @@ int mom_execute(MomPlan* p, const void* xv, void* yv, rfi_window_stats* st, int3
     if (e == hipSuccess) e = j;
     if (rc != RFI_OK) return rc;
     return e == hipSuccess ? RFI_OK : hip_fail(e);
+}
+
+// Groups of 64 windows that a wave of pass 2 takes one after another: one
+// while that leaves at most some 4000 waves (four per SIMD), then as many as
+// keep their number there, since a wave counts a whole history of up to K
+// MADs before its first group; and at least K / 16384 groups, so that a long
+// history is read no more than 256 times per window.
+int32_t groups_per_wave(int32_t n, const int64_t* L, const int32_t* W, int32_t mom_k)
+{
+    int64_t groups = 0;
+    for (int32_t s = 0; s < n; ++s) groups += ((L[s] + W[s] - 1) / W[s] + 63) / 64;
+    return (int32_t)std::min<int64_t>(std::max<int64_t>({1, groups / 4096, mom_k / 16384}), 1 << 16);
 }
 
 std::mutex g_mom_mu;
@@ -345,6 +344,7 @@ int mom_call(const int8_t* x, int8_t* y, int32_t n_streams, const int64_t* lengt
     if (hipGetDevice(&key.device) != hipSuccess) key.device = 0;
     key.stream = (uintptr_t)stream;
     key.pre = carry ? (int64_t)mom_k - 1 : 0;
+    key.per_wave = groups_per_wave(n_streams, lengths, windows, mom_k);
     key.seed = seed;
     key.L.assign(lengths, lengths + n_streams);
     key.W.assign(windows, windows + n_streams);
@@ -363,7 +363,7 @@ int mom_call(const int8_t* x, int8_t* y, int32_t n_streams, const int64_t* lengt
             g_mom.erase(old);
             g_mom_order.erase(g_mom_order.begin());
         }
-        rc = mom_build(n_streams, lengths, windows, k, mode, seed, key.pre, &p);
+        rc = mom_build(n_streams, lengths, windows, k, mode, seed, key.pre, key.per_wave, &p);
         if (rc != RFI_OK) return rc;
         g_mom[key] = p;
         g_mom_order.push_back(key);

@@ -18,9 +18,9 @@ int validate_values(int elem, int32_t n, const int64_t* L, const int32_t* W, con
                     const int32_t* M);
 int plan_build(int elem, int32_t n, const int64_t* L, const int32_t* W, const float* K,
                const int32_t* M, uint64_t seed, rfi_plan** out);
-// sched_override < 0: the plan's own schedule.
+// sched_override < 0: the plan's own schedule.  mads: see LaunchArgs::mad_base.
 int plan_execute(rfi_plan* p, const void* x, void* y, rfi_window_stats* st, hipStream_t s,
-                 int sched_override);
+                 int sched_override, uint8_t* mads = nullptr);
 void plan_free(rfi_plan* p);
 // Free the median-of-MAD and multi-output work tables (rfi_shutdown).
 void mom_shutdown();
