@@ -700,9 +700,11 @@ __global__ __launch_bounds__(NT == 64 ? kBlock : NT, NOISE && (NT == 128 || NT =
     if (it >= a.n_items) return;
     const Item item = a.items[it];
     const StreamView d = resolve(a.streams[item.stream], a);
-    const int64_t first = item.first * (int64_t)d.window;
+    // a tile item is one window, given by its first sample
+    const int64_t win = item.kind == kItemTile ? item.first / d.window : item.first;
+    const int64_t first = win * (int64_t)d.window;
     const int n = (int)min((int64_t)d.window, d.length - first);
-    i16_window<NT, NOISE ? 7 : 3, false>(d, item.first, first, n, a.seed, (int)threadIdx.x & (NT - 1), sm[sub]);
+    i16_window<NT, NOISE ? 7 : 3, false>(d, win, first, n, a.seed, (int)threadIdx.x & (NT - 1), sm[sub]);
 }
 
 union I16FusedSmem {

@@ -152,9 +152,13 @@ __host__ __device__ inline StreamView resolve(const StreamDesc& d, const LaunchA
 // fused: one kernel for all kinds.
 hipError_t launch_i8_tiles(int cls, int modes, int tpw, const LaunchArgs& a, int grid, hipStream_t s);
 // modes: bit m set if some window of the launch uses mode m.
-// small_nt: 64 or 128 if every window of the launch spans at most 4 x that
-// many 16-byte chunks (workgroups of that many threads when the launch has
-// one workgroup per item); 0: 256-thread workgroups.
+// small_nt: threads per window (64, 128 or 256) if every window of the launch
+// spans at most 4 x that many 16-byte chunks of a padded stream that starts
+// at absolute index 0, used when the grid covers every item; 0: windows of
+// any kind, 256 threads each.
+// i8_window_threads: the fewest for windows of up to n samples: n + 30 <= 16 *
+// 4 * NT keeps a window within 4 * NT chunks at any alignment.
+inline int i8_window_threads(int64_t n) { return n <= 4066 ? 64 : n <= 8162 ? 128 : n <= 16354 ? 256 : 0; }
 hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int small_nt = 0);
 hipError_t launch_i8_fused(int modes, const LaunchArgs& a, int grid, hipStream_t s);
 hipError_t launch_i16_tiles(int cls, int modes, const LaunchArgs& a, int grid, hipStream_t s);

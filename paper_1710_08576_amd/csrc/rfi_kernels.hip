@@ -563,38 +563,37 @@ __device__ __forceinline__ TileStats i8_tile_any(const StreamView& d, int64_t fi
 
 // ---------------------------------------------------------------------------
 // int8 generic window: any length, any alignment, optional head segment.
-// One workgroup per window; two passes over the samples in global memory.
 // ---------------------------------------------------------------------------
-struct GenericSmem {
+// Scratch of a workgroup that holds kBlock / NT windows of NT threads each.
+template <int NT>
+struct I8WinSmem {
+    static constexpr int PER = kBlock / NT;
     union {
         uint32_t hist[256];                                // two-pass path
-        __align__(16) uint32_t whist[4 * kWaveHistWords];  // register path: per-wave replicas
+        __align__(16) uint32_t whist[4 * kWaveHistWords];  // per-wave replicated histograms
     };
-    __align__(16) uint32_t tot[256];
-    __align__(16) uint32_t pc[kPadC];
-    WinParams prm;
+    WinParams prm[PER];
+    int64_t j0[PER];     // absolute index of each window's first chunk
+    uint32_t key[PER];   // and its stream's Philox key word
+    uint32_t noise_counts[4];
+    __device__ NoiseScratch noise()
+    {
+        return NoiseScratch{noise_counts, whist, reinterpret_cast<uint4*>(whist + 256)};
+    }
 };
+using GenericSmem = I8WinSmem<kBlock>;
 
-// Register path for a generic int8 window (zero, clip, statistics only,
-// and noise where the instance allows it) with no head segment, 16-byte
-// aligned input and output, and 512 <= n samples in at most four 16-byte
-// chunks per thread: the aligned chunks covering [a, a + n) are loaded (four
-// per lane), their in-window bytes counted into per-wave replicated histograms,
-// the counts summed and selected as the wide tiles do, and the chunks
-// replaced in registers and stored (whole chunks as one 16-byte store, the
-// two edge chunks byte by byte, so a neighbouring window's bytes are never
-// written).
-constexpr int kGenericRegMin = 512;
+__device__ __forceinline__ uint32_t byte_of(uint32_t v, int b) { return (v >> (8 * b)) & 0xFFu; }
 
-// NOISE: noise-mode windows qualify too, when each dword of the stream holds
-// one Philox block (absolute index of the stream's first sample a multiple
-// of 4).
-// HEAD: so do windows with a head segment of whole chunks (a serving
-// stream's carry, whose blocks start and end on 16 samples).
+// Whether a window qualifies for i8_window: 16-byte aligned input and
+// output, no head segment (HEAD: or one of whole chunks, as a serving
+// stream's carry whose blocks start and end on 16 samples), at most four
+// chunks per thread.  NOISE: noise windows too, where each dword of the
+// stream holds one Philox block (absolute index of the stream's first
+// sample a multiple of 4).
 template <bool NOISE, int NT, bool HEAD>
-__device__ __forceinline__ bool i8_generic_reg_ok(const StreamView& d, int64_t a, int n)
+__device__ __forceinline__ bool i8_window_ok(const StreamView& d, int64_t a, int n)
 {
-    if (n < kGenericRegMin) return false;
     if (d.head_len != 0 && (!HEAD || ((d.head_len | (uint32_t)(uintptr_t)d.x_head) & 15u) != 0)) return false;
     if (d.mode == RFI_MODE_NOISE && (!NOISE || (d.abs_base & 3) != 0)) return false;
     if (((uintptr_t)d.x | (uintptr_t)d.y) & 15u) return false;
@@ -604,165 +603,201 @@ __device__ __forceinline__ bool i8_generic_reg_ok(const StreamView& d, int64_t a
     return ((a + n + 15) >> 4) - (a >> 4) <= 4 * NT;
 }
 
-__device__ __forceinline__ uint32_t byte_of(uint32_t v, int b) { return (v >> (8 * b)) & 0xFFu; }
-
-// NT: threads of the workgroup (256, or 64 / 128 for launches whose windows
-// span at most 256 / 512 chunks, so that more windows are in flight per CU).
-template <bool NOISE, int NT, bool HEAD, class Smem>
-__device__ void i8_generic_reg(const StreamView& d, int64_t w, int64_t a, int n, uint64_t seed, Smem& sm)
+// One window [a, a + n) in registers, by the NT threads `tid` of the
+// workgroup's window `sub` (n = 0: no window, which takes part in the
+// barriers).  The 16-byte chunks covering it are loaded, four per thread,
+// and counted into per-wave replicated histograms; the samples of the edge
+// chunks outside the window are counted as the largest value and taken out
+// of its count again.  The counts are summed and selected as the wide tiles
+// do; whole chunks are stored as one, the dwords and bytes of the edge
+// chunks one by one, so that a neighbouring window's bytes are never
+// written.
+//
+// The flagged dwords of every window of the workgroup are pooled for the
+// draws.  With one window per workgroup of 64 or 128 threads, a window of
+// 5000 samples took a wave's draws for its 28 flagged dwords, one of 1000
+// for its 6.
+//
+// MODES: bit m set if the launch has windows in mode m (one bit: the mode is
+// fixed at compile time).
+template <int NT, int MODES, bool HEAD>
+__device__ __forceinline__ void i8_window(const StreamView& d, int64_t w, int64_t a, int n, uint64_t seed, int sub,
+                                          int tid, I8WinSmem<NT>& sm)
 {
-    const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const uint8_t* xb = static_cast<const uint8_t*>(d.x);
-    uint8_t* yb = static_cast<uint8_t*>(d.y);
-    const int64_t c0 = a >> 4, e = a + n;
-    const int64_t nch = ((e + 15) >> 4) - c0;
+    constexpr bool NOISE = (MODES & 4) != 0;
+    const int mode = MODES == 1   ? RFI_MODE_ZERO
+                     : MODES == 2 ? RFI_MODE_CLIP
+                     : MODES == 4 ? RFI_MODE_NOISE
+                     : MODES == 8 ? kModeStats
+                                  : d.mode;
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // of the workgroup
+    const int lead = (int)(a & 15);
+    const int nch = n > 0 ? (lead + n + 15) >> 4 : 0;
+    const int tail = ((lead + n - 1) & 15) + 1;
+    const int64_t base = a - lead;  // first byte of chunk 0
+    const uint8_t* xb = static_cast<const uint8_t*>(d.x) + base;
+    const bool edges = lead != 0 || tail != 16;
     uint32_t v[16];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t c = tid + k * NT;
+    for (int i = 0; i < 4; ++i) {
+        const int c = tid + i * NT;
         uint4 t = make_uint4(0, 0, 0, 0);
         if (c < nch) {
-            const int64_t at = (c0 + c) * 16;
-            t = gload16_nt(HEAD ? (at < d.head_len ? static_cast<const uint8_t*>(d.x_head) + at : xb + (at - d.head_len))
-                                : xb + at);
+            const uint8_t* at = xb + c * 16;
+            if constexpr (HEAD) {
+                const int64_t p = base + c * 16;
+                at = p < d.head_len ? static_cast<const uint8_t*>(d.x_head) + p : at - d.head_len;
+            }
+            t = gload16_nt(at);
         }
-        v[4 * k] = t.x;
-        v[4 * k + 1] = t.y;
-        v[4 * k + 2] = t.z;
-        v[4 * k + 3] = t.w;
+        v[4 * i] = t.x;
+        v[4 * i + 1] = t.y;
+        v[4 * i + 2] = t.z;
+        v[4 * i + 3] = t.w;
     }
-    __syncthreads();  // the previous item is done with the scratch
+    if constexpr (NT == kBlock) __syncthreads();  // the previous item is done with the scratch
     uint32_t* h = sm.whist + wave * kWaveHistWords;
     wide_hist_zero(h);
-    if constexpr (NT > 64)
-        for (int i = tid; i < 256; i += NT) sm.tot[i] = 0;
-    __syncthreads();
+    wave_sync();
     uint32_t* hl = h + (lane & 3) * kRepStride;
+    // bytes of dword j of chunk c that belong to the window
+    auto inside = [&](int c, int j) -> uint32_t {
+        const int f = (c == 0 ? lead : 0) - 4 * j, e = (c == nch - 1 ? tail : 16) - 4 * j;
+        const uint32_t lo = f <= 0 ? ~0u : f >= 4 ? 0u : ~0u << (8 * f);
+        const uint32_t hi = e >= 4 ? ~0u : e <= 0 ? 0u : (1u << (8 * e)) - 1u;
+        return lo & hi;
+    };
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t c = tid + k * NT;
-        if (c >= nch) continue;
-        const int64_t cb = (c0 + c) * 16;
-        if (cb >= a && cb + 16 <= e) {
+    for (int i = 0; i < 4; ++i) {
+        const int c = tid + i * NT;
+        if (c < nch) {
+            uint32_t x[4] = {v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
+            if (edges && (c == 0 || c == nch - 1)) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) wide_hist_add(hl, v[4 * k + j]);
-        } else {
+                for (int j = 0; j < 4; ++j) x[j] = bit_select(inside(c, j), x[j], 0x7F7F7F7Fu);
+            }
 #pragma unroll
-            for (int b = 0; b < 16; ++b)
-                if (cb + b >= a && cb + b < e) atomicAdd(hl + byte_of(v[4 * k + b / 4], b % 4), 1u);
+            for (int j = 0; j < 4; ++j) {
+                wide_hist_add(hl, x[j]);
+                sched_fence();
+            }
         }
     }
     wave_sync();
     uint32_t cnt[4];
     wide_hist_totals(h, cnt);
+    const int wv = NT == 64 ? 0 : wave & (NT / 64 - 1);  // wave of the window
     if constexpr (NT > 64) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) atomicAdd(&sm.tot[lane * 4 + j], cnt[j]);
+        // Each wave leaves its totals in its second replica, which only it
+        // has read.  Two waves both add and select (no second exchange);
+        // four leave that to the first.
+        *reinterpret_cast<uint4*>(h + kRepStride + 4 * lane) = make_uint4(cnt[0], cnt[1], cnt[2], cnt[3]);
         __syncthreads();
-        if (wave == 0) {
-            const uint4 t = *reinterpret_cast<const uint4*>(sm.tot + lane * 4);
-            cnt[0] = t.x;
-            cnt[1] = t.y;
-            cnt[2] = t.z;
-            cnt[3] = t.w;
-        }
-    }
-    if (wave == 0) {
-        int mb, D;
-        wide_select(cnt, sm.pc, (uint32_t)((n - 1) / 2 + 1), mb, D);
-        WinParams p;
-        rfi_window_stats s;
-        wide_params(sm.pc, mb, D, d.k, n, p, s);
-        if (lane == 0) {
-            sm.prm = p;
-            if (d.stats) d.stats[w] = s;
-            if (d.mode == kModeStats && d.mads) gstore(d.mads + w, (uint8_t)D);
-        }
-    }
-    __syncthreads();
-    if (d.mode == kModeStats) return;
-    const WinParams p = sm.prm;
-    const uint32_t lo = rep_i16(p.lo * 256), hi = rep_i16(p.hi * 256);
-    const uint32_t lo_u = rep_i16((p.lo + 128) * 256), hi_u = rep_i16((p.hi + 128) * 256);
-    bool noise = false;
-    if constexpr (NOISE) {
-        if (d.mode == RFI_MODE_NOISE) {
-            // One Philox block per dword holding a flagged sample (dword q
-            // of a lane: chunk tid + (q / 4) NT, samples 4 (q % 4) ..), the
-            // flagged dwords of the workgroup pooled so that the draws take
-            // as few waves as there are flagged dwords.  The histograms are
-            // dead once every wave holds the window's parameters.
-            noise = true;
-            uint32_t cf = 0;
+        if (NT == 128 || wv == 0) {
+            const uint32_t* t0 = sm.whist + (wave - wv) * kWaveHistWords + kRepStride + 4 * lane;
+            cnt[0] = cnt[1] = cnt[2] = cnt[3] = 0;
 #pragma unroll
-            for (int q = 0; q < 16; ++q)
-                if (tid + (q >> 2) * NT < nch) cf |= ((clamp_i8x4(v[q], lo, hi) ^ v[q]) != 0 ? 1u : 0u) << q;
-            const int64_t jb = d.abs_base + c0 * 16;
-            if constexpr (NT >= 128) {
-                auto merged = [&](int wv, int ln, int slot, int part, uint32_t x) -> uint32_t {
-                    const int64_t j0 = jb + ((int64_t)(wv * 64 + ln) + (int64_t)slot * NT) * 16 + 4 * part;
-                    const uint32_t nz = noise_quad_i8((uint64_t)j0, seed, d.key, p.m, p.sq8);
-                    return byte_perm(nz, x, flag_sel_i8x4(x, lo_u, hi_u));
-                };
-                static_assert(sizeof(sm.whist) >= (16 + 2 * NT) * 4, "noise list in the histograms");
-                pool_noise<4, NT>(v, cf,
-                                  NoiseScratch{sm.whist, sm.whist + 16, reinterpret_cast<uint4*>(sm.whist + 16 + NT)},
-                                  merged);
-            } else {
-                // One-wave workgroups (windows of at most 256 chunks) hold
-                // few flagged dwords: each lane draws its own, in a loop over
-                // them (no list, no barriers, fewer registers).
-                while (cf) {
-                    const int q = __builtin_ctz(cf);
-                    cf &= cf - 1;
-                    uint32_t x = 0;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) x = i == q ? v[i] : x;
-                    const int64_t j0 = jb + (tid + (int64_t)(q >> 2) * NT) * 16 + 4 * (q & 3);
-                    const uint32_t nz = noise_quad_i8((uint64_t)j0, seed, d.key, p.m, p.sq8);
-                    x = byte_perm(nz, x, flag_sel_i8x4(x, lo_u, hi_u));
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) v[i] = i == q ? x : v[i];
-                }
+            for (int q = 0; q < NT / 64; ++q) {
+                const uint4 t = *reinterpret_cast<const uint4*>(t0 + q * kWaveHistWords);
+                cnt[0] += t.x;
+                cnt[1] += t.y;
+                cnt[2] += t.z;
+                cnt[3] += t.w;
             }
         }
     }
+    WinParams p;
+    if (n > 0 && (NT <= 128 || wv == 0)) {
+        if (lane == 63) cnt[3] -= (uint32_t)(nch * 16 - n);  // the edge chunks' other samples
+        int mb, D;
+        rfi_window_stats s;
+        // the cumulative counts take the place of the wave's first replica
+        wide_select(cnt, h, (uint32_t)((n - 1) / 2 + 1), mb, D);
+        wide_params(h, mb, D, d.k, n, p, s);
+        if (lane == 0 && wv == 0) {
+            if (NOISE || NT == kBlock) sm.prm[sub] = p;
+            if (d.stats) d.stats[w] = s;
+            if (mode == kModeStats && d.mads) gstore(d.mads + w, (uint8_t)D);
+            if constexpr (NOISE) {
+                sm.j0[sub] = d.abs_base + base;
+                sm.key[sub] = d.key;
+            }
+        }
+    }
+    if constexpr (NT == kBlock) {
+        __syncthreads();
+        p = sm.prm[0];
+    }
+    const uint32_t lo = rep_i16(p.lo * 256), hi = rep_i16(p.hi * 256);
+    const uint32_t lo_u = rep_i16((p.lo + 128) * 256), hi_u = rep_i16((p.hi + 128) * 256);
+    const bool noise = NOISE && mode == RFI_MODE_NOISE;
+    if constexpr (NOISE) {
+        uint32_t cf = 0;  // bit q: dword q holds a flagged sample
+        if (noise) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t c = tid + k * NT;
+            for (int q = 0; q < 16; ++q)
+                if (tid + (q >> 2) * NT < nch) cf |= ((clamp_i8x4(v[q], lo, hi) ^ v[q]) != 0 ? 1u : 0u) << q;
+        }
+        auto merged = [&](int wvs, int ln, int slot, int part, uint32_t x) -> uint32_t {
+            const int s = NT == kBlock ? 0 : wvs / (NT / 64);
+            const int t = NT == 64 ? ln : (wvs & (NT / 64 - 1)) * 64 + ln;
+            const int64_t j0 = sm.j0[s] + (int64_t)(t + slot * NT) * 16 + 4 * part;
+            const WinParams q = sm.prm[s];
+            const uint32_t ql = rep_i16((q.lo + 128) * 256), qh = rep_i16((q.hi + 128) * 256);
+            const uint32_t nz = noise_quad_i8((uint64_t)j0, seed, NT == kBlock ? d.key : sm.key[s], q.m, q.sq8);
+            return byte_perm(nz, x, flag_sel_i8x4(x, ql, qh));
+        };
+        static_assert(sizeof(sm.whist) >= kNoiseAliasWords * 4, "noise list in the histograms");
+        // every thread of the workgroup, whatever its window's mode
+        pool_noise<4>(v, cf, sm.noise(), merged);
+    }
+    if (mode == kModeStats) return;
+    uint8_t* yb = static_cast<uint8_t*>(d.y) + base;
+    const bool clip = mode == RFI_MODE_CLIP;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int c = tid + i * NT;
         if (c >= nch) continue;
-        const int64_t cb = (c0 + c) * 16;
         uint32_t r[4];
-        const bool clip = d.mode == RFI_MODE_CLIP;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const uint32_t x = v[4 * k + j];
+            const uint32_t x = v[4 * i + j];
             r[j] = noise ? x : clip ? clamp_i8x4(x, lo, hi) : byte_perm(0u, x, flag_sel_i8x4(x, lo_u, hi_u));
         }
-        if (cb >= a && cb + 16 <= e) {
-            gstore16_nt(yb + cb, make_uint4(r[0], r[1], r[2], r[3]));
-        } else {
+        uint8_t* at = yb + c * 16;
+        if (edges && (c == 0 || c == nch - 1)) {
 #pragma unroll
-            for (int b = 0; b < 16; ++b)
-                if (cb + b >= a && cb + b < e) gstore(yb + cb + b, (uint8_t)byte_of(r[b / 4], b % 4));
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t m = inside(c, j);
+                if (m == ~0u) {
+                    gstore(reinterpret_cast<uint32_t*>(at) + j, r[j]);
+                } else if (m != 0) {
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        if (byte_of(m, b)) gstore(at + 4 * j + b, (uint8_t)byte_of(r[j], b));
+                }
+            }
+        } else {
+            gstore16_nt(at, make_uint4(r[0], r[1], r[2], r[3]));
         }
     }
 }
 
-// REG: the register path is compiled in (kernels that may see zero or clip
-// windows).
-// REG: zero/clip windows may take the register path; REG_NOISE: noise
-// windows too (kept out of the fused kernels, whose register budget the
-// inlined draw would raise).
-// HEAD: the launch may hold windows with a head segment.
-template <bool REG = true, bool REG_NOISE = false, int NT = kBlock, bool HEAD = NT == kBlock, class Smem = GenericSmem>
-__device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, Smem& sm)
+// A generic window in a workgroup of kBlock threads: in registers if it
+// qualifies, else by two passes over the samples in global memory.
+// REG: zero/clip windows may stay in registers; REG_NOISE: noise windows too
+// (kept out of the fused kernels, whose register budget the inlined draw
+// would raise).
+template <bool REG = true, bool REG_NOISE = false>
+__device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, GenericSmem& sm)
 {
+    constexpr int NT = kBlock;
     const int W = d.window;
     const int64_t a = w * (int64_t)W;
     const int n = (int)min((int64_t)W, d.length - a);
-    if (REG && i8_generic_reg_ok<REG_NOISE, NT, HEAD>(d, a, n)) {
-        i8_generic_reg<REG_NOISE, NT, HEAD>(d, w, a, n, seed, sm);
+    if (REG && i8_window_ok<REG_NOISE, NT, true>(d, a, n)) {
+        i8_window<NT, REG_NOISE ? 15 : 11, true>(d, w, a, n, seed, 0, (int)threadIdx.x, sm);
         return;
     }
     const int tid = (int)threadIdx.x;
@@ -779,14 +814,14 @@ __device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, Smem& 
         rfi_window_stats s;
         params_i8<64>(sm.hist, mb, D, d.k, n, p, s);
         if (tid == 0) {
-            sm.prm = p;
+            sm.prm[0] = p;
             if (d.stats) d.stats[w] = s;
             if (d.mode == kModeStats && d.mads) gstore(d.mads + w, (uint8_t)D);
         }
     }
     __syncthreads();
     if (d.mode == kModeStats) return;
-    const WinParams p = sm.prm;
+    const WinParams p = sm.prm[0];
     for (int i = tid; i < n; i += NT) {
         const int x = load_logical<int8_t>(d, a + i);
         int yv = x;
@@ -798,21 +833,6 @@ __device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, Smem& 
         gstore(y + a + i, (int8_t)yv);
     }
 }
-
-// Scratch of the generic kernels with NW = 1 or 2 waves: their replicated
-// histograms (or the plain histogram of the two-pass path), the summed
-// counts (two waves), the cumulative counts and the window's parameters
-// (5.3 KB for one wave, so LDS admits 30 workgroups per CU; 10.6 KB for two).
-template <int NW>
-struct GenericSmemN {
-    union {
-        uint32_t hist[256];
-        __align__(16) uint32_t whist[NW * kWaveHistWords];
-    };
-    __align__(16) uint32_t tot[NW > 1 ? 256 : 4];
-    __align__(16) uint32_t pc[kPadC];
-    WinParams prm;
-};
 
 // ---------------------------------------------------------------------------
 // Kernels.  All loop over items with a grid stride, so the same kernel
@@ -858,18 +878,28 @@ __global__ __launch_bounds__(kBlock) void k_i8_tiles(LaunchArgs a)
     }
 }
 
-// NT = 64 or 128 threads per window, for launches whose windows all fit
-// 4 * NT chunks (n <= 4066 or 8162 at any alignment): up to 30 or 15
-// windows in flight per CU instead of the 8 of the 256-thread kernel.  One
-// item per workgroup.
-template <int NT, bool NOISE>
-__global__ __launch_bounds__(NT, NOISE && NT >= 128 ? 8 : 0) void k_i8_generic_small(LaunchArgs a)
+// Windows of at most 4 * NT chunks of padded streams (plans), kBlock / NT of
+// them per workgroup.  Bound by the VALU (a window's fixed work: clearing and
+// adding up the replicas, the search) below 3000 samples, near HBM from
+// there on.  60 x 2^22 samples, zero / clip / noise, against one window per
+// workgroup of 64, 128 or 256 threads before, with the edge chunks counted
+// and stored byte by byte: W 1000 210 / 203 / 342 -> 172 / 167 / 290 us, 3000
+// 121 / 114 / 176 -> 107 / 101 / 145, 5000 119 / 112 / 160 -> 110 / 105 / 152,
+// 12000 94 / 90 / 126 -> 91 / 88 / 115.
+template <int NT, int MODES>
+__global__ __launch_bounds__(kBlock, 8) void k_i8_windows(LaunchArgs a)
 {
-    __shared__ GenericSmemN<NT / 64> sm;
-    if ((int64_t)blockIdx.x >= a.n_items) return;
-    const Item item = a.items[blockIdx.x];
+    __shared__ I8WinSmem<NT> sm;
+    constexpr int PER = kBlock / NT;
+    const int sub = __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
+    const int64_t it = (int64_t)blockIdx.x * PER + sub;
+    if (PER == 1 && it >= a.n_items) return;
+    const bool has = it < a.n_items;
+    const Item item = a.items[has ? it : 0];
     const StreamView d = resolve(a.streams[item.stream], a);
-    i8_generic<true, NOISE, NT>(d, item.first, a.seed, sm);
+    const int64_t first = item.first * (int64_t)d.window;
+    const int n = has ? (int)min((int64_t)d.window, d.length - first) : 0;
+    i8_window<NT, MODES, false>(d, item.first, first, n, a.seed, sub, (int)threadIdx.x & (NT - 1), sm);
 }
 
 // NOISE: noise windows may take the register path (launched only for items
@@ -1492,16 +1522,32 @@ hipError_t launch_i8_tiles(int cls, int modes, int tpw, const LaunchArgs& a, int
     if (!k) return hipErrorInvalidValue;
     return launch(k, a, persist ? grid : (int)((a.n_items + tpw - 1) / tpw), s);
 }
+template <int NT>
+static void (*i8_window_kernel(int modes))(LaunchArgs)
+{
+    switch (modes) {
+        case 1: return k_i8_windows<NT, 1>;
+        case 2: return k_i8_windows<NT, 2>;
+        case 3: return k_i8_windows<NT, 3>;
+        case 4: return k_i8_windows<NT, 4>;
+        case 1 << kModeStats: return k_i8_windows<NT, 1 << kModeStats>;
+        default: return k_i8_windows<NT, 7>;
+    }
+}
+
 hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int small_nt)
 {
     const bool persist = grid < a.n_items;
-    if ((small_nt == 64 || small_nt == 128) && !persist) {
-        if (a.n_items <= 0) return hipSuccess;
-        if (a.n_items > (1 << 30)) return hipErrorInvalidValue;
-        const bool noise = (modes & 4) != 0;
-        void (*k)(LaunchArgs) = small_nt == 64 ? (noise ? k_i8_generic_small<64, true> : k_i8_generic_small<64, false>)
-                                               : (noise ? k_i8_generic_small<128, true> : k_i8_generic_small<128, false>);
-        hipLaunchKernelGGL(k, dim3((unsigned)a.n_items), dim3((unsigned)small_nt), 0, s, a);
+    if (small_nt != 0 && !persist && a.n_items > 0) {
+        void (*k)(LaunchArgs) = small_nt == 64    ? i8_window_kernel<64>(modes)
+                                : small_nt == 128 ? i8_window_kernel<128>(modes)
+                                : small_nt == 256 ? i8_window_kernel<256>(modes)
+                                                  : nullptr;
+        if (!k) return hipErrorInvalidValue;
+        const int64_t per = kBlock / small_nt;
+        const int64_t blocks = (a.n_items + per - 1) / per;
+        if (blocks > (1 << 30)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
         return hipGetLastError();
     }
     void (*k)(LaunchArgs) = (modes & 4) ? (persist ? k_i8_generic<true, true> : k_i8_generic<false, true>)

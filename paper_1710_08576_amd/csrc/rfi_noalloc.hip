@@ -254,7 +254,7 @@ extern "C" int rfi_mad_filter_noalloc(const int8_t* x, int8_t* y, int32_t n_stre
         const int grid = (int)std::min<int64_t>(count[g], (int64_t)1 << 30);
         hipError_t e;
         if (g == 0) {
-            const int small = gen_nmax <= 4066 ? 64 : gen_nmax <= 8162 ? 128 : 0;
+            const int small = i8_window_threads(gen_nmax);
             e = launch_i8_generic(la, gen_modes, grid, hs, small);
         } else {
             const int cls = (g - 1) / 3, m = (g - 1) % 3;
