@@ -283,6 +283,29 @@ __device__ __forceinline__ uint32_t flag_sel_i8x4(uint32_t x, uint32_t lo_u, uin
     return 0x03020100u | (fo << 10) | (fe << 2);
 }
 
+// Whether one of the four int8 samples of x lies outside [lo, hi]: the sum of
+// the distances to both bounds is 4 (hi - lo) exactly if none does.  lo4,
+// hi4: the biased bounds (lo + 128, hi + 128) in every byte; span4 =
+// 4 (hi - lo).  Two v_sad_u8, where the packed clamp and its comparison take
+// ten instructions.
+__device__ __forceinline__ bool outside_i8x4(uint32_t x, uint32_t lo4, uint32_t hi4, uint32_t span4)
+{
+    const uint32_t u = x ^ 0x80808080u;
+    return __builtin_amdgcn_sad_u8(u, hi4, __builtin_amdgcn_sad_u8(u, lo4, 0u)) != span4;
+}
+
+// The same for the two int16 samples of x and of y (bounds biased by 32768
+// in both halves).
+__device__ __forceinline__ bool outside_i16x4(uint32_t x, uint32_t y, uint32_t lo2, uint32_t hi2, uint32_t span4)
+{
+    const uint32_t u = x ^ 0x80008000u, w = y ^ 0x80008000u;
+    const uint32_t s = __builtin_amdgcn_sad_u16(u, hi2, __builtin_amdgcn_sad_u16(u, lo2, 0u));
+    return __builtin_amdgcn_sad_u16(w, hi2, __builtin_amdgcn_sad_u16(w, lo2, s)) != span4;
+}
+
+// A byte in all four bytes.
+__device__ __forceinline__ uint32_t rep_i8(int v) { return ((uint32_t)v & 0xFFu) * 0x01010101u; }
+
 __device__ __forceinline__ uint32_t byte_perm(uint32_t hi_src, uint32_t lo_src, uint32_t sel)
 {
     return __builtin_amdgcn_perm(hi_src, lo_src, sel);

@@ -472,27 +472,20 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
     const int sq8 = (int)__fmul_rn(sig, 256.0f);
     const int mode = MODES == 1 ? RFI_MODE_ZERO : MODES == 2 ? RFI_MODE_CLIP : MODES == 4 ? RFI_MODE_NOISE : d.mode;
     uint32_t nflag = 0;
-    uint32_t cf = 0;  // bit 2i + h: dwords 2h, 2h + 1 of chunk i hold a flagged sample
+    if (mode != RFI_MODE_NOISE) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (WHOLE || tid + i * NT < nch) {
+        for (int i = 0; i < 4; ++i) {
+            if (WHOLE || tid + i * NT < nch) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t any = 0;
-#pragma unroll
-                for (int j = 2 * h; j < 2 * h + 2; ++j) {
+                for (int j = 0; j < 4; ++j) {
                     const int q = 4 * i + j;
                     const uint32_t x = v[q];
                     const uint32_t c = pk_clamp_i16(x, lo2, hi2);
-                    const uint32_t diff = c ^ x;                 // non-zero halves: flagged samples
-                    const uint32_t bit = pk_umin1(diff);
+                    const uint32_t bit = pk_umin1(c ^ x);  // 1 in the halves of flagged samples
                     nflag = udot2_u16(bit, 0x00010001u, nflag);
                     pin_vgpr(nflag);
-                    if (mode == RFI_MODE_CLIP) v[q] = c;
-                    else if (mode == RFI_MODE_ZERO) v[q] = x & ~pk_sub_u16(0u, bit);
-                    else any |= diff;
+                    v[q] = mode == RFI_MODE_CLIP ? c : x & ~pk_sub_u16(0u, bit);
                 }
-                if (mode == RFI_MODE_NOISE) cf |= (any != 0 ? 1u : 0u) << (2 * i + h);
             }
         }
     }
@@ -505,9 +498,17 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
                 const uint2 nz = noise_quad_i16((uint64_t)(abs0 + off), seed, key1, m, sq8);
                 const uint32_t m0 = nonzero_half_mask(pk_clamp_i16(x.x, lo2, hi2) ^ x.x);
                 const uint32_t m1 = nonzero_half_mask(pk_clamp_i16(x.y, lo2, hi2) ^ x.y);
+                // every flagged sample is in one part, drawn once
+                nflag += (__popc(m0) + __popc(m1)) >> 4;
                 return make_uint2((x.x & ~m0) | (nz.x & m0), (x.y & ~m1) | (nz.y & m1));
             };
             if constexpr (NT == 64) wave_sync();  // the counts in h are dead: the list takes their place
+            const uint32_t lob = rep_i16(lo + 32768), hib = rep_i16(hi + 32768), span4 = 4u * (uint32_t)(hi - lo);
+            uint32_t cf = 0;  // bit q: dwords 2q, 2q + 1 hold a flagged sample
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (WHOLE || tid + (q >> 1) * NT < nch)
+                    cf |= (outside_i16x4(v[2 * q], v[2 * q + 1], lob, hib, span4) ? 1u : 0u) << q;
             pool_noise_reserved<2, NT>(v, cf, sm.noise(), tid, wave, merged);
         }
     }

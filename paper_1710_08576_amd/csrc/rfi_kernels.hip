@@ -331,10 +331,10 @@ __device__ __forceinline__ void i8_replace(const StreamView& d, int64_t first, u
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const WinParams p = bounds(i);
-            const uint32_t lo = rep_i16(p.lo * 256), hi = rep_i16(p.hi * 256);
+            const uint32_t lo4 = rep_i8(p.lo + 128), hi4 = rep_i8(p.hi + 128), span4 = 4u * (uint32_t)(p.hi - p.lo);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                cf |= ((clamp_i8x4(v[4 * i + j], lo, hi) ^ v[4 * i + j]) != 0 ? 1u : 0u) << (4 * i + j);
+                cf |= (outside_i8x4(v[4 * i + j], lo4, hi4, span4) ? 1u : 0u) << (4 * i + j);
             sched_fence();
         }
         if constexpr (NS) {
@@ -733,11 +733,12 @@ __device__ __forceinline__ void i8_window(const StreamView& d, int64_t w, int64_
     const uint32_t lo_u = rep_i16((p.lo + 128) * 256), hi_u = rep_i16((p.hi + 128) * 256);
     const bool noise = NOISE && mode == RFI_MODE_NOISE;
     if constexpr (NOISE) {
+        const uint32_t lo4 = rep_i8(p.lo + 128), hi4 = rep_i8(p.hi + 128), span4 = 4u * (uint32_t)(p.hi - p.lo);
         uint32_t cf = 0;  // bit q: dword q holds a flagged sample
         if (noise) {
 #pragma unroll
             for (int q = 0; q < 16; ++q)
-                if (tid + (q >> 2) * NT < nch) cf |= ((clamp_i8x4(v[q], lo, hi) ^ v[q]) != 0 ? 1u : 0u) << q;
+                if (tid + (q >> 2) * NT < nch) cf |= (outside_i8x4(v[q], lo4, hi4, span4) ? 1u : 0u) << q;
         }
         auto merged = [&](int wvs, int ln, int slot, int part, uint32_t x) -> uint32_t {
             const int s = NT == kBlock ? 0 : wvs / (NT / 64);
