@@ -146,9 +146,8 @@ __device__ __forceinline__ void params_i8(const uint32_t* hw, int mb, int D, flo
 // ---------------------------------------------------------------------------
 constexpr int kRepStride = 264;                // 256 bins + 8 words
 constexpr int kWaveHistWords = 4 * kRepStride;  // per wave
-// Padded cumulative array: pc[0..3] = 0 (C[-4..-1]), pc[4 + v] = C[v] for
-// the biased value v = 0..255, pc[260..263] = N.
-constexpr int kPadC = 264;
+// Padded cumulative array (264 words): pc[0..3] = 0 (C[-4..-1]), pc[4 + v] =
+// C[v] for the biased value v = 0..255, pc[260..263] = N.
 
 __device__ __forceinline__ void wide_hist_zero(uint32_t* h)
 {
@@ -352,6 +351,67 @@ __device__ __forceinline__ void i8_replace(const StreamView& d, int64_t first, u
     }
 }
 
+// Median bin mb (median + 128) and MAD D of the wide windows (W >= 4096) of
+// a tile, from each wave's own histogram of its 4 KiB.  pc: the window's
+// padded cumulative counts.  W 16384: mb, D and pc are wave 0's alone.
+template <int W, bool NS>
+__device__ __forceinline__ void i8_wide_tile_select(I8TileSmem<W, NS>& sm, const uint32_t (&v)[16], int& mb, int& D,
+                                                    uint32_t*& pc)
+{
+    using Smem = I8TileSmem<W, NS>;
+    constexpr uint32_t need = (W - 1) / 2 + 1;
+    constexpr int WPW = Smem::kWPW;
+    const int lane = lane_id();
+    const int wave = (int)(threadIdx.x >> 6);
+    const int wl = wave / WPW;
+    uint32_t* h = sm.hist + wave * kWaveHistWords;
+    if constexpr (WPW > 1) __syncthreads();  // the previous tile is done with tot and prm
+    wide_hist_zero(h);
+    wave_sync();
+    uint32_t* hl = h + (lane & 3) * kRepStride;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        wide_hist_add(hl, v[q]);
+        sched_fence();
+    }
+    wave_sync();
+    uint32_t c[4];
+    wide_hist_totals(h, c);
+    // The cumulative counts overwrite replica 0 of the selecting wave,
+    // whose reads were all issued above.
+    pc = h;
+    if constexpr (WPW == 2) {
+        // W 8192: both waves publish their totals; after one barrier each
+        // wave adds its window's two and selects by itself (the same
+        // values in both, no second exchange).
+        *reinterpret_cast<uint4*>(sm.tot + wave * 256 + lane * 4) = make_uint4(c[0], c[1], c[2], c[3]);
+        __syncthreads();
+        const uint4 t0 = *reinterpret_cast<const uint4*>(sm.tot + (wl * 2) * 256 + lane * 4);
+        const uint4 t1 = *reinterpret_cast<const uint4*>(sm.tot + (wl * 2 + 1) * 256 + lane * 4);
+        c[0] = t0.x + t1.x;
+        c[1] = t0.y + t1.y;
+        c[2] = t0.z + t1.z;
+        c[3] = t0.w + t1.w;
+    } else if constexpr (WPW == 4) {
+        // W 16384: the four waves' totals are added in LDS and one wave
+        // selects (selecting in all four measured slower).
+        if (threadIdx.x < 64) reinterpret_cast<uint4*>(sm.tot)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) atomicAdd(&sm.tot[lane * 4 + j], c[j]);
+        __syncthreads();
+        if (wave == 0) {
+            const uint4 t = *reinterpret_cast<const uint4*>(sm.tot + lane * 4);
+            c[0] = t.x;
+            c[1] = t.y;
+            c[2] = t.z;
+            c[3] = t.w;
+        }
+    }
+    mb = D = 0;
+    if (WPW < 4 || wave == 0) wide_select(c, pc, need, mb, D);
+}
+
 // Processes one int8 tile whose samples this lane already holds in v
 // (tile_load), stores the output, and returns the statistics record this
 // lane must write (see write_stats).
@@ -370,57 +430,12 @@ __device__ __forceinline__ TileStats i8_tile(const StreamView& d, int64_t first,
     if constexpr (Smem::kWide) {
         constexpr int WPW = Smem::kWPW;
         const int wl = wave / WPW;
-        uint32_t* h = sm.hist + wave * kWaveHistWords;
-        if constexpr (WPW > 1) __syncthreads();  // the previous tile is done with tot and prm
-        wide_hist_zero(h);
-        wave_sync();
-        uint32_t* hl = h + (lane & 3) * kRepStride;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            wide_hist_add(hl, v[q]);
-            sched_fence();
-        }
-        wave_sync();
-        uint32_t c[4];
-        wide_hist_totals(h, c);
-        // The cumulative counts overwrite replica 0 of the selecting wave,
-        // whose reads were all issued above.
-        uint32_t* pc = h;
-        int mb = 0, D = 0;
+        uint32_t* pc;
+        int mb, D;
         WinParams p;
         rfi_window_stats ws;
-        if constexpr (WPW == 2) {
-            // W 8192: both waves publish their totals; after one barrier each
-            // wave adds its window's two and selects by itself (the same
-            // values in both, no second exchange).
-            *reinterpret_cast<uint4*>(sm.tot + wave * 256 + lane * 4) = make_uint4(c[0], c[1], c[2], c[3]);
-            __syncthreads();
-            const uint4 t0 = *reinterpret_cast<const uint4*>(sm.tot + (wl * 2) * 256 + lane * 4);
-            const uint4 t1 = *reinterpret_cast<const uint4*>(sm.tot + (wl * 2 + 1) * 256 + lane * 4);
-            c[0] = t0.x + t1.x;
-            c[1] = t0.y + t1.y;
-            c[2] = t0.z + t1.z;
-            c[3] = t0.w + t1.w;
-        } else if constexpr (WPW == 4) {
-            // W 16384: the four waves' totals are added in LDS and one wave
-            // selects (selecting in all four measured slower).
-            if (threadIdx.x < 64) reinterpret_cast<uint4*>(sm.tot)[threadIdx.x] = make_uint4(0, 0, 0, 0);
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < 4; ++j) atomicAdd(&sm.tot[lane * 4 + j], c[j]);
-            __syncthreads();
-            if (wave == 0) {
-                const uint4 t = *reinterpret_cast<const uint4*>(sm.tot + lane * 4);
-                c[0] = t.x;
-                c[1] = t.y;
-                c[2] = t.z;
-                c[3] = t.w;
-            }
-        }
-        if (WPW < 4 || wave == 0) {
-            wide_select(c, pc, need, mb, D);
-            wide_params(pc, mb, D, d.k, W, p, ws);
-        }
+        i8_wide_tile_select(sm, v, mb, D, pc);
+        if (WPW < 4 || wave == 0) wide_params(pc, mb, D, d.k, W, p, ws);
         if (wave % WPW == 0) {
             if (lane == 0) {
                 sm.prm[wl] = p;
@@ -1006,6 +1021,73 @@ __global__ __launch_bounds__(kBlock, MODES == 7 ? 4 : 0) void k_i8_fused(LaunchA
 // replacement (its own mode) is applied to a copy of the tile and stored.
 // Output o is the same as a single call with that output's k and mode.
 // ---------------------------------------------------------------------------
+// Wide windows (W >= 4096): every wave holds one window or a part of one, and
+// an output's parameters and its flag count are read off the window's
+// cumulative counts, so the outputs follow each other without a barrier, a
+// count of flagged samples or a table of parameters.  60 x 2^22 samples, W
+// 4096, three outputs: 198 us with those, 182 without (the bytes moved take
+// 164 at the copy rate).
+template <int CLS>
+__global__ __launch_bounds__(kBlock, 8) void k_i8_multi_wide(MultiArgs ma)
+{
+    constexpr int W = 512 << CLS;
+    using Smem = I8TileSmem<W, false>;
+    constexpr int WPW = Smem::kWPW;
+    __shared__ Smem sm;
+    const LaunchArgs& a = ma.a;
+    const Item item = a.items[blockIdx.x];
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint32_t v[16];
+    tile_load(resolve(a.streams[item.stream], a), item.first, v);
+    int mb, D;
+    uint32_t* pc;
+    i8_wide_tile_select(sm, v, mb, D, pc);
+    if constexpr (WPW == 4) {
+        if (threadIdx.x == 0) {
+            sm.prm[0].m = mb;
+            sm.mad[0] = D;
+        }
+        __syncthreads();
+        mb = sm.prm[0].m;
+        D = sm.mad[0];
+        pc = sm.hist;
+    }
+    const int64_t off = item.first + wave * 4096 + lane * 16;
+#pragma unroll 1
+    for (int o = 0; o < ma.n_out; ++o) {
+        const StreamDesc& sd = ma.desc[o][item.stream];
+        WinParams p;
+        rfi_window_stats s;
+        wide_params(pc, mb, D, sd.k, W, p, s);
+        if (lane == 0 && wave % WPW == 0 && ma.stats_base[o] != 0) {
+            TileStats ts;
+            ts.s = s;
+            ts.dst = reinterpret_cast<rfi_window_stats*>(ma.stats_base[o] + sd.stats_off) + item.first / W + wave / WPW;
+            write_stats(ts);
+        }
+        uint8_t* yt = reinterpret_cast<uint8_t*>(ma.y_base[o] + sd.y_off) + off;
+        const uint32_t lo = rep_i16(p.lo * 256), hi = rep_i16(p.hi * 256);
+        const uint32_t lo_u = rep_i16((p.lo + 128) * 256), hi_u = rep_i16((p.hi + 128) * 256);
+        const bool clip = sd.mode == RFI_MODE_CLIP;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t r[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                // opaque: the parts of the replacement that no output
+                // changes are not kept in registers over the loop
+                uint32_t x = v[4 * i + j];
+                pin_vgpr(x);
+                r[j] = clip ? clamp_i8x4(x, lo, hi) : byte_perm(0u, x, flag_sel_i8x4(x, lo_u, hi_u));
+            }
+            gstore16_nt(yt + i * 1024, make_uint4(r[0], r[1], r[2], r[3]));
+        }
+    }
+}
+
+// Narrow windows: the flags are counted, since the histograms of one round of
+// windows make room for the next.
 template <int W>
 struct I8MultiSmem {
     I8TileSmem<W, false> t;
@@ -1070,7 +1152,8 @@ __global__ __launch_bounds__(kBlock) void k_i8_multi(MultiArgs ma)
                 uint32_t r[4], nf = 0;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const uint32_t xw = v[4 * i + j];
+                    uint32_t xw = v[4 * i + j];
+                    pin_vgpr(xw);  // as in k_i8_multi_wide
                     const uint32_t c = clamp_i8x4(xw, lo, hi);
                     nf += __popc(nonzero_byte_mask(c ^ xw)) >> 3;
                     r[j] = clip ? c : byte_perm(0u, xw, flag_sel_i8x4(xw, lo_u, hi_u));
@@ -1601,9 +1684,9 @@ hipError_t launch_i8_multi(int cls, const MultiArgs& ma, int grid, hipStream_t s
         case 0: k = k_i8_multi<0>; break;
         case 1: k = k_i8_multi<1>; break;
         case 2: k = k_i8_multi<2>; break;
-        case 3: k = k_i8_multi<3>; break;
-        case 4: k = k_i8_multi<4>; break;
-        case 5: k = k_i8_multi<5>; break;
+        case 3: k = k_i8_multi_wide<3>; break;
+        case 4: k = k_i8_multi_wide<4>; break;
+        case 5: k = k_i8_multi_wide<5>; break;
         default: return hipErrorInvalidValue;
     }
     MultiArgs args = ma;

@@ -53,6 +53,7 @@ struct MultiPlan {
     Item* d_items = nullptr;
     std::vector<int64_t> cls_begin, cls_count;  // tile items per class, then generic
     int64_t gen_begin = 0, gen_count = 0;
+    int gen_threads = 0;  // i8_window_threads of the longest generic window
     int device = 0;  // the plan's buffers and kernels live here
 };
 
@@ -78,7 +79,7 @@ int multi_build(int32_t n_out, int32_t n, const int64_t* L, const int32_t* W, co
     p->seed = seed;
     std::vector<std::vector<Item>> groups(kI8Classes + 1);
     std::vector<std::vector<StreamDesc>> desc(n_out, std::vector<StreamDesc>(n));
-    int64_t soff = 0, woff = 0;
+    int64_t soff = 0, woff = 0, gen_longest = 0;
     for (int s = 0; s < n; ++s) {
         for (int o = 0; o < n_out; ++o) {
             StreamDesc& d = desc[o][s];
@@ -102,6 +103,8 @@ int multi_build(int32_t n_out, int32_t n, const int64_t* L, const int32_t* W, co
             first_generic = nt * (kTileBytes / W[s]);
         }
         for (int64_t w = first_generic; w < nw; ++w) groups[0].push_back(Item{s, kItemGeneric, w});
+        if (first_generic < nw)
+            gen_longest = std::max(gen_longest, std::min<int64_t>(W[s], L[s] - first_generic * W[s]));
         soff += align64(L[s]);
         woff += nw;
     }
@@ -115,6 +118,7 @@ int multi_build(int32_t n_out, int32_t n, const int64_t* L, const int32_t* W, co
     }
     p->gen_begin = (int64_t)items.size();
     p->gen_count = (int64_t)groups[0].size();
+    p->gen_threads = i8_window_threads(gen_longest);
     items.insert(items.end(), groups[0].begin(), groups[0].end());
     hipError_t e = hipSuccess;
     for (int o = 0; o < n_out && e == hipSuccess; ++o) {
@@ -172,7 +176,7 @@ int multi_execute(MultiPlan* p, const void* x, int8_t* const* y, rfi_window_stat
         a.no_stats = ma.stats_base[o] == 0 ? 1 : 0;
         if (a.n_items > (1 << 30)) return RFI_ERR_INVALID;
         // outputs with noise streams are single-output calls of their own
-        hipError_t e = launch_i8_generic(a, 3, (int)a.n_items, s);
+        hipError_t e = launch_i8_generic(a, 3, (int)a.n_items, s, p->gen_threads);
         if (e != hipSuccess) return hip_fail(e);
     }
     return RFI_OK;
