@@ -116,10 +116,54 @@ __device__ __forceinline__ void select_i8(uint32_t* hw, uint32_t need, int& mb, 
     });
 }
 
-// Window parameters and statistics from the cumulative histogram hw.
-template <int G>
-__device__ __forceinline__ void params_i8(const uint32_t* hw, int mb, int D, float k, int n,
-                                          WinParams& p, rfi_window_stats& s)
+// The same for two windows that share a histogram, one in each 16-bit half of
+// a bin: GA lanes turn it into cumulative
+// counts, both windows at once; then the first half of the lanes finds the
+// median bin and the MAD of the window in the low halves, the second half
+// those of the other.  C(v): this lane's window's count at bin v afterwards.
+template <int GA>
+__device__ __forceinline__ uint32_t pair_count(const uint32_t* hw, int shift, int v)
+{
+    return (hw[nphys<GA>(v)] >> shift) & 0xFFFFu;
+}
+
+template <int GA>
+__device__ __forceinline__ void select_i8_pair(uint32_t* hw, int shift, uint32_t need, int& mb, int& D)
+{
+    constexpr int BPL = 256 / GA;
+    const int sl = lane_id() & (GA - 1);
+    uint32_t* my = hw + sl * BPL;
+    const int key = GA == 16 ? (((sl >> 2) & 3) << 2) : 0;  // chunk permutation of nphys
+    uint32_t c[BPL];
+#pragma unroll
+    for (int j = 0; j < BPL; j += 4) {
+        const uint4 t = *reinterpret_cast<const uint4*>(my + (j ^ key));
+        c[j] = t.x;
+        c[j + 1] = t.y;
+        c[j + 2] = t.z;
+        c[j + 3] = t.w;
+    }
+#pragma unroll
+    for (int j = 1; j < BPL; ++j) c[j] += c[j - 1];
+    const uint32_t excl = group_incl_scan<GA>(c[BPL - 1]) - c[BPL - 1];
+#pragma unroll
+    for (int j = 0; j < BPL; ++j) c[j] += excl;
+#pragma unroll
+    for (int j = 0; j < BPL; j += 4)
+        *reinterpret_cast<uint4*>(my + (j ^ key)) = make_uint4(c[j], c[j + 1], c[j + 2], c[j + 3]);
+    wave_sync();
+    mb = group_search<GA / 2, 256>(0, need, [&](int v) { return pair_count<GA>(hw, shift, v); });
+    const int m0 = mb;
+    D = group_search<GA / 2, 256>(0, need, [&](int d) {
+        const int dn = m0 - d - 1;
+        return pair_count<GA>(hw, shift, min(m0 + d, 255)) - (dn >= 0 ? pair_count<GA>(hw, shift, max(dn, 0)) : 0u);
+    });
+}
+
+// Window parameters and statistics from the cumulative counts C(v).
+template <class Count>
+__device__ __forceinline__ void params_i8(const Count& C, int mb, int D, float k, int n, WinParams& p,
+                                          rfi_window_stats& s)
 {
     float sig;
     const float t = threshold_of(D, k, sig);
@@ -127,7 +171,7 @@ __device__ __forceinline__ void params_i8(const uint32_t* hw, int mb, int D, flo
     const int m = mb - 128;
     const int lo = max(m - T, -128), hi = min(m + T, 127);
     const int lob = lo + 128, hib = hi + 128;
-    const uint32_t inside = hw[nphys<G>(hib)] - (lob > 0 ? hw[nphys<G>(max(lob - 1, 0))] : 0u);
+    const uint32_t inside = C(hib) - (lob > 0 ? C(max(lob - 1, 0)) : 0u);
     p.lo = lo;
     p.hi = hi;
     p.m = m;
@@ -251,9 +295,17 @@ struct I8TileSmem {
     static constexpr int kWPW = kWide ? W / 4096 : 1;  // waves per window
     // wide: per-wave replicated histograms; W = 4096 keeps its cumulative
     // counts in replica 0 of its wave, larger W in pc.
-    // W = 512 runs its eight windows per wave in two rounds of four.
-    static constexpr int kRounds = W == 512 ? 2 : 1;
-    static constexpr int kHistWords = kWide ? 4 * kWaveHistWords : (kWin / kRounds) * kNarrowStride;
+    // W = 512: two windows share a histogram, one in each half of its bins
+    // (counts of at most 512), so that clearing, adding up and scanning it
+    // serve both.  Against one histogram per window in two rounds, 60 x 2^22
+    // samples, zero / clip / noise: 129 / 127 / 142 -> 105 / 104 / 117 us
+    // (4.86 TB/s, LDS and VALU); sharing at W 1024 puts more lanes on one
+    // address and gains nothing (101 / 100 / 115 -> 103 / 101 / 116).
+    static constexpr bool kPair = W == 512;
+    static constexpr int kHists = kPair ? kWin / 2 : kWin;
+    static constexpr int kHistWords = kWide ? 4 * kWaveHistWords
+                                      : kHists * kNarrowStride > kNoiseAliasWords ? kHists * kNarrowStride
+                                                                                   : kNoiseAliasWords;
     static_assert(kHistWords >= kNoiseAliasWords, "noise scratch aliases the histograms");
     __align__(16) uint32_t hist[kHistWords];
     __align__(16) uint32_t tot[kWPW > 1 ? 4 * 256 : 0];  // each wave's bin totals
@@ -458,81 +510,70 @@ __device__ __forceinline__ TileStats i8_tile(const StreamView& d, int64_t first,
         if constexpr (MODE != kModeStats) i8_replace<W, NS, MODE>(d, first, seed, sm, v, [&](int) { return p; });
     } else {
         // Several windows per wave: one 256-bin histogram of x + 128 per
-        // window.  W = 512 takes its eight windows per wave in two rounds
-        // (loads 0-1, then 2-3) to halve the histogram space.
-        constexpr int NWW = 4096 / W;           // windows per wave
-        constexpr int ROUNDS = Smem::kRounds;
-        constexpr int NWR = NWW / ROUNDS;       // windows per round
-        constexpr int LPR = 4 / ROUNDS;         // loads per round
-        constexpr int G = 64 / NWR;             // lanes per window in the scan
-        uint32_t* hwave = sm.hist + wave * NWR * kNarrowStride;
+        // window, or per two windows (Smem::kPair) in the halves of its bins.
+        constexpr int NWW = 4096 / W;            // windows per wave
+        constexpr bool PAIR = Smem::kPair;
+        constexpr int NH = PAIR ? NWW / 2 : NWW;  // histograms per wave
+        constexpr int GA = 64 / NH;               // lanes per histogram in the scan
+        constexpr int G = 64 / NWW;               // lanes per window in the search
+        uint32_t* hwave = sm.hist + wave * NH * kNarrowStride;
         // A load's 1 KiB lies in at most two windows, so counting load i in
         // step i would send 32 or 64 lanes of a wave to one histogram and
-        // serialise their same-bin atomics.  Lane groups count the loads of
-        // a round in rotated order instead (lanes 8g .. 8g+7 mod 32 start at
-        // load g for four loads per round, lanes 16g .. 16g+15 mod 32 at
-        // load g for two), so each step spreads the wave over more windows.
-        // The rotation uses masked selects with opaque masks, so it stays
-        // bit-field inserts instead of becoming a per-lane indexed read.
-        const int g = LPR == 4 ? (lane >> 3) & 3 : (lane >> 4) & 1;
+        // serialise their same-bin atomics.  Lane groups count the loads in
+        // rotated order instead (lanes 8g .. 8g+7 mod 32 start at load g), so
+        // each step spreads the wave over more histograms.  The rotation uses
+        // masked selects with opaque masks, so it stays bit-field inserts
+        // instead of becoming a per-lane indexed read.
+        const int g = (lane >> 3) & 3;
         uint32_t m1 = (g & 1) ? ~0u : 0u, m2 = (g & 2) ? ~0u : 0u;
         asm volatile("" : "+v"(m1), "+v"(m2));
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
-            if (r > 0) wave_sync();  // the previous round is done with the histograms
+        for (int j = 0; j < NH; ++j)
+            reinterpret_cast<uint4*>(hwave + j * kNarrowStride)[lane] = make_uint4(0, 0, 0, 0);
+        wave_sync();
+        uint32_t q[16], q2[16];
 #pragma unroll
-            for (int j = 0; j < NWR; ++j)
-                reinterpret_cast<uint4*>(hwave + j * kNarrowStride)[lane] = make_uint4(0, 0, 0, 0);
-            wave_sync();
-            uint32_t q[4 * LPR];
+        for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int t = 0; t < LPR; ++t)
+            for (int j = 0; j < 4; ++j) q2[4 * t + j] = bit_select(m1, v[4 * ((t + 1) & 3) + j], v[4 * t + j]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int l0 = r * LPR + t, l1 = r * LPR + ((t + 1) % LPR);
-                    q[4 * t + j] = bit_select(m1, v[4 * l1 + j], v[4 * l0 + j]);
-                }
-            if constexpr (LPR == 4) {
-                uint32_t q2[16];
+        for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
+            for (int j = 0; j < 4; ++j) q[4 * t + j] = bit_select(m2, q2[4 * ((t + 2) & 3) + j], q2[4 * t + j]);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) q2[4 * t + j] = bit_select(m2, q[4 * ((t + 2) & 3) + j], q[4 * t + j]);
+        for (int t = 0; t < 4; ++t) {
+            const int li = (t + g) & 3;
+            const int win = (li * 1024 + lane * 16) / W;  // of the wave
+            uint32_t* hh = hwave + (PAIR ? win >> 1 : win) * kNarrowStride;
+            const uint32_t one = PAIR ? ((win & 1) ? 0x10000u : 1u) : 1u;
 #pragma unroll
-                for (int k = 0; k < 16; ++k) q[k] = q2[k];
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t u = nphys4<GA>(q[4 * t + j] ^ 0x80808080u);
+                atomicAdd(&hh[u & 0xFFu], one);
+                atomicAdd(&hh[(u >> 8) & 0xFFu], one);
+                atomicAdd(&hh[(u >> 16) & 0xFFu], one);
+                atomicAdd(&hh[u >> 24], one);
+                sched_fence();
             }
-#pragma unroll
-            for (int t = 0; t < LPR; ++t) {
-                const int li = r * LPR + ((t + g) % LPR);
-                uint32_t* hh = hwave + (((li * 1024 + lane * 16) / W) - r * NWR) * kNarrowStride;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t u = nphys4<G>(q[4 * t + j] ^ 0x80808080u);
-                    atomicAdd(&hh[u & 0xFFu], 1u);
-                    atomicAdd(&hh[(u >> 8) & 0xFFu], 1u);
-                    atomicAdd(&hh[(u >> 16) & 0xFFu], 1u);
-                    atomicAdd(&hh[u >> 24], 1u);
-                    sched_fence();
-                }
+        }
+        wave_sync();
+        const int wl = wave * NWW + lane / G;
+        uint32_t* hw = hwave + (lane / GA) * kNarrowStride;
+        const int shift = PAIR ? (lane & G ? 16 : 0) : 0;
+        int mb, D;
+        if constexpr (PAIR) select_i8_pair<GA>(hw, shift, need, mb, D);
+        else select_i8<GA>(hw, need, mb, D);
+        WinParams p;
+        rfi_window_stats ws;
+        params_i8([&](int v) { return PAIR ? pair_count<GA>(hw, shift, v) : hw[nphys<GA>(v)]; }, mb, D, d.k, W, p, ws);
+        if ((lane & (G - 1)) == 0) {
+            sm.prm[wl] = p;
+            if constexpr (MODE == kModeStats) {
+                sm.mad[wl] = D;
+                if (d.mads) gstore(d.mads + first / W + wl, (uint8_t)D);
             }
-            wave_sync();
-            const int wl = wave * NWW + r * NWR + lane / G;
-            uint32_t* hw = hwave + (lane / G) * kNarrowStride;
-            int mb, D;
-            select_i8<G>(hw, need, mb, D);
-            WinParams p;
-            rfi_window_stats ws;
-            params_i8<G>(hw, mb, D, d.k, W, p, ws);
-            // Lane r of the window's group keeps the statistics of round r.
-            if ((lane & (G - 1)) == r) {
-                sm.prm[wl] = p;
-                if constexpr (MODE == kModeStats) {
-                    sm.mad[wl] = D;
-                    if (d.mads) gstore(d.mads + first / W + wl, (uint8_t)D);
-                }
-                ts.s = ws;
-                ts.dst = d.stats ? d.stats + first / W + wl : nullptr;
-            }
+            ts.s = ws;
+            ts.dst = d.stats ? d.stats + first / W + wl : nullptr;
         }
         wave_sync();
         write_stats(ts);
@@ -828,7 +869,7 @@ __device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, Generi
         select_i8<64>(sm.hist, (uint32_t)((n - 1) / 2 + 1), mb, D);
         WinParams p;
         rfi_window_stats s;
-        params_i8<64>(sm.hist, mb, D, d.k, n, p, s);
+        params_i8([&](int v) { return sm.hist[v]; }, mb, D, d.k, n, p, s);
         if (tid == 0) {
             sm.prm[0] = p;
             if (d.stats) d.stats[w] = s;
