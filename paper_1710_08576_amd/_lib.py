@@ -124,12 +124,44 @@ def _check(rc: int, where: str):
 
 
 def _arr(values, dtype, n):
+    if type(values) is np.ndarray and values.dtype == dtype and values.shape == (n,) and values.flags.c_contiguous:
+        return values  # already what the library reads
     a = np.ascontiguousarray(np.broadcast_to(np.asarray(values, dtype=dtype), (n,)))
     return a
 
 
 def _ptr(a: np.ndarray):
     return a.ctypes.data_as(ctypes.c_void_p)
+
+
+def _addr(a: np.ndarray) -> int:
+    """Address of an array that the caller keeps alive over the call."""
+    return a.__array_interface__["data"][0]
+
+
+def _dptr(t):
+    return None if t is None else t.data_ptr()
+
+
+def _raw_stream(stream) -> int:
+    if stream is None:
+        import torch
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream
+
+
+def _n_windows(L, W) -> int:
+    """Windows of all streams (what layout() returns third), without the
+    offset tables."""
+    nw = load().rfi_layout(len(L), _addr(L), _addr(W), None, None, None)
+    if nw < 0:
+        _check(int(nw), "rfi_layout")
+    return int(nw)
+
+
+def _stats_out(nw, like):
+    import torch
+    return torch.empty((max(nw, 1), 4), dtype=torch.int32, device=like.device)
 
 
 def _tptr(t):
@@ -209,20 +241,19 @@ def mad_filter(x, lengths, windows, k, mode, seed: int = 0, y=None, stats=True, 
     n = len(lengths)
     L = np.ascontiguousarray(lengths, dtype=np.int64)
     W, K, M = _arr(windows, np.int32, n), _arr(k, np.float32, n), _arr(mode, np.int32, n)
-    _, _, nw, _ = layout(L, W)
+    nw = _n_windows(L, W)
     if y is None:
         y = torch.empty_like(x)
-    st = torch.empty((max(nw, 1), 4), dtype=torch.int32, device=x.device) if stats else None
+    st = _stats_out(nw, x) if stats else None
     if x.dtype == torch.int8:
         f = load().rfi_mad_filter
     elif x.dtype == torch.int16:
         f = load().rfi_mad_filter_i16
     else:
         raise TypeError("x must be int8 or int16")
-    rc = f(_tptr(x), _tptr(y), n, _ptr(L), _ptr(W), _ptr(K), _ptr(M), seed, _tptr(st),
-           _stream_handle(stream))
+    rc = f(x.data_ptr(), y.data_ptr(), n, _addr(L), _addr(W), _addr(K), _addr(M), seed, _dptr(st), _raw_stream(stream))
     _check(rc, "rfi_mad_filter")
-    return y, (st[:nw] if st is not None else None)
+    return y, (st if st is None or nw > 0 else st[:0])
 
 
 def mad_filter_noalloc(x, lengths, windows, k, mode, seed: int = 0, y=None, stats=None, stream=None):
@@ -238,8 +269,8 @@ def mad_filter_noalloc(x, lengths, windows, k, mode, seed: int = 0, y=None, stat
         raise TypeError("x must be int8")
     if y is None:
         y = torch.empty_like(x)
-    rc = load().rfi_mad_filter_noalloc(_tptr(x), _tptr(y), n, _ptr(L), _ptr(W), _ptr(K), _ptr(M), seed,
-                                       _tptr(stats), _stream_handle(stream))
+    rc = load().rfi_mad_filter_noalloc(x.data_ptr(), y.data_ptr(), n, _addr(L), _addr(W), _addr(K), _addr(M), seed,
+                                       _dptr(stats), _raw_stream(stream))
     _check(rc, "rfi_mad_filter_noalloc")
     return y, stats
 
@@ -253,21 +284,18 @@ def mad_filter_multi(x, lengths, windows, ks, modes, seed: int = 0, ys=None, sta
     W = _arr(windows, np.int32, n)
     K = np.ascontiguousarray(np.concatenate([_arr(k, np.float32, n) for k in ks]))
     M = np.ascontiguousarray(np.concatenate([_arr(m, np.int32, n) for m in modes]))
-    _, _, nw, _ = layout(L, W)
+    nw = _n_windows(L, W)
     if x.dtype != torch.int8:
         raise TypeError("x must be int8")
     if ys is None:
         ys = [torch.empty_like(x) for _ in range(n_out)]
-    sts = [torch.empty((max(nw, 1), 4), dtype=torch.int32, device=x.device) for _ in range(n_out)] \
-        if stats else None
+    sts = [_stats_out(nw, x) for _ in range(n_out)] if stats else None
     yp = (ctypes.c_void_p * n_out)(*[y.data_ptr() for y in ys])
     sp = (ctypes.c_void_p * n_out)(*[t.data_ptr() for t in sts]) if sts is not None else None
-    rc = load().rfi_mad_filter_multi(_tptr(x), n_out, ctypes.cast(yp, ctypes.c_void_p), n, _ptr(L), _ptr(W),
-                                     _ptr(K), _ptr(M), seed,
-                                     ctypes.cast(sp, ctypes.c_void_p) if sp is not None else None,
-                                     _stream_handle(stream))
+    rc = load().rfi_mad_filter_multi(x.data_ptr(), n_out, yp, n, _addr(L), _addr(W), _addr(K), _addr(M), seed, sp,
+                                     _raw_stream(stream))
     _check(rc, "rfi_mad_filter_multi")
-    return ys, ([t[:nw] for t in sts] if sts is not None else None)
+    return ys, (sts if sts is None or nw > 0 else [t[:0] for t in sts])
 
 
 def mom_filter(x, lengths, windows, k, mode, mom_k: int, seed: int = 0, y=None, stats=True,
@@ -278,16 +306,16 @@ def mom_filter(x, lengths, windows, k, mode, mom_k: int, seed: int = 0, y=None, 
     n = len(lengths)
     L = np.ascontiguousarray(lengths, dtype=np.int64)
     W, K, M = _arr(windows, np.int32, n), _arr(k, np.float32, n), _arr(mode, np.int32, n)
-    _, _, nw, _ = layout(L, W)
+    nw = _n_windows(L, W)
     if x.dtype != torch.int8:
         raise TypeError("x must be int8")
     if y is None:
         y = torch.empty_like(x)
-    st = torch.empty((max(nw, 1), 4), dtype=torch.int32, device=x.device) if stats else None
-    rc = load().rfi_mom_filter(_tptr(x), _tptr(y), n, _ptr(L), _ptr(W), _ptr(K), _ptr(M), int(mom_k),
-                               seed, _tptr(st), _stream_handle(stream))
+    st = _stats_out(nw, x) if stats else None
+    rc = load().rfi_mom_filter(x.data_ptr(), y.data_ptr(), n, _addr(L), _addr(W), _addr(K), _addr(M), int(mom_k),
+                               seed, _dptr(st), _raw_stream(stream))
     _check(rc, "rfi_mom_filter")
-    return y, (st[:nw] if st is not None else None)
+    return y, (st if st is None or nw > 0 else st[:0])
 
 
 def mom_filter_carry(x, lengths, windows, k, mode, mom_k: int, abs_base, history, history_len, seed: int = 0,
@@ -299,17 +327,17 @@ def mom_filter_carry(x, lengths, windows, k, mode, mom_k: int, abs_base, history
     n = len(lengths)
     L = np.ascontiguousarray(lengths, dtype=np.int64)
     W, K, M = _arr(windows, np.int32, n), _arr(k, np.float32, n), _arr(mode, np.int32, n)
-    _, _, nw, _ = layout(L, W)
+    nw = _n_windows(L, W)
     if x.dtype != torch.int8:
         raise TypeError("x must be int8")
     if y is None:
         y = torch.empty_like(x)
-    st = torch.empty((max(nw, 1), 4), dtype=torch.int32, device=x.device) if stats else None
-    rc = load().rfi_mom_filter_carry(_tptr(x), _tptr(y), n, _ptr(L), _ptr(W), _ptr(K), _ptr(M), int(mom_k), seed,
-                                     _tptr(abs_base), _tptr(history), _tptr(history_len), _tptr(st),
-                                     _stream_handle(stream))
+    st = _stats_out(nw, x) if stats else None
+    rc = load().rfi_mom_filter_carry(x.data_ptr(), y.data_ptr(), n, _addr(L), _addr(W), _addr(K), _addr(M), int(mom_k),
+                                     seed, _dptr(abs_base), _dptr(history), _dptr(history_len), _dptr(st),
+                                     _raw_stream(stream))
     _check(rc, "rfi_mom_filter_carry")
-    return y, (st[:nw] if st is not None else None)
+    return y, (st if st is None or nw > 0 else st[:0])
 
 
 class Plan:
@@ -346,8 +374,8 @@ class Plan:
         _check(load().rfi_plan_set_graph(self.h, 1 if on else 0), "rfi_plan_set_graph")
 
     def execute(self, x, y, stats=None, stream=None):
-        _check(load().rfi_plan_execute(self.h, _tptr(x), _tptr(y), _tptr(stats),
-                                       _stream_handle(stream)), "rfi_plan_execute")
+        _check(load().rfi_plan_execute(self.h, _dptr(x), _dptr(y), _dptr(stats), _raw_stream(stream)),
+               "rfi_plan_execute")
 
     def info(self):
         nl = np.zeros(1, np.int32)
@@ -523,7 +551,7 @@ def n_blocks(lengths, block: int) -> int:
     a block below 1 (the library rejects it)."""
     if block < 1:
         return 0
-    return int(sum((int(L) + block - 1) // block for L in lengths))
+    return int(((np.asarray(lengths, dtype=np.int64) + (block - 1)) // block).sum())
 
 
 def block_power(x, lengths, block: int, out=None, stream=None):
@@ -537,8 +565,8 @@ def block_power(x, lengths, block: int, out=None, stream=None):
     nb = n_blocks(L, block)
     if out is None:
         out = torch.empty(max(nb, 1), dtype=torch.int64, device=x.device)
-    rc = load().rfi_block_power(_tptr(x), x.element_size(), len(L), _ptr(L), int(block), _tptr(out),
-                                _stream_handle(stream))
+    rc = load().rfi_block_power(x.data_ptr(), x.element_size(), len(L), _addr(L), int(block), out.data_ptr(),
+                                _raw_stream(stream))
     _check(rc, "rfi_block_power")
     return out[:nb]
 
@@ -552,7 +580,7 @@ def improvement(power_u, power_f, lengths, block: int, seg_blocks: int, out=None
     L = np.ascontiguousarray(lengths, dtype=np.int64)
     if out is None:
         out = torch.empty((max(len(L), 1), 3), dtype=torch.float64, device=power_u.device)
-    rc = load().rfi_improvement(_tptr(power_u), _tptr(power_f), len(L), _ptr(L), int(block), int(seg_blocks),
-                                _tptr(out), _stream_handle(stream))
+    rc = load().rfi_improvement(power_u.data_ptr(), power_f.data_ptr(), len(L), _addr(L), int(block), int(seg_blocks),
+                                out.data_ptr(), _raw_stream(stream))
     _check(rc, "rfi_improvement")
     return out[:len(L)]
