@@ -334,13 +334,17 @@ __device__ __forceinline__ void write_stats(const TileStats& t)
 
 // This lane's 64 bytes of a 16 KiB tile: four 16-byte loads at a 1 KiB
 // stride, so each load instruction of the wave covers 1 KiB contiguously.
+// AGAIN: the samples are read a second time soon (the statistics pass of the
+// median of MAD: with non-temporal loads its call took 142 against 134 us
+// for 60 x 2^22 samples, 296 against 291 for 60 x 2^23).
+template <bool AGAIN = false>
 __device__ __forceinline__ void tile_load(const StreamView& d, int64_t first_byte, uint32_t (&v)[16])
 {
     const uint8_t* xt = static_cast<const uint8_t*>(d.x) + first_byte + (threadIdx.x >> 6) * 4096 +
                         lane_id() * 16;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const uint4 t = gload16_nt(xt + i * 1024);
+        const uint4 t = AGAIN ? gload16(xt + i * 1024) : gload16_nt(xt + i * 1024);
         v[4 * i] = t.x;
         v[4 * i + 1] = t.y;
         v[4 * i + 2] = t.z;
@@ -464,6 +468,112 @@ __device__ __forceinline__ void i8_wide_tile_select(I8TileSmem<W, NS>& sm, const
     if (WPW < 4 || wave == 0) wide_select(c, pc, need, mb, D);
 }
 
+// Six consecutive counts of a wave's 2048 samples u (8 dwords per lane,
+// biased bytes): e[j] = 2 #{u > t + j}, 0 <= t, t + 6 <= 255.
+//
+// |u - t| - |u - t - 1| is 1 for u > t and -1 otherwise, so the difference of
+// two neighbouring sums of distances, one v_sad_u8 per dword each, counts
+// the samples above t.
+__device__ __forceinline__ void sad_counts(const uint32_t (&u)[8], int t, uint32_t (&e)[6])
+{
+    uint32_t S[7];
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        S[j] = 32u * (uint32_t)(6 - j);  // each difference gains 32: 2 #{u > t} of 32 samples, never negative
+        const uint32_t t4 = (uint32_t)__builtin_amdgcn_readfirstlane((int)rep_i8(t + j));
+#pragma unroll
+        for (int q = 0; q < 8; ++q) S[j] = __builtin_amdgcn_sad_u8(u[q], t4, S[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 6; ++j) e[j] = S[j] - S[j + 1];
+}
+
+// Sums over the wave of six per-lane values of at most 64 each, two to a
+// register (sums of at most 4096 fit 16 bits).
+__device__ __forceinline__ void wave_sums6(const uint32_t (&e)[6], int (&sum)[6])
+{
+#pragma unroll
+    for (int j = 0; j < 6; j += 2) {
+        const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)group_incl_scan<64>(e[j] | e[j + 1] << 16), 63);
+        sum[j] = (int)(t & 0xFFFFu);
+        sum[j + 1] = (int)(t >> 16);
+    }
+}
+
+// Median bin and MAD of a 4096-sample window from half the atomics, for the
+// statistics-only pass, which nothing but the histogram's LDS atomics bounds
+// (its samples are read once and not written).  Half of the window's samples
+// are counted into the histogram; its median and MAD are within a value or
+// two of the window's.  The other half is counted at the six values around
+// each place that decides the result, the median and m + D and m - D, by
+// sums of distances, and added to the histogram's cumulative counts there.
+// False if the result is not among those values; the counts are then taken
+// from all samples.  60 x 2^21 samples: 44 -> 32 us (3.9
+// TB/s read), 60 x 2^20 23.6 -> 18.
+template <bool NS>
+__device__ __forceinline__ bool i8_stats_select_4096(I8TileSmem<4096, NS>& sm, const uint32_t (&v)[16], int& mb_out,
+                                                     int& D_out)
+{
+    constexpr int need = 2048;  // rank floor((4096 - 1) / 2), 1-based
+    const int lane = lane_id();
+    uint32_t* h = sm.hist + (threadIdx.x >> 6) * kWaveHistWords;
+    wide_hist_zero(h);
+    wave_sync();
+    uint32_t* hl = h + (lane & 3) * kRepStride;
+    // the first two dwords of every 16 bytes: both halves see the same signal
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        wide_hist_add(hl, v[4 * (q >> 1) + (q & 1)]);
+        sched_fence();
+    }
+    wave_sync();
+    uint32_t c[4];
+    wide_hist_totals(h, c);
+    int m, D;
+    wide_select(c, h, 1024, m, D);
+    m = __builtin_amdgcn_readfirstlane(m);
+    D = __builtin_amdgcn_readfirstlane(D);
+    const uint32_t* C = h + 4;  // cumulative counts of the histogram's half
+    uint32_t u[8], e[6];
+    int s[6];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) u[q] = v[4 * (q >> 1) + 2 + (q & 1)] ^ 0x80808080u;
+    // The median: the first value whose count reaches the rank, among the
+    // five above t.
+    const int t = m - 3;
+    if (t < 0 || t + 6 > 255) return false;
+    sad_counts(u, t, e);
+    wave_sums6(e, s);
+    int cv = (int)C[min(t + lane, 255)];
+    int below = 0;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        s[j] = __builtin_amdgcn_readlane(cv, j) + 2048 - (s[j] >> 1);
+        below += s[j] < need ? 1 : 0;
+    }
+    if (below == 0 || below == 6) return false;
+    m = t + below;
+    // The MAD: the first d with C(m + d) - C(m - d - 1) >= need, among d0 ..
+    // d0 + 5.
+    const int d0 = max(D - 3, 0);
+    const int hi = m + d0, lo = m - d0 - 6;  // lo + 5 - j goes with hi + j
+    if (lo < 0 || hi + 6 > 255) return false;
+    uint32_t el[6];
+    sad_counts(u, lo, el);
+    sad_counts(u, hi, e);
+#pragma unroll
+    for (int j = 0; j < 6; ++j) e[j] = el[5 - j] - e[j];
+    wave_sums6(e, s);
+    cv = (int)C[min(hi + lane, 255)] - (int)C[max(lo + 5 - lane, 0)];
+    below = 0;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) below += __builtin_amdgcn_readlane(cv, j) + (s[j] >> 1) < need ? 1 : 0;
+    if (below == 6 || (below == 0 && d0 > 0)) return false;
+    mb_out = m;
+    D_out = d0 + below;
+    return true;
+}
+
 // Processes one int8 tile whose samples this lane already holds in v
 // (tile_load), stores the output, and returns the statistics record this
 // lane must write (see write_stats).
@@ -486,8 +596,23 @@ __device__ __forceinline__ TileStats i8_tile(const StreamView& d, int64_t first,
         int mb, D;
         WinParams p;
         rfi_window_stats ws;
-        i8_wide_tile_select(sm, v, mb, D, pc);
-        if (WPW < 4 || wave == 0) wide_params(pc, mb, D, d.k, W, p, ws);
+        if constexpr (W == 4096 && MODE == kModeStats) {
+            if (i8_stats_select_4096(sm, v, mb, D)) {
+                // flag count and threshold are the replacement pass's
+                ws.median = mb - 128;
+                ws.mad = D;
+                ws.n_flagged = 0;
+                ws.threshold = 0.0f;
+                p.m = ws.median;
+            } else {
+                wave_sync();  // the histogram is taken again
+                i8_wide_tile_select(sm, v, mb, D, pc);
+                wide_params(pc, mb, D, d.k, W, p, ws);
+            }
+        } else {
+            i8_wide_tile_select(sm, v, mb, D, pc);
+            if (WPW < 4 || wave == 0) wide_params(pc, mb, D, d.k, W, p, ws);
+        }
         if (wave % WPW == 0) {
             if (lane == 0) {
                 sm.prm[wl] = p;
@@ -909,7 +1034,7 @@ __global__ __launch_bounds__(kBlock) void k_i8_tiles(LaunchArgs a)
             const Item item = a.items[it];
             const StreamView d = resolve(a.streams[item.stream], a);
             uint32_t v[16];
-            tile_load(d, item.first, v);
+            tile_load<MODES == (1 << kModeStats)>(d, item.first, v);
             write_stats(i8_tile_any<W, NOISE, MODES>(d, item.first, a.seed, sm, v));
         });
     } else {
@@ -1069,7 +1194,7 @@ __global__ __launch_bounds__(kBlock, MODES == 7 ? 4 : 0) void k_i8_fused(LaunchA
 // 4096, three outputs: 198 us with those, 182 without (the bytes moved take
 // 164 at the copy rate).
 template <int CLS>
-__global__ __launch_bounds__(kBlock, 8) void k_i8_multi_wide(MultiArgs ma)
+__global__ __launch_bounds__(kBlock, CLS == 3 ? 8 : 7) void k_i8_multi_wide(MultiArgs ma)
 {
     constexpr int W = 512 << CLS;
     using Smem = I8TileSmem<W, false>;
