@@ -152,13 +152,19 @@ __host__ __device__ inline StreamView resolve(const StreamDesc& d, const LaunchA
 // fused: one kernel for all kinds.
 hipError_t launch_i8_tiles(int cls, int modes, int tpw, const LaunchArgs& a, int grid, hipStream_t s);
 // modes: bit m set if some window of the launch uses mode m.
-// small_nt: threads per window (64, 128 or 256) if every window of the launch
-// spans at most 4 x that many 16-byte chunks of a padded stream that starts
-// at absolute index 0, used when the grid covers every item; 0: windows of
-// any kind, 256 threads each.
-// i8_window_threads: the fewest for windows of up to n samples: n + 30 <= 16 *
-// 4 * NT keeps a window within 4 * NT chunks at any alignment.
-inline int i8_window_threads(int64_t n) { return n <= 4066 ? 64 : n <= 8162 ? 128 : n <= 16354 ? 256 : 0; }
+// small_nt: i8_window_threads of the longest window of the launch, if its
+// streams are padded and start at absolute index 0, used when the grid covers
+// every item; 0: windows of any kind, 256 threads each.
+// i8_window_threads: the fewest threads for windows of up to n samples: four
+// 16-byte chunks per thread, or eight (kWideThreads), which one wave holds
+// without exchanging counts with another; n + 30 <= 16 * chunks * threads
+// keeps a window within them at any alignment.
+constexpr int kWideThreads = 1;
+inline int i8_window_threads(int64_t n)
+{
+    return n <= 4066 ? 64 : n <= 8162 ? 64 | kWideThreads : n <= 16354 ? 128 | kWideThreads
+           : n <= 32738 ? 256 | kWideThreads : 0;
+}
 hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int small_nt = 0);
 hipError_t launch_i8_fused(int modes, const LaunchArgs& a, int grid, hipStream_t s);
 hipError_t launch_i16_tiles(int cls, int modes, const LaunchArgs& a, int grid, hipStream_t s);

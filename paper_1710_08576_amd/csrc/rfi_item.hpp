@@ -58,7 +58,7 @@ __device__ __forceinline__ uint32_t noise_quad_i8(uint64_t j0, uint64_t seed, ui
 // are pooled into one list, and one thread turns each entry into its
 // merged part (noise in the flagged samples), so the draws of a workgroup
 // occupy as few waves as the list needs and an isolated flagged sample
-// costs one block.  A lane holds 4 load slots of P parts (4 / P dwords
+// costs one block.  A lane holds load slots of P parts (4 / P dwords
 // each); cf bit (slot * P + part) marks a part holding a flagged sample;
 // merged(wave, lane, slot, part, x) returns the merged part from the input
 // part x.  The list (1 KiB) and the parts (<= 2 KiB) live in LDS that the tile no
@@ -79,10 +79,11 @@ template <> struct NoisePart<2> { using T = uint2; };
 
 // NT: threads of the workgroup (a multiple of 64, at most 256); the list
 // holds NT parts a round.
-template <int P, int NT = kBlock, class PartFn>
-__device__ __forceinline__ void pool_noise(uint32_t (&v)[16], uint32_t cf, const NoiseScratch& ns,
+template <int P, int NT = kBlock, int NV = 16, class PartFn>
+__device__ __forceinline__ void pool_noise(uint32_t (&v)[NV], uint32_t cf, const NoiseScratch& ns,
                                            PartFn merged)
 {
+    constexpr int NQ = NV * P / 4;  // parts per lane
     using PartT = typename NoisePart<P>::T;
     constexpr int WPP = 4 / P;  // dwords per part
     constexpr int C = NT;       // parts per round
@@ -107,10 +108,10 @@ __device__ __forceinline__ void pool_noise(uint32_t (&v)[16], uint32_t cf, const
     for (int r0 = 0; r0 < F; r0 += C) {
         int e = base - r0;
 #pragma unroll
-        for (int q = 0; q < 4 * P; ++q) {
+        for (int q = 0; q < NQ; ++q) {
             if ((cf >> q) & 1u) {
                 if (e >= 0 && e < C) {
-                    ns.list[e] = (uint32_t)(wave << 8 | lane << 2 | (q / P)) | (uint32_t)(q % P) << 16;
+                    ns.list[e] = (uint32_t)(q / P << 10 | wave << 8 | lane << 2 | (q % P));
                     if constexpr (P == 4) data[e] = v[q];
                     else data[e] = make_uint2(v[WPP * q], v[WPP * q + 1]);
                 }
@@ -121,13 +122,13 @@ __device__ __forceinline__ void pool_noise(uint32_t (&v)[16], uint32_t cf, const
         const int k = (int)threadIdx.x;
         if (k < min(C, F - r0)) {
             const uint32_t ent = ns.list[k];
-            data[k] = merged((int)((ent >> 8) & 3u), (int)((ent >> 2) & 63u), (int)(ent & 3u),
-                             (int)(ent >> 16), data[k]);
+            data[k] = merged((int)((ent >> 8) & 3u), (int)((ent >> 2) & 63u), (int)(ent >> 10), (int)(ent & 3u),
+                             data[k]);
         }
         __syncthreads();
         e = base - r0;
 #pragma unroll
-        for (int q = 0; q < 4 * P; ++q) {
+        for (int q = 0; q < NQ; ++q) {
             if ((cf >> q) & 1u) {
                 if (e >= 0 && e < C) {
                     if constexpr (P == 4) {

@@ -768,11 +768,11 @@ __device__ __forceinline__ uint32_t byte_of(uint32_t v, int b) { return (v >> (8
 
 // Whether a window qualifies for i8_window: 16-byte aligned input and
 // output, no head segment (HEAD: or one of whole chunks, as a serving
-// stream's carry whose blocks start and end on 16 samples), at most four
-// chunks per thread.  NOISE: noise windows too, where each dword of the
+// stream's carry whose blocks start and end on 16 samples), at most K chunks
+// per thread.  NOISE: noise windows too, where each dword of the
 // stream holds one Philox block (absolute index of the stream's first
 // sample a multiple of 4).
-template <bool NOISE, int NT, bool HEAD>
+template <bool NOISE, int NT, int K, bool HEAD>
 __device__ __forceinline__ bool i8_window_ok(const StreamView& d, int64_t a, int n)
 {
     if (d.head_len != 0 && (!HEAD || ((d.head_len | (uint32_t)(uintptr_t)d.x_head) & 15u) != 0)) return false;
@@ -781,12 +781,12 @@ __device__ __forceinline__ bool i8_window_ok(const StreamView& d, int64_t a, int
     // the last chunk may reach up to 15 bytes past the window: inside the
     // stream, or inside the packed layout's padding
     if (!d.padded && ((a + n + 15) & ~(int64_t)15) > d.length) return false;
-    return ((a + n + 15) >> 4) - (a >> 4) <= 4 * NT;
+    return ((a + n + 15) >> 4) - (a >> 4) <= K * NT;
 }
 
 // One window [a, a + n) in registers, by the NT threads `tid` of the
 // workgroup's window `sub` (n = 0: no window, which takes part in the
-// barriers).  The 16-byte chunks covering it are loaded, four per thread,
+// barriers).  The 16-byte chunks covering it are loaded, K per thread,
 // and counted into per-wave replicated histograms; the samples of the edge
 // chunks outside the window are counted as the largest value and taken out
 // of its count again.  The counts are summed and selected as the wide tiles
@@ -801,7 +801,7 @@ __device__ __forceinline__ bool i8_window_ok(const StreamView& d, int64_t a, int
 //
 // MODES: bit m set if the launch has windows in mode m (one bit: the mode is
 // fixed at compile time).
-template <int NT, int MODES, bool HEAD>
+template <int NT, int K, int MODES, bool HEAD>
 __device__ __forceinline__ void i8_window(const StreamView& d, int64_t w, int64_t a, int n, uint64_t seed, int sub,
                                           int tid, I8WinSmem<NT>& sm)
 {
@@ -819,9 +819,9 @@ __device__ __forceinline__ void i8_window(const StreamView& d, int64_t w, int64_
     const int64_t base = a - lead;  // first byte of chunk 0
     const uint8_t* xb = static_cast<const uint8_t*>(d.x) + base;
     const bool edges = lead != 0 || tail != 16;
-    uint32_t v[16];
+    uint32_t v[4 * K];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < K; ++i) {
         const int c = tid + i * NT;
         uint4 t = make_uint4(0, 0, 0, 0);
         if (c < nch) {
@@ -850,7 +850,7 @@ __device__ __forceinline__ void i8_window(const StreamView& d, int64_t w, int64_
         return lo & hi;
     };
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < K; ++i) {
         const int c = tid + i * NT;
         if (c < nch) {
             uint32_t x[4] = {v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
@@ -918,7 +918,7 @@ __device__ __forceinline__ void i8_window(const StreamView& d, int64_t w, int64_
         uint32_t cf = 0;  // bit q: dword q holds a flagged sample
         if (noise) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q)
+            for (int q = 0; q < 4 * K; ++q)
                 if (tid + (q >> 2) * NT < nch) cf |= (outside_i8x4(v[q], lo4, hi4, span4) ? 1u : 0u) << q;
         }
         auto merged = [&](int wvs, int ln, int slot, int part, uint32_t x) -> uint32_t {
@@ -938,7 +938,7 @@ __device__ __forceinline__ void i8_window(const StreamView& d, int64_t w, int64_
     uint8_t* yb = static_cast<uint8_t*>(d.y) + base;
     const bool clip = mode == RFI_MODE_CLIP;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < K; ++i) {
         const int c = tid + i * NT;
         if (c >= nch) continue;
         uint32_t r[4];
@@ -978,8 +978,8 @@ __device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, Generi
     const int W = d.window;
     const int64_t a = w * (int64_t)W;
     const int n = (int)min((int64_t)W, d.length - a);
-    if (REG && i8_window_ok<REG_NOISE, NT, true>(d, a, n)) {
-        i8_window<NT, REG_NOISE ? 15 : 11, true>(d, w, a, n, seed, 0, (int)threadIdx.x, sm);
+    if (REG && i8_window_ok<REG_NOISE, NT, 4, true>(d, a, n)) {
+        i8_window<NT, 4, REG_NOISE ? 15 : 11, true>(d, w, a, n, seed, 0, (int)threadIdx.x, sm);
         return;
     }
     const int tid = (int)threadIdx.x;
@@ -1060,16 +1060,19 @@ __global__ __launch_bounds__(kBlock) void k_i8_tiles(LaunchArgs a)
     }
 }
 
-// Windows of at most 4 * NT chunks of padded streams (plans), kBlock / NT of
+// Windows of at most K * NT chunks of padded streams (plans), kBlock / NT of
 // them per workgroup.  Bound by the VALU (a window's fixed work: clearing and
 // adding up the replicas, the search) below 3000 samples, near HBM from
-// there on.  60 x 2^22 samples, zero / clip / noise, against one window per
-// workgroup of 64, 128 or 256 threads before, with the edge chunks counted
-// and stored byte by byte: W 1000 210 / 203 / 342 -> 172 / 167 / 290 us, 3000
-// 121 / 114 / 176 -> 107 / 101 / 145, 5000 119 / 112 / 160 -> 110 / 105 / 152,
-// 12000 94 / 90 / 126 -> 91 / 88 / 115.
-template <int NT, int MODES>
-__global__ __launch_bounds__(kBlock, 8) void k_i8_windows(LaunchArgs a)
+// there on.  K = 8 (windows of more than 4066 samples): half the waves per
+// window, so half its fixed work, and one wave up to 8162.  60 x 2^22 samples,
+// zero / clip / noise, against one window per workgroup of 64, 128 or 256
+// threads with the edge chunks counted and stored byte by byte: W 1000 210 /
+// 203 / 342 -> 172 / 167 / 283 us, 3000 121 / 114 / 176 -> 107 / 101 / 137,
+// 5000 119 / 112 / 160 -> 100 / 95 / 124 (K = 4: 110 / 105 / 146), 9000 117 /
+// 109 / 163 -> 100 / 96 / 127, 12000 94 / 90 / 126 -> 93 / 90 / 108.  Noise
+// with K = 8: seven waves per SIMD (W 5000 124 us; six 132, five 143).
+template <int NT, int K, int MODES>
+__global__ __launch_bounds__(kBlock, K == 8 && (MODES & 4) ? 7 : 8) void k_i8_windows(LaunchArgs a)
 {
     __shared__ I8WinSmem<NT> sm;
     constexpr int PER = kBlock / NT;
@@ -1081,7 +1084,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_i8_windows(LaunchArgs a)
     const StreamView d = resolve(a.streams[item.stream], a);
     const int64_t first = item.first * (int64_t)d.window;
     const int n = has ? (int)min((int64_t)d.window, d.length - first) : 0;
-    i8_window<NT, MODES, false>(d, item.first, first, n, a.seed, sub, (int)threadIdx.x & (NT - 1), sm);
+    i8_window<NT, K, MODES, false>(d, item.first, first, n, a.seed, sub, (int)threadIdx.x & (NT - 1), sm);
 }
 
 // NOISE: noise windows may take the register path (launched only for items
@@ -1558,6 +1561,14 @@ __device__ __forceinline__ void mom_apply_item(const LaunchArgs& a, const MomIte
             const uint32_t lo = rep_i16(p.lo * 256), hi = rep_i16(p.hi * 256);
             const uint32_t lo_u = rep_i16((p.lo + 128) * 256), hi_u = rep_i16((p.hi + 128) * 256);
             uint32_t nf = 0;
+            if constexpr (MODE == RFI_MODE_NOISE) {
+                // the flags are counted where they are drawn
+                const uint32_t lo4 = rep_i8(p.lo + 128), hi4 = rep_i8(p.hi + 128), span4 = 4u * (uint32_t)(p.hi - p.lo);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    cf |= (outside_i8x4(v[4 * i + q], lo4, hi4, span4) ? 1u : 0u) << (4 * i + q);
+                continue;
+            }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const uint32_t xw = v[4 * i + q];
@@ -1579,7 +1590,9 @@ __device__ __forceinline__ void mom_apply_item(const LaunchArgs& a, const MomIte
                 const WinParams p = sm.prm[rel >> sh];
                 const uint32_t lo_u = rep_i16((p.lo + 128) * 256), hi_u = rep_i16((p.hi + 128) * 256);
                 const uint32_t nz = noise_quad_i8((uint64_t)(d.abs_base + c), a.seed, d.key, p.m, p.sq8);
-                return byte_perm(nz, xw, flag_sel_i8x4(xw, lo_u, hi_u));
+                const uint32_t sel = flag_sel_i8x4(xw, lo_u, hi_u);
+                atomicAdd(&sm.flagged[rel >> sh], (uint32_t)__popc(sel ^ 0x03020100u));  // one bit per flagged byte
+                return byte_perm(nz, xw, sel);
             };
             pool_noise<4>(v, cf, sm.noise(), merged);
         }
@@ -1772,16 +1785,16 @@ hipError_t launch_i8_tiles(int cls, int modes, int tpw, const LaunchArgs& a, int
     if (!k) return hipErrorInvalidValue;
     return launch(k, a, persist ? grid : (int)((a.n_items + tpw - 1) / tpw), s);
 }
-template <int NT>
+template <int NT, int K>
 static void (*i8_window_kernel(int modes))(LaunchArgs)
 {
     switch (modes) {
-        case 1: return k_i8_windows<NT, 1>;
-        case 2: return k_i8_windows<NT, 2>;
-        case 3: return k_i8_windows<NT, 3>;
-        case 4: return k_i8_windows<NT, 4>;
-        case 1 << kModeStats: return k_i8_windows<NT, 1 << kModeStats>;
-        default: return k_i8_windows<NT, 7>;
+        case 1: return k_i8_windows<NT, K, 1>;
+        case 2: return k_i8_windows<NT, K, 2>;
+        case 3: return k_i8_windows<NT, K, 3>;
+        case 4: return k_i8_windows<NT, K, 4>;
+        case 1 << kModeStats: return k_i8_windows<NT, K, 1 << kModeStats>;
+        default: return k_i8_windows<NT, K, 7>;
     }
 }
 
@@ -1789,12 +1802,14 @@ hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream
 {
     const bool persist = grid < a.n_items;
     if (small_nt != 0 && !persist && a.n_items > 0) {
-        void (*k)(LaunchArgs) = small_nt == 64    ? i8_window_kernel<64>(modes)
-                                : small_nt == 128 ? i8_window_kernel<128>(modes)
-                                : small_nt == 256 ? i8_window_kernel<256>(modes)
-                                                  : nullptr;
+        const int nt = small_nt & ~kWideThreads;
+        void (*k)(LaunchArgs) = small_nt == 64                   ? i8_window_kernel<64, 4>(modes)
+                                : small_nt == (64 | kWideThreads)  ? i8_window_kernel<64, 8>(modes)
+                                : small_nt == (128 | kWideThreads) ? i8_window_kernel<128, 8>(modes)
+                                : small_nt == (256 | kWideThreads) ? i8_window_kernel<256, 8>(modes)
+                                                                   : nullptr;
         if (!k) return hipErrorInvalidValue;
-        const int64_t per = kBlock / small_nt;
+        const int64_t per = kBlock / nt;
         const int64_t blocks = (a.n_items + per - 1) / per;
         if (blocks > (1 << 30)) return hipErrorInvalidValue;
         hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kBlock), 0, s, a);

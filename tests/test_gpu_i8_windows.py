@@ -21,9 +21,10 @@ def _streams(rng, n):
         np.where(rng.random(n) < 0.5, -128, 127), g(2))]
 
 
-# 64 threads hold 4066 samples at any start, 128 8162, 256 16354; 16355 takes
-# the two-pass kernel unless it starts on a chunk
-@pytest.mark.parametrize("W", [1, 5, 15, 16, 17, 100, 511, 1000, 4066, 4067, 4095, 8162, 8163, 9000, 16354, 16355, 16383])
+# 64 threads hold 4066 samples at any start, or 8162 in eight chunks each, 128
+# threads 16354, 256 threads 32738; longer windows take the two-pass kernel
+@pytest.mark.parametrize("W", [1, 5, 15, 16, 17, 100, 511, 1000, 4066, 4067, 4095, 8162, 8163, 9000, 16354, 16355, 16383,
+                               32738, 32739])
 @pytest.mark.parametrize("mode", [rfi.ZERO, rfi.CLIP, rfi.NOISE])
 def test_window_sizes(gpu, W, mode):
     rng = np.random.default_rng(W + mode)
