@@ -697,7 +697,9 @@ static int effective_schedule(const rfi_plan* p)
 static int launch_list(const rfi_plan* p)
 {
     if (p->schedule != RFI_SCHED_AUTO) return p->schedule;
-    return tuned(p->tune_key).sched;
+    const int s = tuned(p->tune_key).sched;
+    // tiles per workgroup, when set, are an option of SPLIT's tile launches
+    return s == RFI_SCHED_AUTO && p->tpw > 0 ? RFI_SCHED_SPLIT : s;
 }
 
 // Issues a schedule's launches on s; SPLIT_CONCURRENT forks them over the

@@ -591,6 +591,12 @@ int rfi_server_create(const rfi_server_config* cfg, rfi_server** out)
             e = hipEventCreateWithFlags(&L.slots[s].ev, hipEventDisableTiming);
             // Growing a slot later synchronises the device; start large.
             if (e == hipSuccess) rc = ensure_slot(L.slots[s], kSlotPrealloc);
+            // Touch the staging pages from both sides, so that no block's
+            // latency pays for their first use.
+            if (e == hipSuccess && rc == RFI_OK) {
+                std::memset(L.slots[s].h_stage, 0, L.slots[s].cap);
+                e = launch_stage(L.slots[s].d_buf, L.slots[s].h_stage, (int64_t)(L.slots[s].cap / 16), L.s);
+            }
         }
         // The batch kernels this lane will launch, once, with no items.
         if (e == hipSuccess && rc == RFI_OK) e = (cfg->elem_size == 1 ? warm_i8_fused(false, L.s) : warm_i16_fused(false, L.s));
