@@ -348,16 +348,26 @@ static hipError_t run_launch(const rfi_plan* p, const PlanLaunch& l, const Launc
 }
 
 // Threads of the int16 kernel that holds a stream's windows in registers,
-// four 16-byte chunks (32 samples) per thread: the fewest that span the
-// stream's longest window wherever its windows start (a window that is a
-// multiple of 8 samples starts on a chunk, others up to 7 samples into
-// one).  0: too long, the two-pass radix kernel.  Fewer threads per window
-// means more windows in flight and fewer idle lanes.
+// with four 16-byte chunks (32 samples) each or eight (kWideThreads), for the
+// longest window wherever its windows start (a window that is a multiple of
+// 8 samples starts on a chunk, others up to 7 samples into one).  0: too
+// long, the radix kernel.  Fewer threads per window means less fixed work
+// and fewer barriers, eight chunks fewer waves per SIMD; 60 x 2^21 samples,
+// clip / noise, the taken against the other: W 4096 (512 chunks) 128 x 4
+// against 64 x 8 85 / 103 to 93 / 108 us; W 5000 128 x 8 against 256 x 4 91 /
+// 110 to 107 / 145, W 7000 92 / 103 to 92 / 117; W 9000 256 x 8 against 512 x
+// 4 95 / 144 to 130 / 156, W 12000 90 / 124 to 103 / 127; W 16384 512 x 4
+// against 256 x 8 90 / 105 to 92 / 110.
 static int i16_window_threads(int32_t W, int64_t L)
 {
     const int64_t n = std::min<int64_t>(W, L);
     const int64_t chunks = (n + (W % 8 ? 7 : 0) + 7) / 8;
-    return chunks <= 256 ? 64 : chunks <= 512 ? 128 : chunks <= 1024 ? 256 : chunks <= 2048 ? 512 : 0;
+    return chunks <= 256    ? 64
+           : chunks <= 512  ? 128
+           : chunks <= 1024 ? 128 | kWideThreads
+           : chunks <= 1792 ? 256 | kWideThreads
+           : chunks <= 2048 ? 512
+                            : 0;
 }
 
 // Whose launches a plan takes that nothing was tuned for: SPLIT's, unless

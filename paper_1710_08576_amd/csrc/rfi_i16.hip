@@ -92,15 +92,15 @@ __device__ __forceinline__ uint2 noise_quad_i16(uint64_t j0, uint64_t seed, uint
 }
 
 // ---------------------------------------------------------------------------
-// int16 windows in registers: one window of at most 32 * NT samples per NT
-// threads (four 16-byte chunks per thread).
+// int16 windows in registers: one window of at most 8 * K * NT samples per NT
+// threads (K 16-byte chunks per thread).
 // ---------------------------------------------------------------------------
 // A window is one contiguous run of 16-byte chunks; the samples of the edge
 // chunks outside the window are set to the largest value, whose count in
 // excess is known (`pad` below), so that the counting has no per-sample
 // bounds test.  Chunks past the window's end are skipped: counted too, they
-// would all meet in one slot (W 5000, 19 % of them: 180 us against 110 for
-// 60 x 2^21 samples).
+// would all meet in one slot (W 5000 by 256 threads of four chunks, 19 % of
+// them: 180 us against 110 for 60 x 2^21 samples).
 constexpr uint32_t kI16Pad = 0x7FFF7FFFu;
 
 // Slots of the window's histogram: 16 per thread.
@@ -136,14 +136,14 @@ struct I16WinSmem {
 // which the histogram reaches 1.5 of the samples' MAD on either side of it.
 // -1 if the wave holds no sample.  Only the place and the width of the
 // histogram depend on it, not the results.
-template <int NT>
-__device__ __forceinline__ void i16_estimate(const uint32_t (&v)[16], int nch, int& est, int& shift)
+template <int NT, int K>
+__device__ __forceinline__ void i16_estimate(const uint32_t (&v)[4 * K], int nch, int& est, int& shift)
 {
     constexpr int kSlots = 16 * NT;
     constexpr int kMaxShift = I16WinSmem<NT, false>::kMaxShift;
     const int lane = lane_id();
     uint32_t pick = v[0];
-    if (nch > 3 * NT) pick = lane < 16 ? v[0] : lane < 32 ? v[5] : lane < 48 ? v[10] : v[15];
+    if (nch > 3 * NT) pick = lane < 16 ? v[0] : lane < 32 ? v[5] : lane < 48 ? v[10] : v[15];  // of the first four chunks
     const uint32_t us = (pick ^ 0x8000u) & 0xFFFFu;
     const uint64_t vm = __ballot(us != 0xFFFFu);  // not padding
     const int half = ((int)__popcll(vm) + 1) >> 1;
@@ -177,8 +177,8 @@ __device__ __forceinline__ void i16_estimate(const uint32_t (&v)[16], int nch, i
 // [m - d, m + d], and a pass over |x - m| gives its place in the bracket.
 // If the median or the MAD lies outside the counted values (every thread
 // alike), the histogram is taken again over all 65536 values.
-template <int NT, bool NOISE, bool WHOLE>
-__device__ __forceinline__ void i16_select(const uint32_t (&v)[16], int nch, int pad, int n, int tid, int wave,
+template <int NT, int K, bool NOISE, bool WHOLE>
+__device__ __forceinline__ void i16_select(const uint32_t (&v)[4 * K], int nch, int pad, int n, int tid, int wave,
                                            I16WinSmem<NT, NOISE>& sm, int& m_out, int& D_out)
 {
     using Smem = I16WinSmem<NT, NOISE>;
@@ -188,7 +188,7 @@ __device__ __forceinline__ void i16_select(const uint32_t (&v)[16], int nch, int
     const int lane = lane_id();
     const uint32_t need = (uint32_t)((n - 1) / 2 + 1);
     int est, s;
-    i16_estimate<NT>(v, nch, est, s);
+    i16_estimate<NT, K>(v, nch, est, s);
     auto have = [&](int q) { return WHOLE || tid + (q >> 2) * NT < nch; };  // dword q of this thread
     for (bool full = false;; full = true) {
         group_sync<NT>();  // the previous use of the scratch is over
@@ -256,7 +256,7 @@ __device__ __forceinline__ void i16_select(const uint32_t (&v)[16], int nch, int
         // range are counted from x + 32768 as unsigned halves.
         if (sh == Smem::kMaxShift) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
+            for (int q = 0; q < 4 * K; ++q) {
                 if (have(q)) {
                     const uint32_t u = v[q] ^ bias;
                     atomicAdd(sm.h + ((u & 0xFFFFu) >> Smem::kMaxShift), 1u);
@@ -266,11 +266,11 @@ __device__ __forceinline__ void i16_select(const uint32_t (&v)[16], int nch, int
             }
         } else if (sh == 0) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q)
+            for (int q = 0; q < 4 * K; ++q)
                 if (have(q)) count(v[q], std::false_type{});
         } else {
 #pragma unroll
-            for (int q = 0; q < 16; ++q)
+            for (int q = 0; q < 4 * K; ++q)
                 if (have(q)) count(v[q], std::true_type{});
         }
         group_sync<NT>();
@@ -344,7 +344,7 @@ __device__ __forceinline__ void i16_select(const uint32_t (&v)[16], int nch, int
             // slots start at base, which need not be a multiple of 2^sh
             const uint32_t bu = mtu * 0x10001u;
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
+            for (int q = 0; q < 4 * K; ++q) {
                 if ((q >> 2) * NT < nch) {
                     const uint32_t r = pk_sub_u16(v[q] ^ bias, bu);
                     const bool in0 = have(q) && (r & topmask) == 0, in1 = have(q) && (r & (topmask << 16)) == 0;
@@ -383,7 +383,7 @@ __device__ __forceinline__ void i16_select(const uint32_t (&v)[16], int nch, int
             const uint32_t m2 = rep_i16(m), l2 = rep_i16(lo);
             uint32_t nbelow = 0;
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
+            for (int q = 0; q < 4 * K; ++q) {
                 if ((q >> 2) * NT < nch) {
                     const uint32_t dq = pk_absdiff_i16(v[q], m2);
                     nbelow += (uint32_t)__popcll(__ballot(have(q) && (dq & 0xFFFFu) < (uint32_t)lo)) +
@@ -418,11 +418,11 @@ __device__ __forceinline__ void i16_select(const uint32_t (&v)[16], int nch, int
 }
 
 // One window of NT threads (tid: the thread's index among them).  WHOLE:
-// the window is 32 * NT samples and starts on a chunk (tiles); otherwise any
-// length up to 32 * NT - 14, or any position that spans at most 4 * NT
-// chunks.  MODES: bit m set if the launch has windows in mode m (one bit:
-// the mode is fixed at compile time).
-template <int NT, int MODES, bool WHOLE>
+// the window is 8 * K * NT samples and starts on a chunk (tiles); otherwise
+// any length and position that spans at most K * NT chunks.  MODES: bit m
+// set if the launch has windows in mode m (one bit: the mode is fixed at
+// compile time).
+template <int NT, int K, int MODES, bool WHOLE>
 __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64_t a, int n, uint64_t seed, int tid,
                                            I16WinSmem<NT, (MODES & 4) != 0>& sm)
 {
@@ -430,7 +430,7 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
     const int wave = NT == 64 ? 0 : tid >> 6;
     const int64_t c0 = a >> 3;
     const int lead = WHOLE ? 0 : (int)(a & 7);       // first sample of the window in chunk 0
-    const int nch = WHOLE ? 4 * NT : __builtin_amdgcn_readfirstlane((lead + n + 7) >> 3);
+    const int nch = WHOLE ? K * NT : __builtin_amdgcn_readfirstlane((lead + n + 7) >> 3);
     const int tail = WHOLE ? 8 : ((lead + n - 1) & 7) + 1;  // end of the window in the last chunk
     // first byte of this thread's chunk 0
     const uint8_t* xt = static_cast<const uint8_t*>(d.x) + (c0 + tid) * 16;
@@ -439,9 +439,9 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
         const int f = c == 0 ? lead : 0, e = c == nch - 1 ? tail : 8;
         return (2 * j >= f && 2 * j < e ? 0xFFFFu : 0u) | (2 * j + 1 >= f && 2 * j + 1 < e ? 0xFFFF0000u : 0u);
     };
-    uint32_t v[16];
+    uint32_t v[4 * K];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < K; ++i) {
         uint4 t = make_uint4(kI16Pad, kI16Pad, kI16Pad, kI16Pad);
         if (WHOLE || tid + i * NT < nch) t = gload16_nt(xt + i * NT * 16);
         v[4 * i] = t.x;
@@ -452,7 +452,7 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
     const bool edges = !WHOLE && (lead != 0 || tail != 8);
     if (edges) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < K; ++i) {
             const int c = tid + i * NT;
             if (c == 0 || c == nch - 1) {
 #pragma unroll
@@ -462,7 +462,7 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
     }
     const int pad = nch * 8 - n;
     int m, D;
-    i16_select<NT, (MODES & 4) != 0, WHOLE>(v, nch, pad, n, tid, wave, sm, m, D);
+    i16_select<NT, K, (MODES & 4) != 0, WHOLE>(v, nch, pad, n, tid, wave, sm, m, D);
 
     float sig;
     const float t = threshold_of(D, d.k, sig);
@@ -474,7 +474,7 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
     uint32_t nflag = 0;
     if (mode != RFI_MODE_NOISE) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < K; ++i) {
             if (WHOLE || tid + i * NT < nch) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -506,7 +506,7 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
             const uint32_t lob = rep_i16(lo + 32768), hib = rep_i16(hi + 32768), span4 = 4u * (uint32_t)(hi - lo);
             uint32_t cf = 0;  // bit q: dwords 2q, 2q + 1 hold a flagged sample
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
+            for (int q = 0; q < 2 * K; ++q)
                 if (WHOLE || tid + (q >> 1) * NT < nch)
                     cf |= (outside_i16x4(v[2 * q], v[2 * q + 1], lob, hib, span4) ? 1u : 0u) << q;
             pool_noise_reserved<2, NT>(v, cf, sm.noise(), tid, wave, merged);
@@ -519,7 +519,7 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
     asm volatile("" : "+v"(t2));
     uint8_t* yt = static_cast<uint8_t*>(d.y) + c0 * 16 + (uint64_t)t2 * 16;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < K; ++i) {
         const int c = (int)t2 + i * NT;
         if (!WHOLE && c >= nch) continue;
         if (edges && (c == 0 || c == nch - 1)) {
@@ -551,18 +551,18 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
     }
 }
 
-// Whether a window qualifies for i16_window<NT, , false>: no head segment,
+// Whether a window qualifies for i16_window: no head segment,
 // 16-byte aligned buffers, noise quads that are whole (the stream's first
 // absolute index a multiple of 4), a last chunk that ends inside the stream
-// or the packed layout's padding, at most 4 * NT chunks.
-template <int NT>
+// or the packed layout's padding, at most K * NT chunks.
+template <int NT, int K>
 __device__ __forceinline__ bool i16_window_ok(const StreamView& d, int64_t a, int n)
 {
     if (d.head_len != 0) return false;
     if (d.mode == RFI_MODE_NOISE && (d.abs_base & 3) != 0) return false;
     if (((uintptr_t)d.x | (uintptr_t)d.y) & 15u) return false;
     if (!d.padded && ((a + n + 7) & ~(int64_t)7) > d.length) return false;
-    return ((a + n + 7) >> 3) - (a >> 3) <= 4 * NT;
+    return ((a + n + 7) >> 3) - (a >> 3) <= K * NT;
 }
 
 // Generic int16 window: radix passes over global memory.
@@ -677,22 +677,22 @@ __global__ __launch_bounds__(kBlock, PERSIST ? 0 : (MODES & 4) ? 7 : 8) void k_i
     for_items<PERSIST>(a, [&](int64_t it) {
         const Item item = a.items[it];
         const StreamView d = resolve(a.streams[item.stream], a);
-        i16_window<kBlock, MODES, true>(d, item.first / 8192, item.first, 8192, a.seed, (int)threadIdx.x, sm);
+        i16_window<kBlock, 4, MODES, true>(d, item.first / 8192, item.first, 8192, a.seed, (int)threadIdx.x, sm);
     });
 }
 
-// Windows of at most 4 * NT chunks, NT threads each, of padded streams
+// Windows of at most K * NT chunks, NT threads each, of padded streams
 // (plans).  NT = 64: four windows per workgroup, one per wave, which never
 // wait for each other.  Bound by the selection's VALU and LDS work below
 // 2048 samples (the fixed cost of a window: 1024 slots to clear, add up and
 // search), by HBM from there on.  60 x 2^21 samples, clip, against the
 // radix select over global memory that took every window but 8192 before:
-// W 512 953 -> 196 us, 1000 762 -> 124, 2048 665 -> 95, 4096 630 -> 85,
-// 5000 632 -> 109, 16384 655 -> 94 (5.35 TB/s); noise W 4096 710 -> 109.
-// Eight waves per SIMD; the noise kernels of 128 and 256 threads take seven
-// (no spill: W 4096 114 -> 109 us), those of 64 and 512 measured slower so.
-template <int NT, bool NOISE>
-__global__ __launch_bounds__(NT == 64 ? kBlock : NT, NOISE && (NT == 128 || NT == 256) ? 7 : 8) void k_i16_windows(LaunchArgs a)
+// W 512 953 -> 196 us, 1000 762 -> 120, 2048 665 -> 96, 4096 630 -> 85,
+// 5000 632 -> 91, 16384 655 -> 90 (5.6 TB/s); noise W 4096 710 -> 102.
+// Eight waves per SIMD; the noise kernel of 128 threads and those with eight
+// chunks take seven, so as not to spill.
+template <int NT, int K, bool NOISE>
+__global__ __launch_bounds__(NT == 64 ? kBlock : NT, K == 8 || (NOISE && NT == 128) ? 7 : 8) void k_i16_windows(LaunchArgs a)
 {
     constexpr int PER = NT == 64 ? kBlock / 64 : 1;
     __shared__ I16WinSmem<NT, NOISE> sm[PER];
@@ -705,7 +705,7 @@ __global__ __launch_bounds__(NT == 64 ? kBlock : NT, NOISE && (NT == 128 || NT =
     const int64_t win = item.kind == kItemTile ? item.first / d.window : item.first;
     const int64_t first = win * (int64_t)d.window;
     const int n = (int)min((int64_t)d.window, d.length - first);
-    i16_window<NT, NOISE ? 7 : 3, false>(d, win, first, n, a.seed, (int)threadIdx.x & (NT - 1), sm[sub]);
+    i16_window<NT, K, NOISE ? 7 : 3, false>(d, win, first, n, a.seed, (int)threadIdx.x & (NT - 1), sm[sub]);
 }
 
 union I16FusedSmem {
@@ -718,8 +718,8 @@ __device__ __forceinline__ void i16_generic_any(const StreamView& d, int64_t w, 
 {
     const int64_t first = w * (int64_t)d.window;
     const int n = (int)min((int64_t)d.window, d.length - first);
-    if (i16_window_ok<kBlock>(d, first, n)) {
-        i16_window<kBlock, 7, false>(d, w, first, n, seed, (int)threadIdx.x, sm.t);
+    if (i16_window_ok<kBlock, 4>(d, first, n)) {
+        i16_window<kBlock, 4, 7, false>(d, w, first, n, seed, (int)threadIdx.x, sm.t);
         __syncthreads();  // a following item may use the scratch as the other kind
     } else {
         i16_generic(d, w, seed, sm.g);
@@ -779,15 +779,17 @@ hipError_t launch_i16_generic(const LaunchArgs& a, int modes, int grid, hipStrea
         const bool noise = (modes & 4) != 0;
         void (*k)(LaunchArgs) = nullptr;
         switch (nt) {
-            case 64: k = noise ? k_i16_windows<64, true> : k_i16_windows<64, false>; break;
-            case 128: k = noise ? k_i16_windows<128, true> : k_i16_windows<128, false>; break;
-            case 256: k = noise ? k_i16_windows<256, true> : k_i16_windows<256, false>; break;
-            case 512: k = noise ? k_i16_windows<512, true> : k_i16_windows<512, false>; break;
+            case 64: k = noise ? k_i16_windows<64, 4, true> : k_i16_windows<64, 4, false>; break;
+            case 128: k = noise ? k_i16_windows<128, 4, true> : k_i16_windows<128, 4, false>; break;
+            case 128 | kWideThreads: k = noise ? k_i16_windows<128, 8, true> : k_i16_windows<128, 8, false>; break;
+            case 256 | kWideThreads: k = noise ? k_i16_windows<256, 8, true> : k_i16_windows<256, 8, false>; break;
+            case 512: k = noise ? k_i16_windows<512, 4, true> : k_i16_windows<512, 4, false>; break;
             default: return hipErrorInvalidValue;
         }
-        const int64_t blocks = nt == 64 ? (a.n_items + 3) / 4 : a.n_items;
+        const int threads = nt & ~kWideThreads;
+        const int64_t blocks = threads == 64 ? (a.n_items + 3) / 4 : a.n_items;
         if (blocks > (1 << 30)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(nt == 64 ? kBlock : (unsigned)nt), 0, s, a);
+        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(threads == 64 ? kBlock : (unsigned)threads), 0, s, a);
         return hipGetLastError();
     }
     return launch(RFI_PICK(k_i16_generic, a, grid), a, grid, s);

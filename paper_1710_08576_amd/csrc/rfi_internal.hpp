@@ -168,10 +168,10 @@ inline int i8_window_threads(int64_t n)
 hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int small_nt = 0);
 hipError_t launch_i8_fused(int modes, const LaunchArgs& a, int grid, hipStream_t s);
 hipError_t launch_i16_tiles(int cls, int modes, const LaunchArgs& a, int grid, hipStream_t s);
-// nt: threads per window (64, 128, 256 or 512) if every window of the launch
-// spans at most 4 * nt 16-byte chunks of a padded stream that starts at
-// absolute index 0, used when the grid covers every item; 0: 256-thread
-// workgroups for windows of any kind.
+// nt: threads per window (64, 128 or 512 with four 16-byte chunks each, 128 or
+// 256 with eight: kWideThreads) if they hold every window of the launch, its
+// streams are padded and start at absolute index 0, used when the grid covers
+// every item; 0: 256-thread workgroups for windows of any kind.
 hipError_t launch_i16_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int nt = 0);
 hipError_t launch_i16_fused(const LaunchArgs& a, int grid, hipStream_t s);
 // One workgroup of the all-modes fused kernel (int8) or of the int16 fused

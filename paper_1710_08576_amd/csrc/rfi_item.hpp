@@ -165,8 +165,8 @@ __device__ __forceinline__ void group_sync()
 // workgroup may still be reading.  NT = 64: one wave by itself, with no
 // barriers and no counter, whose list may take the place of what the wave
 // no longer needs.  tid: the thread's index among the NT.
-template <int P, int NT, class PartFn>
-__device__ __forceinline__ void pool_noise_reserved(uint32_t (&v)[16], uint32_t cf, const NoiseScratch& ns, int tid,
+template <int P, int NT, int NV = 16, class PartFn>
+__device__ __forceinline__ void pool_noise_reserved(uint32_t (&v)[NV], uint32_t cf, const NoiseScratch& ns, int tid,
                                                     int wave, PartFn merged)
 {
     using PartT = typename NoisePart<P>::T;
@@ -188,10 +188,10 @@ __device__ __forceinline__ void pool_noise_reserved(uint32_t (&v)[16], uint32_t 
     for (int r0 = 0;; r0 += C) {
         int e = base - r0;
 #pragma unroll
-        for (int q = 0; q < 4 * P; ++q) {
+        for (int q = 0; q < NV * P / 4; ++q) {
             if ((cf >> q) & 1u) {
                 if (e >= 0 && e < C) {
-                    ns.list[e] = (uint32_t)(wave << 8 | lane << 2 | (q / P)) | (uint32_t)(q % P) << 16;
+                    ns.list[e] = (uint32_t)(q / P << 12 | wave << 8 | lane << 2 | (q % P));
                     if constexpr (P == 4) data[e] = v[q];
                     else data[e] = make_uint2(v[WPP * q], v[WPP * q + 1]);
                 }
@@ -203,13 +203,13 @@ __device__ __forceinline__ void pool_noise_reserved(uint32_t (&v)[16], uint32_t 
         const int k = tid;
         if (k < min(C, F - r0)) {
             const uint32_t ent = ns.list[k];
-            data[k] = merged((int)((ent >> 8) & 0xFFu), (int)((ent >> 2) & 63u), (int)(ent & 3u),
-                             (int)(ent >> 16), data[k]);
+            data[k] = merged((int)((ent >> 8) & 15u), (int)((ent >> 2) & 63u), (int)(ent >> 12), (int)(ent & 3u),
+                             data[k]);
         }
         group_sync<NT>();
         e = base - r0;
 #pragma unroll
-        for (int q = 0; q < 4 * P; ++q) {
+        for (int q = 0; q < NV * P / 4; ++q) {
             if ((cf >> q) & 1u) {
                 if (e >= 0 && e < C) {
                     if constexpr (P == 4) {

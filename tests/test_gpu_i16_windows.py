@@ -29,9 +29,9 @@ def _signals(rng, n):
     return [np.asarray(s).astype(np.int16) for s in out]
 
 
-# 64 threads hold 2048 samples (2041 at any start), 128, 256 and 512 threads
-# twice as many each; 16384 is the longest, 16385 takes the radix kernel
-@pytest.mark.parametrize("W", [9, 500, 512, 1000, 2041, 2042, 2048, 2049, 4088, 4096, 4097, 8184, 8185, 8191, 16376,
+# 64 threads hold 2048 samples (2041 at any start), 128 4096, or 8192 in eight
+# chunks each, 256 14336, 512 16384; 16385 takes the radix kernel
+@pytest.mark.parametrize("W", [9, 500, 512, 1000, 2041, 2042, 2048, 2049, 4088, 4096, 4097, 8184, 8185, 8191, 9001, 14329, 14336, 14337, 16376,
                                16377, 16384, 16385])
 @pytest.mark.parametrize("mode", [rfi.ZERO, rfi.CLIP, rfi.NOISE])
 def test_window_sizes(gpu, W, mode):
