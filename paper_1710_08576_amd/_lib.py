@@ -551,7 +551,9 @@ def n_blocks(lengths, block: int) -> int:
     a block below 1 (the library rejects it)."""
     if block < 1:
         return 0
-    return int(((np.asarray(lengths, dtype=np.int64) + (block - 1)) // block).sum())
+    if isinstance(lengths, np.ndarray) and lengths.dtype == np.int64 and block < 1 << 62:
+        return int((-(-lengths // block)).sum())
+    return sum(-(-int(L) // block) for L in lengths)
 
 
 def block_power(x, lengths, block: int, out=None, stream=None):
