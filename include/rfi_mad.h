@@ -340,8 +340,9 @@ int rfi_shutdown(void);
 /* into shared batched launches (continuous batching): stream s runs   */
 /* on lane s % n_lanes (one HIP stream each); a lane launches, per     */
 /* batch, the next admitted block of each of its streams (at most      */
-/* max_batch blocks) as one fused kernel launch plus one carry-update  */
-/* launch, and keeps up to two batches in flight.                      */
+/* max_batch blocks) as one kernel launch that filters the windows and */
+/* updates the carries, after a copy kernel that brings in the batch's */
+/* tables, and keeps up to two batches in flight.                      */
 /* Output of a stream is emitted window by window: a submit emits the  */
 /* carry plus as many whole windows as the block completes, into       */
 /* out_dev, which must hold n + W - 1 elements.                        */

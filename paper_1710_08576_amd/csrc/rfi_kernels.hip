@@ -25,9 +25,8 @@
 //   one list, one thread draws one Philox4x64-10 block per entry, and the
 //   owners merge the noise bytes back, so the cost follows the number of
 //   flagged parts, not the worst lane.
-// Also here: the several-outputs tile kernel, the median-of-MAD passes
-//   (MAD gather, block counts, search, history, replacement) and the serving
-//   carry copy.
+// Also here: the several-outputs kernels, the median-of-MAD search and
+//   replacement, and the copy that brings a serving batch's tables in.
 #include "rfi_item.hpp"
 
 namespace rfi {
@@ -508,8 +507,8 @@ __device__ __forceinline__ void wave_sums6(const uint32_t (&e)[6], int (&sum)[6]
 // each place that decides the result, the median and m + D and m - D, by
 // sums of distances, and added to the histogram's cumulative counts there.
 // False if the result is not among those values; the counts are then taken
-// from all samples.  60 x 2^21 samples: 44 -> 32 us (3.9
-// TB/s read), 60 x 2^20 23.6 -> 18.
+// from all samples.  60 x 2^21 samples: 44 -> 32 us (3.9 TB/s read), 60 x
+// 2^20 23.6 -> 18.
 template <bool NS>
 __device__ __forceinline__ bool i8_stats_select_4096(I8TileSmem<4096, NS>& sm, const uint32_t (&v)[16], int& mb_out,
                                                      int& D_out)
@@ -1353,11 +1352,12 @@ __global__ __launch_bounds__(kBlock) void k_i8_multi(MultiArgs ma)
 // [a0, p0) that precede the group's first window in its history are counted
 // into a 256-value histogram; window i of the group then differs from that
 // by its predecessors' and its own MAD added and by the entries from a0 on
-// that its history no longer holds (for K < 64 the group's own among them), which for one value v are two ballots and their popcounts for all
-// 64 windows at once.  The medians are found by trying the values in order
-// from the first that any window can reach; MADs of neighbouring windows
-// differ little, so a few values do.  From group to group the histogram
-// takes up 64 entries and drops as many.
+// that its history no longer holds (for K < 64 the group's own among them),
+// which for one value v are two ballots and their popcounts for all 64
+// windows at once.  The medians are found by trying the values in order from
+// the first that any window can reach; MADs of neighbouring windows differ
+// little, so a few values do.  From group to group the histogram takes up 64
+// entries and drops as many.
 //
 // The counts have 16 replicas (lane & 15): MADs cluster on a few values, on
 // which the atomics of a wave would meet.  Latency-bound: 60 streams of 256
@@ -1904,12 +1904,18 @@ hipError_t launch_stage(void* dst, const void* src_host, int64_t n16, hipStream_
     return hipGetLastError();
 }
 
+// Every instance that a batch may take (one mode, or mixed): a kernel's first
+// dispatch pays for bringing its code in.
 hipError_t warm_i8_fused(bool persist, hipStream_t s)
 {
     LaunchArgs a{};  // no items: the workgroup returns at once
-    void (*k)(LaunchArgs) = persist ? i8_fused_kernel<true>(7) : i8_fused_kernel<false>(7);
     void* kargs[] = {&a};
-    return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3(1), dim3(kBlock), kargs, 0, s);
+    for (int modes : {1, 2, 4, 7}) {
+        void (*k)(LaunchArgs) = persist ? i8_fused_kernel<true>(modes) : i8_fused_kernel<false>(modes);
+        hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(k), dim3(1), dim3(kBlock), kargs, 0, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 int i8_persistent_grid(int cls, int modes, bool fused)
