@@ -1072,10 +1072,11 @@ __global__ __launch_bounds__(kBlock) void k_i8_tiles(LaunchArgs a)
 // window, so half its fixed work, and one wave up to 8162.  60 x 2^22 samples,
 // zero / clip / noise, against one window per workgroup of 64, 128 or 256
 // threads with the edge chunks counted and stored byte by byte: W 1000 210 /
-// 203 / 342 -> 172 / 167 / 283 us, 3000 121 / 114 / 176 -> 107 / 101 / 137,
-// 5000 119 / 112 / 160 -> 100 / 95 / 124 (K = 4: 110 / 105 / 146), 9000 117 /
-// 109 / 163 -> 100 / 96 / 127, 12000 94 / 90 / 126 -> 93 / 90 / 108.  Noise
-// with K = 8: seven waves per SIMD (W 5000 124 us; six 132, five 143).
+// 203 / 342 -> 172 / 167 / 273 us, 3000 121 / 114 / 176 -> 107 / 101 / 133,
+// 5000 119 / 112 / 160 -> 100 / 95 / 122 (K = 4: 110 / 105 / 146), 9000 117 /
+// 109 / 163 -> 100 / 96 / 127, 12000 94 / 90 / 126 -> 93 / 90 / 106.  Noise
+// with K = 8: seven waves per SIMD (W 5000, before the offsets were formed again
+// after the draws, 124 us; six 132, five 143).
 template <int NT, int K, int MODES>
 __global__ __launch_bounds__(kBlock, K == 8 && (MODES & 4) ? 7 : 8) void k_i8_windows(LaunchArgs a)
 {
