@@ -1544,13 +1544,15 @@ __device__ __forceinline__ void mom_apply_item(const LaunchArgs& a, const MomIte
     const int64_t s1 = min((it.first_window + it.n_windows) * (int64_t)W, d.length);
     const int8_t* x = static_cast<const int8_t*>(d.x);
     int8_t* y = static_cast<int8_t*>(d.y);
-    if (s1 - s0 == 16384 && (W & 15) == 0) {
-        // A whole 16 KiB tile of windows that are multiples of 16 samples:
-        // every 16-byte chunk lies in one window.  All four loads of a lane
-        // are issued before any store; noise goes through the workgroup pool.
+    if (s1 - s0 == 16384 && (W & 15) == 0 && (W & (W - 1)) == 0) {
+        // A whole 16 KiB tile of windows of a power of two of samples, at
+        // least 16: every 16-byte chunk lies in one window.  (Another W above
+        // 16384 may end a stream with a window of 16384 samples.)  All four
+        // loads of a lane are issued before any store; noise goes through the
+        // workgroup pool.
         const int lane = tid & 63, wave = tid >> 6;
         const int64_t base = s0 + wave * 4096 + lane * 16;
-        const int sh = __builtin_ctz((unsigned)W);  // W divides 16384: a power of two
+        const int sh = __builtin_ctz((unsigned)W);
         uint32_t v[16];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
