@@ -1544,7 +1544,10 @@ __device__ __forceinline__ void mom_apply_item(const LaunchArgs& a, const MomIte
     const int64_t s1 = min((it.first_window + it.n_windows) * (int64_t)W, d.length);
     const int8_t* x = static_cast<const int8_t*>(d.x);
     int8_t* y = static_cast<int8_t*>(d.y);
-    if (s1 - s0 == 16384 && (W & 15) == 0 && (W & (W - 1)) == 0) {
+    // Noise is drawn four samples (one Philox block) at a time where the
+    // stream's dwords are whole blocks.
+    const bool quads = MODE != RFI_MODE_NOISE || (d.abs_base & 3) == 0;
+    if (s1 - s0 == 16384 && (W & 15) == 0 && (W & (W - 1)) == 0 && quads) {
         // A whole 16 KiB tile of windows of a power of two of samples, at
         // least 16: every 16-byte chunk lies in one window.  (Another W above
         // 16384 may end a stream with a window of 16384 samples.)  All four
@@ -1608,7 +1611,7 @@ __device__ __forceinline__ void mom_apply_item(const LaunchArgs& a, const MomIte
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             gstore16_nt(y + base + i * 1024, make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]));
-    } else if (W >= 16 && (MODE != RFI_MODE_NOISE || (d.abs_base & 3) == 0)) {
+    } else if (W >= 16 && quads) {
         // Other items (irregular W, stream tails): 16-byte chunks of the
         // stream, 16 KiB a pass.  A chunk holds samples of at most two of the
         // item's windows, the second from its byte t on; the edge chunks hold

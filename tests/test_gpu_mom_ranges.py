@@ -1,5 +1,6 @@
 """Median of MAD over the whole range of its arguments, bit-exact against the
-CPU oracle: windows longer than a 16 KiB tile."""
+CPU oracle: windows longer than a 16 KiB tile, and noise from any absolute
+index."""
 import numpy as np
 import pytest
 import torch
@@ -29,3 +30,21 @@ def test_windows_above_a_tile(gpu, W, mode):
     args = (L, [W] * 4, [2.0] * 4, [mode] * 4, 2)
     y, st = rfi.mom_filter(x.to(gpu), *args, seed=5)
     _compare(y.cpu().numpy(), rfi.stats_numpy(st), x.numpy(), *args, 5)
+
+
+@pytest.mark.parametrize("W", [512, 4096, 16384, 1000])
+@pytest.mark.parametrize("base", [0, 1, 2, 3, 4097])
+def test_noise_at_any_absolute_index(gpu, W, base):
+    """A stream whose first sample has an absolute index that is no multiple
+    of 4: sample j of whole tiles and of tails draws word j & 3 of block
+    j >> 2 (mom_k 1, so each window equals the plain filter's)."""
+    L, k, seed = 2 * 16384 + 700, 1.5, 11
+    x = synth.gen_packed([synth.StreamSpec(L, W, k, rfi.NOISE, 9.0, 0.01, 8, 3000)], W + base, 31)
+    absb = torch.tensor([base], dtype=torch.int64, device=gpu)
+    y, st = rfi.mom_filter_carry(x.to(gpu), [L], [W], [k], [rfi.NOISE], 1, absb, None, None, seed=seed)
+    y, st, xn = y.cpu().numpy(), rfi.stats_numpy(st), x.numpy()
+    for w, o in enumerate(range(0, L, W)):
+        n = min(W, L - o)
+        yo, so = oracle.window(xn[o:o + n], k, rfi.NOISE, abs_start=base + o, stream=0, seed=seed)
+        assert np.array_equal(y[o:o + n], yo), w
+        assert st[w] == so, w
