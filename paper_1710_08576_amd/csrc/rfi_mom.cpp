@@ -36,7 +36,6 @@ struct MomKey {
     int device;
     uintptr_t stream;  // temporaries are per stream: calls on one stream are ordered
     int64_t pre;       // history slots per stream (0, or K - 1 with a carried history)
-    int32_t per_wave;  // groups of 64 windows per wave of pass 2
     uint64_t seed;
     std::vector<int64_t> L;
     std::vector<int32_t> W;
@@ -47,7 +46,6 @@ struct MomKey {
         if (device != o.device) return device < o.device;
         if (stream != o.stream) return stream < o.stream;
         if (pre != o.pre) return pre < o.pre;
-        if (per_wave != o.per_wave) return per_wave < o.per_wave;
         if (seed != o.seed) return seed < o.seed;
         if (L != o.L) return L < o.L;
         if (W != o.W) return W < o.W;
@@ -112,8 +110,25 @@ int alloc(T** dst, int64_t n)
     return e == hipSuccess ? RFI_OK : hip_fail(e);
 }
 
+// Groups of 64 windows that a wave of pass 2 takes one after another: as many
+// as keep the waves at 2048, which is what the device holds at once (17 KiB of
+// LDS each).  A wave counts a whole history before its first group, so a
+// further round of waves costs more than the groups it takes off the others,
+// whatever the history's length.  W 16, windows x streams, mom_k, groups per
+// wave, microseconds of the whole call: 8192 x 60, 4096, 1 / 4 / 16 groups 238
+// / 226 / 241, 10^6 246 / 229 / 246; 65536 x 60, 4096, 8 / 32 / 128 groups 1681
+// / 1680 / 1822; 2^20 x 8, 60000, 32 / 64 / 128 groups 3666 / 3606 / 3699; and
+// fewer windows than that, W 512, 32768 x 1, 10^6, 1 / 4 / 64 groups 50 / 54 /
+// 134.
+int32_t groups_per_wave(int32_t n, const int64_t* L, const int32_t* W)
+{
+    int64_t groups = 0;
+    for (int32_t s = 0; s < n; ++s) groups += ((L[s] + W[s] - 1) / W[s] + 63) / 64;
+    return (int32_t)std::min<int64_t>(std::max<int64_t>(1, (groups + 2047) / 2048), 1 << 16);
+}
+
 int mom_build(int32_t n, const int64_t* L, const int32_t* W, const float* K, const int32_t* M,
-              uint64_t seed, int64_t pre, int32_t per_wave, MomPlan** out)
+              uint64_t seed, int64_t pre, MomPlan** out)
 {
     MomPlan* p = new MomPlan;
     if (hipGetDevice(&p->device) != hipSuccess) p->device = 0;
@@ -128,6 +143,7 @@ int mom_build(int32_t n, const int64_t* L, const int32_t* W, const float* K, con
     std::vector<MomItem> items;
     std::vector<MomSeg> segs;
     std::vector<int64_t> woff(n);
+    const int64_t seg = 64 * (int64_t)groups_per_wave(n, L, W);
     int64_t soff = 0, wo = 0;
     for (int s = 0; s < n && rc == RFI_OK; ++s) {
         StreamDesc& d = desc[s];
@@ -146,8 +162,7 @@ int mom_build(int32_t n, const int64_t* L, const int32_t* W, const float* K, con
         ms[s].nw = nw;
         ms[s].pre = pre;
         woff[s] = wo;
-        for (int64_t w = 0; w < nw; w += 64 * (int64_t)per_wave)
-            segs.push_back(MomSeg{s, (int32_t)std::min<int64_t>(64 * (int64_t)per_wave, nw - w), w});
+        for (int64_t w = 0; w < nw; w += seg) segs.push_back(MomSeg{s, (int32_t)std::min(seg, nw - w), w});
         const int64_t per = std::max<int64_t>(1, std::min<int64_t>(256, 16384 / W[s]));
         for (int64_t w = 0; w < nw; w += per)
             items.push_back(MomItem{s, (int32_t)std::min<int64_t>(per, nw - w), w});
@@ -201,18 +216,6 @@ int mom_execute(MomPlan* p, const void* x, void* y, rfi_window_stats* st, int32_
     return e == hipSuccess ? RFI_OK : hip_fail(e);
 }
 
-// Groups of 64 windows that a wave of pass 2 takes one after another: one
-// while that leaves at most some 4000 waves (four per SIMD), then as many as
-// keep their number there, since a wave counts a whole history of up to K
-// MADs before its first group; and at least K / 16384 groups, so that a long
-// history is read no more than 256 times per window.
-int32_t groups_per_wave(int32_t n, const int64_t* L, const int32_t* W, int32_t mom_k)
-{
-    int64_t groups = 0;
-    for (int32_t s = 0; s < n; ++s) groups += ((L[s] + W[s] - 1) / W[s] + 63) / 64;
-    return (int32_t)std::min<int64_t>(std::max<int64_t>({1, groups / 4096, mom_k / 16384}), 1 << 16);
-}
-
 std::mutex g_mom_mu;
 std::map<MomKey, MomPlan*> g_mom;
 std::vector<MomKey> g_mom_order;
@@ -237,7 +240,6 @@ int mom_call(const int8_t* x, int8_t* y, int32_t n_streams, const int64_t* lengt
     if (hipGetDevice(&key.device) != hipSuccess) key.device = 0;
     key.stream = (uintptr_t)stream;
     key.pre = carry ? (int64_t)mom_k - 1 : 0;
-    key.per_wave = groups_per_wave(n_streams, lengths, windows, mom_k);
     key.seed = seed;
     key.L.assign(lengths, lengths + n_streams);
     key.W.assign(windows, windows + n_streams);
@@ -256,7 +258,7 @@ int mom_call(const int8_t* x, int8_t* y, int32_t n_streams, const int64_t* lengt
             g_mom.erase(old);
             g_mom_order.erase(g_mom_order.begin());
         }
-        rc = mom_build(n_streams, lengths, windows, k, mode, seed, key.pre, key.per_wave, &p);
+        rc = mom_build(n_streams, lengths, windows, k, mode, seed, key.pre, &p);
         if (rc != RFI_OK) return rc;
         g_mom[key] = p;
         g_mom_order.push_back(key);

@@ -1,6 +1,6 @@
 """Median of MAD over the whole range of its arguments, bit-exact against the
-CPU oracle: windows longer than a 16 KiB tile, and noise from any absolute
-index."""
+CPU oracle: windows longer than a 16 KiB tile, noise from any absolute index,
+and histories over many groups of 64 windows."""
 import numpy as np
 import pytest
 import torch
@@ -9,7 +9,7 @@ import oracle
 import paper_1710_08576_amd as rfi
 from paper_1710_08576_amd import synth
 
-pytestmark = pytest.mark.gpu
+gpu_only = pytest.mark.gpu
 
 
 def _compare(y, st, x, L, W, K, M, mom_k, seed):
@@ -19,6 +19,7 @@ def _compare(y, st, x, L, W, K, M, mom_k, seed):
     assert np.array_equal(st, sto)
 
 
+@gpu_only
 @pytest.mark.parametrize("W", [16400, 20000, 24576, 32768, 65536])
 @pytest.mark.parametrize("mode", [rfi.ZERO, rfi.CLIP, rfi.NOISE])
 def test_windows_above_a_tile(gpu, W, mode):
@@ -32,6 +33,7 @@ def test_windows_above_a_tile(gpu, W, mode):
     _compare(y.cpu().numpy(), rfi.stats_numpy(st), x.numpy(), *args, 5)
 
 
+@gpu_only
 @pytest.mark.parametrize("W", [512, 4096, 16384, 1000])
 @pytest.mark.parametrize("base", [0, 1, 2, 3, 4097])
 def test_noise_at_any_absolute_index(gpu, W, base):
@@ -48,3 +50,104 @@ def test_noise_at_any_absolute_index(gpu, W, base):
         yo, so = oracle.window(xn[o:o + n], k, rfi.NOISE, abs_start=base + o, stream=0, seed=seed)
         assert np.array_equal(y[o:o + n], yo), w
         assert st[w] == so, w
+
+
+def _reference(x, L, W, K, M, mom_k):
+    """mom_filter of zero and clip streams from each window's median and MAD
+    (the oracle's plain filter) and running counts of the MADs: the oracle's
+    own median of MAD takes a time that grows with windows x mom_k."""
+    _, own = oracle.filter_batch(x, L, W, K, M)
+    so, wo, nw, _ = rfi.layout(L, W)
+    y, st = x.copy(), own.copy()
+    for s, n in enumerate(L):
+        o, w0, w1 = so[s], wo[s], wo[s] + -(-n // W[s])
+        mad, b = own["mad"][w0:w1], np.arange(1, w1 - w0 + 1)
+        a = np.maximum(b - mom_k, 0)
+        scale = np.full(len(b), -1)
+        for v in np.unique(mad):
+            count = np.concatenate([[0], np.cumsum(mad <= v)])
+            scale[(scale < 0) & (count[b] - count[a] > (b - a - 1) // 2)] = v
+        thr = np.float32(K[s]) * (np.float32(1.4826) * scale.astype(np.float32))
+        of = np.arange(n) // W[s]
+        v, m, e = x[o:o + n].astype(np.int64), own["median"][w0:w1][of], np.floor(thr).astype(np.int64)[of]
+        hit = np.abs(v - m) > e
+        y[o:o + n] = np.where(hit, 0, v) if M[s] == rfi.ZERO else np.clip(v, np.maximum(m - e, -128), np.minimum(m + e, 127))
+        st["threshold"][w0:w1] = thr
+        st["n_flagged"][w0:w1] = np.bincount(of[hit], minlength=w1 - w0)
+    return y, st
+
+
+def _drifting(seed, nw, W):
+    """nw windows whose level goes up and down, so that the medians move."""
+    sd = 4 + 20 * (1 + np.sin(np.arange(nw) / (nw / 9.7)))
+    x = np.random.default_rng(seed).normal(0, 1, (nw, W)) * sd[:, None]
+    return np.clip(np.round(x), -128, 127).astype(np.int8).reshape(-1)
+
+
+def test_reference_is_the_oracle():
+    x = synth.pack([torch.as_tensor(_drifting(5, 700, 16)[:-3]), torch.as_tensor(_drifting(6, 90, 50))]).numpy()
+    for mom_k in (1, 7, 64, 300):
+        args = ([700 * 16 - 3, 90 * 50], [16, 50], [2.0, 1.5], [rfi.ZERO, rfi.CLIP], mom_k)
+        y, st = _reference(x, *args)
+        yo, sto = oracle.mom_filter_batch(x, *args)
+        assert np.array_equal(y, yo) and np.array_equal(st, sto)
+
+
+# waves of two and of five groups of 64 windows, a last one that is not whole,
+# histories shorter and longer than a wave's windows
+@gpu_only
+@pytest.mark.parametrize("nw", [132_000, 600_007])
+@pytest.mark.parametrize("mom_k", [1, 7, 63, 64, 65, 300, 40_000])
+def test_waves_of_several_groups(gpu, nw, mom_k):
+    x = _drifting(nw + mom_k, nw, 16)
+    x = synth.pack([torch.as_tensor(x[:-3]), torch.as_tensor(x[:333 * 16])])
+    args = ([nw * 16 - 3, 333 * 16], [16] * 2, [2.0] * 2, [rfi.ZERO, rfi.CLIP], mom_k)
+    y, st = rfi.mom_filter(x.to(gpu), *args, seed=3)
+    yo, sto = _reference(x.numpy(), *args)
+    so = rfi.layout(args[0], args[1])[0]
+    for o, n in zip(so, args[0]):
+        assert np.array_equal(y.cpu().numpy()[o:o + n], yo[o:o + n])
+    assert np.array_equal(rfi.stats_numpy(st), sto)
+
+
+@gpu_only
+@pytest.mark.parametrize("mom_k", [65, 40_000])
+def test_carried_history_of_many_windows(gpu, mom_k):
+    """A stream in two calls of about 140000 windows with its history carried
+    equals one call."""
+    W, cut, nw = 16, 140_004, 285_000
+    x = torch.as_tensor(_drifting(mom_k, nw, W))
+    yo, sto = _reference(x.numpy(), [nw * W], [W], [2.0], [rfi.CLIP], mom_k)
+    hist = torch.zeros((1, mom_k - 1), dtype=torch.uint8, device=gpu)
+    hlen = torch.zeros(1, dtype=torch.int32, device=gpu)
+    for a, b in ((0, cut), (cut, nw)):
+        absb = torch.tensor([a * W], dtype=torch.int64, device=gpu)
+        xd = torch.zeros(synth.align_up((b - a) * W), dtype=torch.int8, device=gpu)
+        xd[:(b - a) * W] = x[a * W:b * W].to(gpu)
+        y, st = rfi.mom_filter_carry(xd, [(b - a) * W], [W], [2.0], [rfi.CLIP], mom_k, absb, hist, hlen, seed=3)
+        assert np.array_equal(y.cpu().numpy()[:(b - a) * W], yo[a * W:b * W])
+        assert np.array_equal(rfi.stats_numpy(st), sto[a:b])
+    assert hlen.item() == mom_k - 1
+
+
+@gpu_only
+def test_capture_with_another_history(gpu):
+    """A call of known sizes but another mom_k needs no new work tables, so it
+    can be captured; every replay equals the eager call."""
+    L, W, K, M = [200_000, 30_000], [512, 700], [3.0, 2.0], [rfi.NOISE, rfi.CLIP]
+    specs = [synth.StreamSpec(*v, 9.0, 0.02, 8, 600) for v in zip(L, W, K, M)]
+    x = [synth.gen_packed(specs, s, 31) for s in (1, 2)]
+    xd = x[0].to(gpu)
+    y, s = torch.zeros_like(xd), torch.cuda.Stream()
+    rfi.mom_filter(xd, L, W, K, M, 3, seed=4, y=y, stream=s)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        _, st = rfi.mom_filter(xd, L, W, K, M, 40_000, seed=4, y=y, stream=s)
+    for r in range(4):
+        xd.copy_(x[r % 2])
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        _compare(y.cpu().numpy(), rfi.stats_numpy(st), x[r % 2].numpy(), L, W, K, M, 40_000, 4)
+        y.zero_()
