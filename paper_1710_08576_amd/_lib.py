@@ -582,7 +582,7 @@ def improvement(power_u, power_f, lengths, block: int, seg_blocks: int, out=None
     L = np.ascontiguousarray(lengths, dtype=np.int64)
     if out is None:
         out = torch.empty((max(len(L), 1), 3), dtype=torch.float64, device=power_u.device)
-    rc = load().rfi_improvement(power_u.data_ptr(), power_f.data_ptr(), len(L), _addr(L), int(block), int(seg_blocks),
+    rc = load().rfi_improvement(_dptr(power_u), _dptr(power_f), len(L), _addr(L), int(block), int(seg_blocks),
                                 out.data_ptr(), _raw_stream(stream))
     _check(rc, "rfi_improvement")
     return out[:len(L)]
