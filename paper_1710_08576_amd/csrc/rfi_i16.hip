@@ -789,8 +789,7 @@ hipError_t launch_i16_generic(const LaunchArgs& a, int modes, int grid, hipStrea
         const int threads = nt & ~kWideThreads;
         const int64_t blocks = threads == 64 ? (a.n_items + 3) / 4 : a.n_items;
         if (blocks > (1 << 30)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(threads == 64 ? kBlock : (unsigned)threads), 0, s, a);
-        return hipGetLastError();
+        return launch_kernel(k, dim3((unsigned)blocks), dim3(threads == 64 ? kBlock : (unsigned)threads), s, a);
     }
     return launch(RFI_PICK(k_i16_generic, a, grid), a, grid, s);
 }

@@ -242,6 +242,16 @@ hipError_t launch_mom_apply(const LaunchArgs& a, const MomItem* items, int64_t n
 // Copies n16 16-byte units from pinned host memory to device memory.
 hipError_t launch_stage(void* dst, const void* src_host, int64_t n16, hipStream_t s);
 
+// Launches k and returns this launch's own status (hipGetLastError would also
+// report an error that the program left before).
+template <class T> struct SameType { using type = T; };
+template <class... P>
+hipError_t launch_kernel(void (*k)(P...), dim3 grid, dim3 block, hipStream_t s, typename SameType<P>::type... args)
+{
+    void* kargs[] = {const_cast<void*>(static_cast<const volatile void*>(&args))...};
+    return hipLaunchKernel(reinterpret_cast<const void*>(k), grid, block, kargs, 0, s);
+}
+
 // Occupancy cap for the launches issued by this thread (0: none).
 void set_wg_per_cu(int n);
 int wg_per_cu();

@@ -1824,8 +1824,7 @@ hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream
         const int64_t per = kBlock / nt;
         const int64_t blocks = (a.n_items + per - 1) / per;
         if (blocks > (1 << 30)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
-        return hipGetLastError();
+        return launch_kernel(k, dim3((unsigned)blocks), dim3(kBlock), s, a);
     }
     void (*k)(LaunchArgs) = (modes & 4) ? (persist ? k_i8_generic<true, true> : k_i8_generic<false, true>)
                                         : (persist ? k_i8_generic<true, false> : k_i8_generic<false, false>);
@@ -1893,9 +1892,7 @@ hipError_t launch_mom_select(const MomStream* streams, const MomSeg* segs, int64
 {
     if (n_segs <= 0) return hipSuccess;
     if (n_segs > (1 << 30)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mom_select, dim3((unsigned)n_segs), dim3(64), 0, s, streams, segs, mom_k, mad, hist,
-                       hist_len, dm);
-    return hipGetLastError();
+    return launch_kernel(k_mom_select, dim3((unsigned)n_segs), dim3(64), s, streams, segs, mom_k, mad, hist, hist_len, dm);
 }
 
 hipError_t launch_mom_apply(const LaunchArgs& a, const MomItem* items, int64_t n_items, const int32_t* dm,
@@ -1904,16 +1901,14 @@ hipError_t launch_mom_apply(const LaunchArgs& a, const MomItem* items, int64_t n
 {
     if (n_items + h.n_hist <= 0) return hipSuccess;
     if (n_items > (1 << 30)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mom_apply, dim3((unsigned)(n_items + h.n_hist)), dim3(kBlock), 0, s, a, items, dm,
-                       stream_woff, abs_add, stats, h);
-    return hipGetLastError();
+    return launch_kernel(k_mom_apply, dim3((unsigned)(n_items + h.n_hist)), dim3(kBlock), s, a, items, dm, stream_woff,
+                         abs_add, stats, h);
 }
 
 hipError_t launch_stage(void* dst, const void* src_host, int64_t n16, hipStream_t s)
 {
     if (n16 <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_stage, dim3((unsigned)((n16 + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, dst, src_host, n16);
-    return hipGetLastError();
+    return launch_kernel(k_stage, dim3((unsigned)((n16 + kBlock - 1) / kBlock)), dim3(kBlock), s, dst, src_host, n16);
 }
 
 // Every instance that a batch may take (one mode, or mixed): a kernel's first

@@ -233,8 +233,7 @@ extern "C" int rfi_mad_filter_noalloc(const int8_t* x, int8_t* y, int32_t n_stre
             woff += (lengths[s] + windows[s] - 1) / windows[s];
         }
         const unsigned gx = (unsigned)std::min<int64_t>((most + 255) / 256, 256);
-        hipLaunchKernelGGL(k_noalloc_tables, dim3(gx, (unsigned)a.n), dim3(256), 0, hs, a);
-        hipError_t e = hipGetLastError();
+        hipError_t e = launch_kernel(k_noalloc_tables, dim3(gx, (unsigned)a.n), dim3(256), hs, a);
         if (e != hipSuccess) return hip_fail(e);
     }
 

@@ -29,6 +29,7 @@
 #include <vector>
 
 #include "rfi_device.hpp"
+#include "rfi_internal.hpp"
 #include "rfi_mad.h"
 #include "rfi_runtime.hpp"
 
@@ -389,18 +390,13 @@ int rfi_block_power(const void* x, int32_t elem_bytes, int32_t n_streams, const 
     hipStream_t s = (hipStream_t)stream;
     const int direct = p->ppb == 1 ? 1 : 0;
     const uint8_t* xb8 = static_cast<const uint8_t*>(x);
-    if (elem_bytes == 1)
-        hipLaunchKernelGGL(k_block_power<1>, dim3((unsigned)p->n_parts), dim3(kPowBlock), 0, s, xb8, p->d_rows,
-                           p->n_rows, (int64_t)block, p->ppb, p->d_parts, power_out, direct);
-    else
-        hipLaunchKernelGGL(k_block_power<2>, dim3((unsigned)p->n_parts), dim3(kPowBlock), 0, s, xb8, p->d_rows,
-                           p->n_rows, (int64_t)block, p->ppb, p->d_parts, power_out, direct);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_kernel(elem_bytes == 1 ? k_block_power<1> : k_block_power<2>, dim3((unsigned)p->n_parts),
+                                 dim3(kPowBlock), s, xb8, p->d_rows, p->n_rows, (int64_t)block, p->ppb, p->d_parts,
+                                 power_out, direct);
     if (e == hipSuccess && !direct) {
         const int64_t grid = (p->n_blocks + kPowBlock - 1) / kPowBlock;
-        hipLaunchKernelGGL(k_block_power_sum, dim3((unsigned)grid), dim3(kPowBlock), 0, s, p->d_rows, p->n_rows,
-                           (int64_t)block, p->ppb, p->n_blocks, p->d_parts, power_out, (int)elem_bytes);
-        e = hipGetLastError();
+        e = launch_kernel(k_block_power_sum, dim3((unsigned)grid), dim3(kPowBlock), s, p->d_rows, p->n_rows,
+                          (int64_t)block, p->ppb, p->n_blocks, p->d_parts, power_out, (int)elem_bytes);
     }
     return e == hipSuccess ? RFI_OK : hip_fail(e);
 }
@@ -429,9 +425,8 @@ int rfi_improvement(const int64_t* power_u, const int64_t* power_f, int32_t n_st
     PowPlan* p = nullptr;
     int rc = pow_plan(0, n_streams, lengths, block, (hipStream_t)stream, &p);
     if (rc != RFI_OK) return rc;
-    hipLaunchKernelGGL(k_improvement, dim3((unsigned)n_streams), dim3(kPowBlock), 0, (hipStream_t)stream,
-                       p->d_rows, (int64_t)block, seg_blocks, power_u, power_f, out);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_kernel(k_improvement, dim3((unsigned)n_streams), dim3(kPowBlock), (hipStream_t)stream,
+                                 p->d_rows, (int64_t)block, seg_blocks, power_u, power_f, out);
     return e == hipSuccess ? RFI_OK : hip_fail(e);
 }
 
