@@ -1135,6 +1135,7 @@ __device__ __noinline__ void i8_generic_item(const StreamDesc* sd, uint64_t x_ba
     la.y_base = y_base;
     la.stats_base = stats_base;
     la.no_stats = no_stats;
+    la.mad_base = 0;
     const StreamView d = resolve(*sd, la);
     i8_generic<REG>(d, w, seed, sm);
 }
