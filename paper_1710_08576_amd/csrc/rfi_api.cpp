@@ -265,8 +265,8 @@ struct PlanLaunch {
     int modes;  // bit m: some stream of the launch uses mode m
     int64_t first, count;
     int grid;
-    // generic: threads per window if every window fits them (int8: 64 / 128,
-    // at most 256 / 512 chunks; int16: i16_window_threads), else 0
+    // generic: threads per window if every window fits them (int8:
+    // kShortWindows or i8_window_threads; int16: i16_window_threads), else 0
     int small = 0;
 };
 
@@ -289,6 +289,7 @@ struct rfi_plan {
     std::vector<int32_t> W;
     std::vector<float> K;
     std::vector<int32_t> M;
+    bool noise = false;  // some stream is in noise mode
     std::vector<StreamDesc> hdesc;
     std::vector<Item> hitems;
     // the same items twice: mode-major (fused launches), then from
@@ -440,10 +441,25 @@ static void build_launches(rfi_plan* p)
                 e = b;
                 modes = 0;
                 while (e < gend[g] && nt(e) == threads) modes |= 1 << p->M[p->hitems[e++].stream];
+            } else {
+                // short windows come first: a launch of their own, if they
+                // are many or all
+                auto is_short = [&](int64_t i) {
+                    const int s = p->hitems[i].stream;
+                    return i8_short_windows(p->W[s], p->L[s], p->noise);
+                };
+                int64_t m = b;
+                while (m < gend[g] && is_short(m)) ++m;
+                if (m == gend[g] || m - b >= kShortLaunch) {
+                    e = m;
+                    threads = kShortWindows;
+                }
+                modes = 0;
+                for (int64_t i = b; i < e; ++i) modes |= 1 << p->M[p->hitems[i].stream];
             }
             PlanLaunch l{g == 0 ? 1 : 0, 0, cls, modes, b, e - b, clamp_grid(e - b)};
             l.small = threads;
-            if (g == 0 && elem == 1) {
+            if (g == 0 && elem == 1 && threads == 0) {
                 // longest window of the launch
                 int64_t nmax = 0;
                 for (int64_t i = b; i < e; ++i) {
@@ -451,7 +467,7 @@ static void build_launches(rfi_plan* p)
                     const int64_t w = p->W[it.stream];
                     nmax = std::max<int64_t>(nmax, std::min<int64_t>(w, p->L[it.stream] - it.first * w));
                 }
-                l.small = i8_window_threads(nmax);
+                l.small = i8_window_threads(nmax, e - b);
             }
             p->launches[RFI_SCHED_SPLIT].push_back(l);
             l.grid = (int)std::min<int64_t>(e - b, persistent_grid(elem, cls, l.modes, false));
@@ -568,6 +584,7 @@ int plan_build(int elem, int32_t n, const int64_t* L, const int32_t* W, const fl
     p->W.assign(W, W + n);
     p->K.assign(K, K + n);
     p->M.assign(M, M + n);
+    p->noise = std::find(M, M + n, (int32_t)RFI_MODE_NOISE) != M + n;
     if (hipGetDevice(&p->device) != hipSuccess) p->device = 0;
     const int64_t tile_samples = kTileBytes / elem;
     const int ncls = elem == 1 ? kI8Classes : kI16Classes;
@@ -612,6 +629,10 @@ int plan_build(int elem, int32_t n, const int64_t* L, const int32_t* W, const fl
     if (elem == 2)  // one run of generic items per int16 window size class
         std::stable_sort(groups[0].begin(), groups[0].end(), [&](const Item& a, const Item& b) {
             return i16_window_threads(W[a.stream], L[a.stream]) < i16_window_threads(W[b.stream], L[b.stream]);
+        });
+    if (elem == 1)
+        std::stable_partition(groups[0].begin(), groups[0].end(), [&](const Item& it) {
+            return i8_short_windows(W[it.stream], L[it.stream], p->noise);
         });
     for (auto& g : groups) p->hitems.insert(p->hitems.end(), g.begin(), g.end());
     for (int m = 0; m < 3; ++m) {  // the statistics-only mode has no fused launch

@@ -152,19 +152,44 @@ __host__ __device__ inline StreamView resolve(const StreamDesc& d, const LaunchA
 // fused: one kernel for all kinds.
 hipError_t launch_i8_tiles(int cls, int modes, int tpw, const LaunchArgs& a, int grid, hipStream_t s);
 // modes: bit m set if some window of the launch uses mode m.
-// small_nt: i8_window_threads of the longest window of the launch, if its
-// streams are padded and start at absolute index 0, used when the grid covers
-// every item; 0: windows of any kind, 256 threads each.
-// i8_window_threads: the fewest threads for windows of up to n samples: four
-// 16-byte chunks per thread, or eight (kWideThreads), which one wave holds
-// without exchanging counts with another; n + 30 <= 16 * chunks * threads
-// keeps a window within them at any alignment.
+// small_nt: kShortWindows if every stream of the launch has short windows,
+// else i8_window_threads of its longest window, if its streams are padded and
+// start at absolute index 0, used when the grid covers every item; 0: windows
+// of any kind, 256 threads each.
+// i8_window_threads: threads per window for `count` windows of up to n
+// samples: four 16-byte chunks per thread, or eight (kWideThreads), which
+// need fewer waves per window; n + 30 <= 16 * chunks * threads keeps a window
+// within them at any alignment.  A launch of few windows leaves the device
+// idle and takes as long as one window, so it gives each more threads (60
+// streams, noise, microseconds, 256 threads against the fewest: 60 windows of
+// 3000 samples 6.8 / 8.3, 480 of 4067 7.2 / 10.0; 128 threads of four chunks
+// against 64 of eight, 960 of 6000 8.7 / 10.3, 3840 16.8 / 17.8, 15360 45.1 /
+// 42.8), and so does one whose chunks nearly fill them (16354 samples, clip,
+// 15360 windows, 256 threads of four against 128 of eight 88 / 101; 12000
+// samples, noise, 79 / 75).  no_scratch: only kernels without private memory
+// (eight chunks of 64 or 128 threads spill in noise mode).
 constexpr int kWideThreads = 1;
-inline int i8_window_threads(int64_t n)
+constexpr int kShortWindows = 2;
+inline int i8_window_threads(int64_t n, int64_t count, bool no_scratch = false)
 {
-    return n <= 4066 ? 64 : n <= 8162 ? 64 | kWideThreads : n <= 16354 ? 128 | kWideThreads
-           : n <= 32738 ? 256 | kWideThreads : 0;
+    if (n > 32738) return 0;
+    if (n > 16354) return 256 | kWideThreads;
+    if (count <= 512) return 256;
+    if (n <= 4066) return 64;
+    const bool few = count <= 4096 || no_scratch;
+    if (n <= 8162) return few ? 128 : 64 | kWideThreads;
+    return few || n > 14000 ? 256 : 128 | kWideThreads;
 }
+// Whether a stream's windows are short: counting them into one plain
+// histogram by one wave, sample by sample, beats holding 16-byte chunks in
+// registers and four replicas of the histogram, which cost the same for any
+// length (61440 windows, noise, W 1 26 / 63 us, 100 40 / 63, 200 56 / 64, 300 69
+// / 65; clip, W 100 31 / 36, 150 36 / 38, 200 40 / 37).  noise: some stream of
+// the batch is in noise mode.  In a batch that also has longer windows, short
+// ones take a launch of their own (3 us) if they are this many: below, they
+// cost no more than that in the longer ones' kernel.
+inline bool i8_short_windows(int32_t W, int64_t L, bool noise) { return (L < W ? L : W) <= (noise ? 256 : 160); }
+constexpr int64_t kShortLaunch = 4096;
 hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int small_nt = 0);
 hipError_t launch_i8_fused(int modes, const LaunchArgs& a, int grid, hipStream_t s);
 hipError_t launch_i16_tiles(int cls, int modes, const LaunchArgs& a, int grid, hipStream_t s);

@@ -765,8 +765,8 @@ using GenericSmem = I8WinSmem<kBlock>;
 
 __device__ __forceinline__ uint32_t byte_of(uint32_t v, int b) { return (v >> (8 * b)) & 0xFFu; }
 
-// Whether a window qualifies for i8_window: 16-byte aligned input and
-// output, no head segment (HEAD: or one of whole chunks, as a serving
+// Whether a window qualifies for i8_window in a launch of windows of any kind:
+// not a short one, 16-byte aligned input and output, no head segment (HEAD: or one of whole chunks, as a serving
 // stream's carry whose blocks start and end on 16 samples), at most K chunks
 // per thread.  NOISE: noise windows too, where each dword of the
 // stream holds one Philox block (absolute index of the stream's first
@@ -774,6 +774,7 @@ __device__ __forceinline__ uint32_t byte_of(uint32_t v, int b) { return (v >> (8
 template <bool NOISE, int NT, int K, bool HEAD>
 __device__ __forceinline__ bool i8_window_ok(const StreamView& d, int64_t a, int n)
 {
+    if (n < 512) return false;
     if (d.head_len != 0 && (!HEAD || ((d.head_len | (uint32_t)(uintptr_t)d.x_head) & 15u) != 0)) return false;
     if (d.mode == RFI_MODE_NOISE && (!NOISE || (d.abs_base & 3) != 0)) return false;
     if (((uintptr_t)d.x | (uintptr_t)d.y) & 15u) return false;
@@ -971,21 +972,22 @@ __device__ __forceinline__ void i8_window(const StreamView& d, int64_t w, int64_
     }
 }
 
-// A generic window in a workgroup of kBlock threads: in registers if it
+// A generic window in a workgroup of NT threads: in registers if it
 // qualifies, else by two passes over the samples in global memory.
 // REG: zero/clip windows may stay in registers; REG_NOISE: noise windows too
 // (kept out of the fused kernels, whose register budget the inlined draw
 // would raise).
-template <bool REG = true, bool REG_NOISE = false>
-__device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, GenericSmem& sm)
+template <bool REG = true, bool REG_NOISE = false, int NT = kBlock, class Smem = GenericSmem>
+__device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, Smem& sm)
 {
-    constexpr int NT = kBlock;
     const int W = d.window;
     const int64_t a = w * (int64_t)W;
     const int n = (int)min((int64_t)W, d.length - a);
-    if (REG && i8_window_ok<REG_NOISE, NT, 4, true>(d, a, n)) {
-        i8_window<NT, 4, REG_NOISE ? 15 : 11, true>(d, w, a, n, seed, 0, (int)threadIdx.x, sm);
-        return;
+    if constexpr (REG) {
+        if (i8_window_ok<REG_NOISE, NT, 4, true>(d, a, n)) {
+            i8_window<NT, 4, REG_NOISE ? 15 : 11, true>(d, w, a, n, seed, 0, (int)threadIdx.x, sm);
+            return;
+        }
     }
     const int tid = (int)threadIdx.x;
     int8_t* y = static_cast<int8_t*>(d.y);
@@ -1071,7 +1073,8 @@ __global__ __launch_bounds__(kBlock) void k_i8_tiles(LaunchArgs a)
 // there on.  K = 8 (windows of more than 4066 samples): half the waves per
 // window, so half its fixed work, and one wave up to 8162.  60 x 2^22 samples,
 // zero / clip / noise, against one window per workgroup of 64, 128 or 256
-// threads with the edge chunks counted and stored byte by byte: W 1000 210 /
+// threads with the edge chunks counted and stored byte by byte, in batches
+// that fill the device (i8_window_threads has the others): W 1000 210 /
 // 203 / 342 -> 172 / 167 / 273 us, 3000 121 / 114 / 176 -> 107 / 101 / 133,
 // 5000 119 / 112 / 160 -> 100 / 95 / 122 (K = 4: 110 / 105 / 146), 9000 117 /
 // 109 / 163 -> 100 / 96 / 127, 12000 94 / 90 / 126 -> 93 / 90 / 106.  Noise
@@ -1091,6 +1094,20 @@ __global__ __launch_bounds__(kBlock, K == 8 && (MODES & 4) ? 7 : 8) void k_i8_wi
     const int64_t first = item.first * (int64_t)d.window;
     const int n = has ? (int)min((int64_t)d.window, d.length - first) : 0;
     i8_window<NT, K, MODES, false>(d, item.first, first, n, a.seed, sub, (int)threadIdx.x & (NT - 1), sm);
+}
+
+// Short windows (i8_short_windows) of any kind of stream, one wave each.
+struct I8ShortSmem {
+    __align__(16) uint32_t hist[256];
+    WinParams prm[1];
+};
+__global__ __launch_bounds__(64) void k_i8_short(LaunchArgs a)
+{
+    __shared__ I8ShortSmem sm;
+    if ((int64_t)blockIdx.x >= a.n_items) return;
+    const Item item = a.items[blockIdx.x];
+    const StreamView d = resolve(a.streams[item.stream], a);
+    i8_generic<false, false, 64>(d, item.first, a.seed, sm);
 }
 
 // NOISE: noise windows may take the register path (launched only for items
@@ -1815,10 +1832,13 @@ hipError_t launch_i8_generic(const LaunchArgs& a, int modes, int grid, hipStream
 {
     const bool persist = grid < a.n_items;
     if (small_nt != 0 && !persist && a.n_items > 0) {
+        if (small_nt == kShortWindows) return launch_kernel(k_i8_short, dim3((unsigned)a.n_items), dim3(64), s, a);
         const int nt = small_nt & ~kWideThreads;
         void (*k)(LaunchArgs) = small_nt == 64                   ? i8_window_kernel<64, 4>(modes)
                                 : small_nt == (64 | kWideThreads)  ? i8_window_kernel<64, 8>(modes)
+                                : small_nt == 128                  ? i8_window_kernel<128, 4>(modes)
                                 : small_nt == (128 | kWideThreads) ? i8_window_kernel<128, 8>(modes)
+                                : small_nt == 256                  ? i8_window_kernel<256, 4>(modes)
                                 : small_nt == (256 | kWideThreads) ? i8_window_kernel<256, 8>(modes)
                                                                    : nullptr;
         if (!k) return hipErrorInvalidValue;

@@ -52,8 +52,13 @@ struct MultiPlan {
     StreamDesc* d_desc[3] = {nullptr, nullptr, nullptr};
     Item* d_items = nullptr;
     std::vector<int64_t> cls_begin, cls_count;  // tile items per class, then generic
-    int64_t gen_begin = 0, gen_count = 0;
-    int gen_threads = 0;  // i8_window_threads of the longest generic window
+    // generic items: those of short windows (a launch of their own if they
+    // are many or all), then the others
+    struct GenericRun {
+        int64_t begin, count;
+        int threads;  // launch_i8_generic's small_nt
+    };
+    std::vector<GenericRun> gen;
     int device = 0;  // the plan's buffers and kernels live here
 };
 
@@ -79,7 +84,8 @@ int multi_build(int32_t n_out, int32_t n, const int64_t* L, const int32_t* W, co
     p->seed = seed;
     std::vector<std::vector<Item>> groups(kI8Classes + 1);
     std::vector<std::vector<StreamDesc>> desc(n_out, std::vector<StreamDesc>(n));
-    int64_t soff = 0, woff = 0, gen_longest = 0;
+    std::vector<Item> short_items;
+    int64_t soff = 0, woff = 0, gen_longest = 0, short_longest = 0;
     for (int s = 0; s < n; ++s) {
         for (int o = 0; o < n_out; ++o) {
             StreamDesc& d = desc[o][s];
@@ -102,9 +108,11 @@ int multi_build(int32_t n_out, int32_t n, const int64_t* L, const int32_t* W, co
             for (int64_t t = 0; t < nt; ++t) groups[cls + 1].push_back(Item{s, kItemTile, t * kTileBytes});
             first_generic = nt * (kTileBytes / W[s]);
         }
-        for (int64_t w = first_generic; w < nw; ++w) groups[0].push_back(Item{s, kItemGeneric, w});
-        if (first_generic < nw)
-            gen_longest = std::max(gen_longest, std::min<int64_t>(W[s], L[s] - first_generic * W[s]));
+        const bool sh = i8_short_windows(W[s], L[s], false);  // no output here is noise
+        for (int64_t w = first_generic; w < nw; ++w)
+            (sh ? short_items : groups[0]).push_back(Item{s, kItemGeneric, w});
+        int64_t& longest = sh ? short_longest : gen_longest;
+        if (first_generic < nw) longest = std::max(longest, std::min<int64_t>(W[s], L[s] - first_generic * W[s]));
         soff += align64(L[s]);
         woff += nw;
     }
@@ -116,10 +124,19 @@ int multi_build(int32_t n_out, int32_t n, const int64_t* L, const int32_t* W, co
         p->cls_count[c] = (int64_t)groups[c + 1].size();
         items.insert(items.end(), groups[c + 1].begin(), groups[c + 1].end());
     }
-    p->gen_begin = (int64_t)items.size();
-    p->gen_count = (int64_t)groups[0].size();
-    p->gen_threads = i8_window_threads(gen_longest);
-    items.insert(items.end(), groups[0].begin(), groups[0].end());
+    if ((int64_t)short_items.size() >= kShortLaunch || groups[0].empty()) {
+        if (!short_items.empty())
+            p->gen.push_back({(int64_t)items.size(), (int64_t)short_items.size(), kShortWindows});
+        items.insert(items.end(), short_items.begin(), short_items.end());
+    } else {
+        groups[0].insert(groups[0].end(), short_items.begin(), short_items.end());
+        gen_longest = std::max(gen_longest, short_longest);
+    }
+    if (!groups[0].empty()) {
+        const int64_t c = (int64_t)groups[0].size();
+        p->gen.push_back({(int64_t)items.size(), c, i8_window_threads(gen_longest, c)});
+        items.insert(items.end(), groups[0].begin(), groups[0].end());
+    }
     hipError_t e = hipSuccess;
     for (int o = 0; o < n_out && e == hipSuccess; ++o) {
         e = hipMalloc(&p->d_desc[o], sizeof(StreamDesc) * n);
@@ -163,12 +180,14 @@ int multi_execute(MultiPlan* p, const void* x, int8_t* const* y, rfi_window_stat
         hipError_t e = launch_i8_multi(c, mc, (int)mc.a.n_items, s);
         if (e != hipSuccess) return hip_fail(e);
     }
-    for (int o = 0; o < p->n_out && p->gen_count > 0; ++o) {
+    for (int i = 0; i < p->n_out * (int)p->gen.size(); ++i) {
+        const int o = i / (int)p->gen.size();
+        const MultiPlan::GenericRun& run = p->gen[i % p->gen.size()];
         LaunchArgs a;
         std::memset(&a, 0, sizeof(a));
         a.streams = p->d_desc[o];
-        a.items = p->d_items + p->gen_begin;
-        a.n_items = p->gen_count;
+        a.items = p->d_items + run.begin;
+        a.n_items = run.count;
         a.seed = p->seed;
         a.x_base = (uint64_t)(uintptr_t)x;
         a.y_base = (uint64_t)(uintptr_t)y[o];
@@ -176,7 +195,7 @@ int multi_execute(MultiPlan* p, const void* x, int8_t* const* y, rfi_window_stat
         a.no_stats = ma.stats_base[o] == 0 ? 1 : 0;
         if (a.n_items > (1 << 30)) return RFI_ERR_INVALID;
         // outputs with noise streams are single-output calls of their own
-        hipError_t e = launch_i8_generic(a, 3, (int)a.n_items, s, p->gen_threads);
+        hipError_t e = launch_i8_generic(a, 3, (int)a.n_items, s, run.threads);
         if (e != hipSuccess) return hip_fail(e);
     }
     return RFI_OK;

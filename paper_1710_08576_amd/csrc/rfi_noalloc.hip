@@ -127,9 +127,10 @@ int na_scratch(uint8_t** out)
     return RFI_OK;
 }
 
-// Item groups in the order of the split schedule: generic items, then the
-// tiles of window class c and mode m at 1 + 3 c + m.
-constexpr int kNaGroups = 1 + kI8Classes * 3;
+// Item groups: generic items, the tiles of window class c and mode m at
+// 1 + 3 c + m, and the short windows' items if they have a launch of their own.
+constexpr int kNaShort = 1 + kI8Classes * 3;
+constexpr int kNaGroups = kNaShort + 1;
 constexpr int64_t kNaTileSamples = kTileBytes;  // int8
 
 // Per stream: tiles, first generic window and generic items (as plan_build).
@@ -167,20 +168,30 @@ extern "C" int rfi_mad_filter_noalloc(const int8_t* x, int8_t* y, int32_t n_stre
     if (n_streams > kNaMaxStreams) return RFI_ERR_UNSUPPORTED;
 
     // Pass 1: items per group, the modes of the generic items and the
-    // longest generic window (which picks the generic kernel's workgroup).
+    // longest generic window (which picks the generic kernel's workgroup),
+    // short windows apart.
+    const bool noise = std::find(mode, mode + n_streams, (int32_t)RFI_MODE_NOISE) != mode + n_streams;
     int64_t count[kNaGroups] = {};
-    int gen_modes = 0;
-    int64_t gen_nmax = 0;
+    int modes_of[2] = {0, 0};
+    int64_t nmax_of[2] = {0, 0};
     for (int32_t s = 0; s < n_streams; ++s) {
         int64_t nt, fg, ng;
         int cls;
         na_counts(lengths[s], windows[s], nt, fg, ng, cls);
         if (nt > 0) count[1 + 3 * cls + mode[s]] += nt;
         if (ng > 0) {
-            count[0] += ng;
-            gen_modes |= 1 << mode[s];
-            gen_nmax = std::max<int64_t>(gen_nmax, std::min<int64_t>(windows[s], lengths[s] - fg * windows[s]));
+            const bool sh = i8_short_windows(windows[s], lengths[s], noise);
+            count[sh ? kNaShort : 0] += ng;
+            modes_of[sh] |= 1 << mode[s];
+            nmax_of[sh] = std::max<int64_t>(nmax_of[sh], std::min<int64_t>(windows[s], lengths[s] - fg * windows[s]));
         }
+    }
+    const bool apart = count[0] == 0 || count[kNaShort] >= kShortLaunch;
+    if (!apart) {  // too few: with the others
+        count[0] += count[kNaShort];
+        count[kNaShort] = 0;
+        modes_of[0] |= modes_of[1];
+        nmax_of[0] = std::max(nmax_of[0], nmax_of[1]);
     }
     int64_t begin[kNaGroups], n_items = 0;
     for (int g = 0; g < kNaGroups; ++g) {
@@ -226,8 +237,9 @@ extern "C" int rfi_mad_filter_noalloc(const int8_t* x, int8_t* y, int32_t n_stre
                 q.tile_pos = c;
                 c += q.n_tiles;
             }
-            q.gen_pos = cursor[0];
-            cursor[0] += q.n_generic;
+            int64_t& gen = cursor[apart && i8_short_windows(windows[s], lengths[s], noise) ? kNaShort : 0];
+            q.gen_pos = gen;
+            gen += q.n_generic;
             most = std::max(most, std::max(q.n_tiles, q.n_generic));
             soff += (lengths[s] + 63) / 64 * 64;
             woff += (lengths[s] + windows[s] - 1) / windows[s];
@@ -252,9 +264,10 @@ extern "C" int rfi_mad_filter_noalloc(const int8_t* x, int8_t* y, int32_t n_stre
         la.n_items = count[g];
         const int grid = (int)std::min<int64_t>(count[g], (int64_t)1 << 30);
         hipError_t e;
-        if (g == 0) {
-            const int small = i8_window_threads(gen_nmax);
-            e = launch_i8_generic(la, gen_modes, grid, hs, small);
+        if (g == 0 || g == kNaShort) {
+            const int i = g == 0 ? 0 : 1;
+            const int small = i ? kShortWindows : i8_window_threads(nmax_of[i], count[g], true);
+            e = launch_i8_generic(la, modes_of[i], grid, hs, small);
         } else {
             const int cls = (g - 1) / 3, m = (g - 1) % 3;
             e = launch_i8_tiles(cls, 1 << m, 1, la, grid, hs);
