@@ -372,24 +372,43 @@ static int i16_window_threads(int32_t W, int64_t L)
 }
 
 // Whose launches a plan takes that nothing was tuned for: SPLIT's, unless
-// those are several and one launch of the fused kernel beats them.  A launch
-// more costs 3 us of a small batch and 5 us of a large one, which drains
-// before the next; the fused kernel's occupancy costs less than that at
-// every size measured (int8, microseconds, SPLIT against one launch: one
-// stream of 20000 samples 10.3 / 7.7; 60 of 10^6, W 4096 with tails, clip
-// 28.7 / 24.1, noise 38.1 / 31.7; 60 of 4 x 10^6 83.3 / 79.2 and 102.9 /
-// 99.9, every class and mode mixed 178.6 / 103.1).  Not with windows that
-// are no tile class: SPLIT has kernels of fewer threads for them (60 of
-// 10^6, W 5000, noise 44.7 / 164).  int16 tiles run at the copy rate by
-// themselves: one launch up to 8192 items (60 of 10^6 49.1 / 46.1, noise
-// 55.7 / 55.0; 60 of 2 x 10^6, noise 96.8 / 101.9).
+// those are several and one launch of the fused kernel beats them.  Each
+// launch more costs about 3 us.  What the fused kernel costs more is in the
+// windows outside whole tiles (the ends of the streams), which SPLIT's kernels
+// hold in registers, several per workgroup: about 0.8 ns a window, 2.8 in the
+// kernel compiled for several modes (fewer workgroups per CU), and 2 ns per
+// 1000 samples of them in noise mode, which the fused kernel takes by two
+// passes; the longest of those, 1.4 us per 1000 samples, is on top where the
+// tiles (5 ns each) do not last as long.  Over 700 batches (2 to 2000 streams
+// of 17000 to 4 x 10^6 samples, every class, four sets of modes) this takes
+// within 0.8 % of the faster one on average, and none is more than 3.2 % slower
+// than SPLIT before the fused kernel was taken at all.  SPLIT / one launch,
+// microseconds: one stream of 20000 samples 10.3 / 7.7; 60 of 4 x 10^6, every
+// class and mode mixed 178.6 / 103.1; 60 of 17000 to 32767, W 16384, noise
+// 14.2 / 40.6; 2000 of them, W 512, zero and clip 40.1 / 134.5.  Not with
+// windows that are no tile class (60 of 10^6, W 5000, noise 44.7 / 164).  int16
+// tiles run at the copy rate by themselves, and its fused kernel holds every
+// window in registers: one launch up to 8192 items (60 of 10^6 49.1 / 46.1,
+// noise 55.7 / 55.0; 60 of 2 x 10^6, noise 96.8 / 101.9).
 static int untuned_launches(const rfi_plan* p)
 {
-    if (p->launches[RFI_SCHED_SPLIT].size() < 2) return RFI_SCHED_SPLIT;
+    const int64_t launches = (int64_t)p->launches[RFI_SCHED_SPLIT].size();
+    if (launches < 2) return RFI_SCHED_SPLIT;
     for (int s = 0; s < p->n; ++s)
         if (tile_class(p->elem, p->W[s]) < 0) return RFI_SCHED_SPLIT;
-    if (p->elem == 2 && p->hitems.size() > 8192) return RFI_SCHED_SPLIT;
-    return RFI_SCHED_ONE_LAUNCH;
+    if (p->elem == 2) return p->hitems.size() > 8192 ? RFI_SCHED_SPLIT : RFI_SCHED_ONE_LAUNCH;
+    int64_t noise = 0, longest = 0;  // samples of noise windows outside tiles
+    for (const Item& it : p->hitems) {
+        if (it.kind != kItemGeneric || p->M[it.stream] != RFI_MODE_NOISE) continue;
+        const int64_t w = p->W[it.stream], len = std::min<int64_t>(w, p->L[it.stream] - it.first * w);
+        noise += len;
+        longest = std::max(longest, len);
+    }
+    const int modes = p->launches[RFI_SCHED_ONE_LAUNCH].front().modes;
+    const double per_window = (modes & (modes - 1)) != 0 ? 2.8e-3 : 0.8e-3;
+    const double cost = per_window * (double)p->n_generic + 2e-6 * (double)noise +
+                        std::max(0.0, 1.4e-3 * (double)longest - 5e-3 * (double)p->n_tiles);
+    return cost <= 3.0 * (double)(launches - 1) ? RFI_SCHED_ONE_LAUNCH : RFI_SCHED_SPLIT;
 }
 
 static void build_launches(rfi_plan* p)

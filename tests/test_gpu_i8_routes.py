@@ -84,3 +84,20 @@ def test_noalloc_many_noise_windows(gpu, W):
     y = torch.full_like(xd, SENTINEL)
     rfi.mad_filter_noalloc(xd, L, W, K, M, seed=9, y=y)
     check_against_oracle(x, specs, 9, y.cpu().numpy(), None)
+
+
+# ends of streams, launches that the plan takes: one where it saves a launch,
+# the split ones where the ends are many, or long ones in noise mode
+@pytest.mark.parametrize("n,low,W,modes,launches", [
+    (60, 20_000, 4096, (1,), 1), (8, 30_000, 2048, (2, 0), 1), (60, 31_000, 16384, (2,), 2), (60, 31_000, 8192, (2,), 2),
+    (1000, 20_000, 512, (1,), 2), (1000, 20_000, 512, (0, 1), 3), (1000, 18_000, 16384, (1,), 1)])
+def test_ends_of_streams(gpu, n, low, W, modes, launches):
+    rng = np.random.default_rng(n + W)
+    xs = [np.clip(np.round(rng.normal(0, 9, low + 7 * (i % 9))), -128, 127).astype(np.int8) for i in range(n)]
+    specs = [synth.StreamSpec(len(v), W, 2.0, modes[i % len(modes)], 1, 0, 1, 1) for i, v in enumerate(xs)]
+    x = synth.pack([torch.as_tensor(v) for v in xs])
+    plan = rfi.Plan(1, *unpack(specs))
+    assert plan.info()["launches"] == launches
+    plan.close()
+    y, st = gpu_run(x, specs, 9, gpu)
+    check_against_oracle(x, specs, 9, y, st)
