@@ -393,7 +393,8 @@ static int i16_window_threads(int32_t W, int64_t L)
 static int untuned_launches(const rfi_plan* p)
 {
     const int64_t launches = (int64_t)p->launches[RFI_SCHED_SPLIT].size();
-    if (launches < 2) return RFI_SCHED_SPLIT;
+    // (statistics-only plans have no fused launch)
+    if (launches < 2 || p->launches[RFI_SCHED_ONE_LAUNCH].empty()) return RFI_SCHED_SPLIT;
     for (int s = 0; s < p->n; ++s)
         if (tile_class(p->elem, p->W[s]) < 0) return RFI_SCHED_SPLIT;
     if (p->elem == 2) return p->hitems.size() > 8192 ? RFI_SCHED_SPLIT : RFI_SCHED_ONE_LAUNCH;
