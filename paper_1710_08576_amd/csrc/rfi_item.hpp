@@ -247,8 +247,9 @@ __device__ __forceinline__ int noise_sample(int64_t j, uint64_t seed, uint32_t k
 }
 
 // A carry update by one workgroup.  The usual carry is one run of whole
-// 16-byte units (a block's tail).
-__device__ __forceinline__ void carry_copy(const CarryItem& c)
+// 16-byte units (a block's tail).  The item is taken by value: through a
+// reference its fields are read again after every store.
+__device__ __forceinline__ void carry_copy(CarryItem c)
 {
     const uint64_t bytes = (uint64_t)c.count * (uint64_t)c.elem;
     if (c.from == 0 && c.count <= c.head_len && ((c.head | c.dst | bytes) & 15u) == 0) {
