@@ -137,7 +137,7 @@ struct Lane {
     // hands them out in order, starts its longest items first.
     std::vector<Item> generic;
     std::vector<Item> tiles[2][kI8Classes];
-    std::vector<Item> items;  // all of them, carry updates among them
+    std::vector<Item> carry_items;
     std::vector<CarryItem> carries;
     int modes = 0;            // bit m: some block of the batch has mode m
     std::vector<uint64_t> batch;
@@ -202,19 +202,26 @@ int ensure_slot(Slot& sl, size_t bytes)
     return RFI_OK;
 }
 
-// Stages the tables in the slot and copies them to the device on stream s
-// (one copy); returns the device addresses of the three tables.
-int upload(Slot& sl, const std::vector<StreamDesc>& descs, const std::vector<Item>& items,
-           const std::vector<CarryItem>& carries, hipStream_t s, StreamDesc** dd, Item** di,
-           CarryItem** dc)
+// Stages the tables in the slot (the item lists one after another) and copies
+// them to the device on stream s (one copy); returns the device addresses of
+// the three tables and the number of items.
+int upload(Slot& sl, const std::vector<StreamDesc>& descs, const std::vector<const std::vector<Item>*>& items,
+           const std::vector<CarryItem>& carries, hipStream_t s, StreamDesc** dd, Item** di, CarryItem** dc,
+           int64_t* n_items)
 {
-    const size_t bd = descs.size() * sizeof(StreamDesc), bi = items.size() * sizeof(Item),
-                 bc = carries.size() * sizeof(CarryItem);
+    size_t n = 0;
+    for (const auto* v : items) n += v->size();
+    *n_items = (int64_t)n;
+    const size_t bd = descs.size() * sizeof(StreamDesc), bi = n * sizeof(Item), bc = carries.size() * sizeof(CarryItem);
     const size_t oi = align256(bd), oc = oi + align256(bi), total = oc + align256(bc);
     int rc = ensure_slot(sl, total);
     if (rc != RFI_OK) return rc;
     if (bd) std::memcpy(sl.h_stage, descs.data(), bd);
-    if (bi) std::memcpy(sl.h_stage + oi, items.data(), bi);
+    char* at = sl.h_stage + oi;
+    for (const auto* v : items) {
+        if (!v->empty()) std::memcpy(at, v->data(), v->size() * sizeof(Item));
+        at += v->size() * sizeof(Item);
+    }
     if (bc) std::memcpy(sl.h_stage + oc, carries.data(), bc);
     if (total) {
         hipError_t e = launch_stage(sl.d_buf, sl.h_stage, (int64_t)(total / 16), s);
@@ -351,7 +358,7 @@ int dispatch_lane(rfi_server* srv, int li)
     if (si < 0 || L.members.empty()) return RFI_OK;
     if (srv->fault != hipSuccess) return hip_fail(srv->fault);
     L.descs.clear();
-    L.items.clear();
+    L.carry_items.clear();
     L.generic.clear();
     for (auto& m : L.tiles)
         for (auto& v : m) v.clear();
@@ -391,17 +398,18 @@ int dispatch_lane(rfi_server* srv, int li)
     L.rr = (L.rr + 1) % nm;
     // A carry update reads what no item of the batch writes (input blocks and
     // the stream's other carry buffer), so it is an item like the others.
-    L.items.insert(L.items.end(), L.generic.begin(), L.generic.end());
-    for (size_t i = 0; i < L.carries.size(); ++i) L.items.push_back(Item{(int32_t)i, kItemCarry, 0});
+    for (size_t i = 0; i < L.carries.size(); ++i) L.carry_items.push_back(Item{(int32_t)i, kItemCarry, 0});
+    std::vector<const std::vector<Item>*> items{&L.generic, &L.carry_items};
     for (auto& m : L.tiles)
-        for (auto& v : m) L.items.insert(L.items.end(), v.begin(), v.end());
+        for (auto& v : m) items.push_back(&v);
     Slot& sl = L.slots[si];
     StreamDesc* dd = nullptr;
     Item* di = nullptr;
     CarryItem* dc = nullptr;
+    int64_t n_items = 0;
     int rc = RFI_OK;
     if (++srv->uploads >= srv->fail_from && srv->uploads < srv->fail_from + srv->fail_count) rc = RFI_ERR_NOMEM;
-    if (rc == RFI_OK) rc = upload(sl, L.descs, L.items, L.carries, L.s, &dd, &di, &dc);
+    if (rc == RFI_OK) rc = upload(sl, L.descs, items, L.carries, L.s, &dd, &di, &dc, &n_items);
     if (rc != RFI_OK) {
         // Nothing of this batch reached the device: undo it.
         for (int j = 0; j < nm; ++j) {
@@ -420,14 +428,13 @@ int dispatch_lane(rfi_server* srv, int li)
         return rc;
     }
     hipError_t e = hipSuccess;
-    const std::vector<Item>& items = L.items;
-    if (!items.empty()) {
+    if (n_items > 0) {
         LaunchArgs a;
         std::memset(&a, 0, sizeof(a));
         a.streams = dd;
         a.items = di;
         a.carries = dc;
-        a.n_items = (int64_t)items.size();
+        a.n_items = n_items;
         a.seed = srv->cfg.seed;
         set_wg_per_cu(0);
         int64_t grid = a.n_items;
@@ -726,14 +733,15 @@ int rfi_server_flush(rfi_server* srv, uint32_t stream_id, void* out_dev, rfi_win
     StreamDesc* dd = nullptr;
     Item* di = nullptr;
     CarryItem* dc = nullptr;
-    rc = upload(L.slots[0], std::vector<StreamDesc>{d}, std::vector<Item>{Item{0, kItemGeneric, 0}},
-                std::vector<CarryItem>{}, L.s, &dd, &di, &dc);
+    const std::vector<Item> item{Item{0, kItemGeneric, 0}};
+    int64_t n_items = 0;
+    rc = upload(L.slots[0], std::vector<StreamDesc>{d}, {&item}, std::vector<CarryItem>{}, L.s, &dd, &di, &dc, &n_items);
     if (rc != RFI_OK) return rc;
     LaunchArgs a;
     std::memset(&a, 0, sizeof(a));
     a.streams = dd;
     a.items = di;
-    a.n_items = 1;
+    a.n_items = n_items;
     a.seed = srv->cfg.seed;
     set_wg_per_cu(0);
     hipError_t e = srv->cfg.elem_size == 1 ? launch_i8_generic(a, 1 << st.mode, 1, L.s) : launch_i16_generic(a, 1 << st.mode, 1, L.s);
