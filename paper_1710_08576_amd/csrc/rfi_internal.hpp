@@ -199,11 +199,11 @@ hipError_t launch_i16_tiles(int cls, int modes, const LaunchArgs& a, int grid, h
 // every item; 0: 256-thread workgroups for windows of any kind.
 hipError_t launch_i16_generic(const LaunchArgs& a, int modes, int grid, hipStream_t s, int nt = 0);
 hipError_t launch_i16_fused(const LaunchArgs& a, int grid, hipStream_t s);
-// One workgroup of the all-modes fused kernel (int8) or of the int16 fused
-// kernel with no items.  A kernel that needs private (scratch) memory has
-// it set up by the runtime at its first dispatch on a hardware queue, which
-// can hold that queue for milliseconds; a server runs this once per lane
-// when it is created, so that no block's latency pays for it.
+// One workgroup of each fused kernel that a server's batch may take, with no
+// items.  A kernel that needs private (scratch) memory has it set up by the
+// runtime at its first dispatch on a hardware queue, which can hold that queue
+// for milliseconds; a server runs this once per lane when it is created, so
+// that no block's latency pays for it.
 hipError_t warm_i8_fused(bool persist, hipStream_t s);
 hipError_t warm_i16_fused(bool persist, hipStream_t s);
 

@@ -1932,13 +1932,14 @@ hipError_t launch_stage(void* dst, const void* src_host, int64_t n16, hipStream_
     return launch_kernel(k_stage, dim3((unsigned)((n16 + kBlock - 1) / kBlock)), dim3(kBlock), s, dst, src_host, n16);
 }
 
-// Every instance that a batch may take (one mode, or mixed): a kernel's first
-// dispatch pays for bringing its code in.
+// Every instance that a batch may take (one mode, or mixed; persistent ones
+// mixed): a kernel's first dispatch pays for bringing its code in.
 hipError_t warm_i8_fused(bool persist, hipStream_t s)
 {
     LaunchArgs a{};  // no items: the workgroup returns at once
     void* kargs[] = {&a};
     for (int modes : {1, 2, 4, 7}) {
+        if (persist && modes != 7) continue;
         void (*k)(LaunchArgs) = persist ? i8_fused_kernel<true>(modes) : i8_fused_kernel<false>(modes);
         hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(k), dim3(1), dim3(kBlock), kargs, 0, s);
         if (e != hipSuccess) return e;

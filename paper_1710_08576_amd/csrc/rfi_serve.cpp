@@ -438,8 +438,17 @@ int dispatch_lane(rfi_server* srv, int li)
         a.seed = srv->cfg.seed;
         set_wg_per_cu(0);
         int64_t grid = a.n_items;
-        if (srv->cfg.schedule == RFI_SCHED_FUSED_PERSIST) grid = std::min<int64_t>(grid, srv->persist_grid);
-        e = srv->cfg.elem_size == 1 ? launch_i8_fused(L.modes, a, (int)grid, L.s)
+        int modes = L.modes;
+        // The persistent loop compiled for one mode needs 158 to 177 VGPRs (two
+        // or three workgroups per CU against four), which costs windows
+        // outside tiles more than one mode saves: 60 blocks of 10^6 samples, W
+        // 1000, noise 685 us against 456, zero 390 / 354; W 4096 91 / 80 and 66 /
+        // 68.
+        if (srv->cfg.schedule == RFI_SCHED_FUSED_PERSIST) {
+            grid = std::min<int64_t>(grid, srv->persist_grid);
+            modes = 7;
+        }
+        e = srv->cfg.elem_size == 1 ? launch_i8_fused(modes, a, (int)grid, L.s)
                                     : launch_i16_fused(a, (int)grid, L.s);
         ++srv->n_launches;
     }
