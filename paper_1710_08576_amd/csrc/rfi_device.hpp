@@ -74,14 +74,6 @@ __device__ __forceinline__ int group_count(bool pred)
 }
 
 template <int G>
-__device__ __forceinline__ int group_min(int v)
-{
-#pragma unroll
-    for (int d = G / 2; d >= 1; d >>= 1) v = min(v, __shfl_xor(v, d, G));
-    return v;
-}
-
-template <int G>
 __device__ __forceinline__ uint32_t group_sum(uint32_t v)
 {
 #pragma unroll
@@ -342,12 +334,6 @@ __device__ __forceinline__ uint32_t pk_sub_u16(uint32_t a, uint32_t b)
     return __builtin_bit_cast(uint32_t, (ushort2v)(__builtin_bit_cast(ushort2v, a) - __builtin_bit_cast(ushort2v, b)));
 }
 
-__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(ushort2v, a),
-                                                                  __builtin_bit_cast(ushort2v, b)));
-}
-
 // a - b of the two int16 halves, saturated.
 __device__ __forceinline__ uint32_t pk_subsat_i16(uint32_t a, uint32_t b)
 {
@@ -370,13 +356,6 @@ __device__ __forceinline__ uint32_t udot2_u16(uint32_t a, uint32_t b, uint32_t c
 __device__ __forceinline__ uint32_t pk_shl2_u16(uint32_t a)
 {
     return __builtin_bit_cast(uint32_t, (ushort2v)(__builtin_bit_cast(ushort2v, a) << (ushort2v){2, 2}));
-}
-
-// 0xFFFF in every 16-bit half of `diff` that is non-zero: min(half, 1)
-// subtracted from zero.
-__device__ __forceinline__ uint32_t pk_mask_nonzero_u16(uint32_t diff)
-{
-    return pk_sub_u16(0u, pk_umin1(diff));
 }
 
 __device__ __forceinline__ uint32_t rep_i16(int v)

@@ -18,31 +18,14 @@ struct I16RadixSmem {
 // ---------------------------------------------------------------------------
 // int16: radix select over two 8-bit digits.
 // ---------------------------------------------------------------------------
-// Find the bucket of rank `need` (1-based) in a 256-bin histogram whose bins
-// are spread over R replicas (bin b, replica r at b * R + r).  Every lane of
-// the wave gets the bucket and the count below it.  hw is left unchanged.
-template <int R>
-__device__ __forceinline__ void bucket_of(const uint32_t* hw, uint32_t need, int& bucket,
-                                          uint32_t& below)
+// Find the bucket of rank `need` (1-based) in a 256-bin histogram.  Every lane
+// of the wave gets the bucket and the count below it.  hw is left unchanged.
+__device__ __forceinline__ void bucket_of(const uint32_t* hw, uint32_t need, int& bucket, uint32_t& below)
 {
     const int lane = lane_id();
     uint32_t c[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t* src = hw + (lane * 4 + j) * R;
-        uint32_t s = 0;
-        if constexpr (R >= 4) {
-#pragma unroll
-            for (int r = 0; r < R; r += 4) {
-                const uint4 t = *reinterpret_cast<const uint4*>(src + r);
-                s += t.x + t.y + t.z + t.w;
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < R; ++r) s += src[r];
-        }
-        c[j] = s;
-    }
+    for (int j = 0; j < 4; ++j) c[j] = hw[lane * 4 + j];
 #pragma unroll
     for (int j = 1; j < 4; ++j) c[j] += c[j - 1];
     const uint32_t incl = group_incl_scan<64>(c[3]);
@@ -60,12 +43,6 @@ __device__ __forceinline__ void bucket_of(const uint32_t* hw, uint32_t need, int
     const uint32_t mine = pj == 0 ? c[0] : pj == 1 ? c[1] : pj == 2 ? c[2] : c[3];
     const uint32_t got = (uint32_t)__builtin_amdgcn_readlane((int)mine, max(prev, 0) >> 2);
     below = prev >= 0 ? got : 0u;
-}
-
-__device__ __forceinline__ void zero_words(uint32_t* p, int words, int tid, int nthreads)
-{
-    for (int i = tid * 4; i < words; i += nthreads * 4)
-        *reinterpret_cast<uint4*>(p + i) = make_uint4(0, 0, 0, 0);
 }
 
 // 4 int16 noise samples starting at absolute index j0 (a multiple of 4):
@@ -509,7 +486,7 @@ __device__ __forceinline__ void i16_window(const StreamView& d, int64_t w, int64
             for (int q = 0; q < 2 * K; ++q)
                 if (WHOLE || tid + (q >> 1) * NT < nch)
                     cf |= (outside_i16x4(v[2 * q], v[2 * q + 1], lob, hib, span4) ? 1u : 0u) << q;
-            pool_noise_reserved<2, NT>(v, cf, sm.noise(), tid, wave, merged);
+            pool_noise_reserved<NT>(v, cf, sm.noise(), tid, wave, merged);
         }
     }
     // The store address is formed here from a fresh copy of the thread
@@ -585,7 +562,7 @@ __device__ void i16_generic(const StreamView& d, int64_t w, uint64_t seed, I16Ra
     if (tid < 64) {
         int b;
         uint32_t below;
-        bucket_of<1>(h, need, b, below);
+        bucket_of(h, need, b, below);
         if (tid == 0) {
             sm.sel[0] = b;
             sm.sel[1] = (int)below;
@@ -602,7 +579,7 @@ __device__ void i16_generic(const StreamView& d, int64_t w, uint64_t seed, I16Ra
     if (tid < 64) {
         int b;
         uint32_t below;
-        bucket_of<1>(h + 256, need - below1, b, below);
+        bucket_of(h + 256, need - below1, b, below);
         if (tid == 0) sm.sel[2] = ((b1 << 8) | b) - 32768;
     }
     __syncthreads();
@@ -615,7 +592,7 @@ __device__ void i16_generic(const StreamView& d, int64_t w, uint64_t seed, I16Ra
     if (tid < 64) {
         int b;
         uint32_t below;
-        bucket_of<1>(h + 512, need, b, below);
+        bucket_of(h + 512, need, b, below);
         if (tid == 0) {
             sm.sel[0] = b;
             sm.sel[1] = (int)below;
@@ -632,7 +609,7 @@ __device__ void i16_generic(const StreamView& d, int64_t w, uint64_t seed, I16Ra
     if (tid < 64) {
         int b;
         uint32_t below;
-        bucket_of<1>(h + 768, need - below3, b, below);
+        bucket_of(h + 768, need - below3, b, below);
         if (tid == 0) sm.sel[3] = (b3 << 8) | b;
     }
     __syncthreads();

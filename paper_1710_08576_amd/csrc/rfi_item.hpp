@@ -58,10 +58,10 @@ __device__ __forceinline__ uint32_t noise_quad_i8(uint64_t j0, uint64_t seed, ui
 // are pooled into one list, and one thread turns each entry into its
 // merged part (noise in the flagged samples), so the draws of a workgroup
 // occupy as few waves as the list needs and an isolated flagged sample
-// costs one block.  A lane holds load slots of P parts (4 / P dwords
-// each); cf bit (slot * P + part) marks a part holding a flagged sample;
+// costs one block.  int8: a lane holds load slots of four parts, one dword
+// each; cf bit (slot * 4 + part) marks a part holding a flagged sample;
 // merged(wave, lane, slot, part, x) returns the merged part from the input
-// part x.  The list (1 KiB) and the parts (<= 2 KiB) live in LDS that the tile no
+// part x.  The list and the parts (1 KiB each) live in LDS that the tile no
 // longer needs once its windows' parameters are known (its histograms):
 // nothing is written there before the first barrier below, which every
 // wave reaches only after its selection.  The per-wave counts have storage
@@ -69,25 +69,16 @@ __device__ __forceinline__ uint32_t noise_quad_i8(uint64_t j0, uint64_t seed, ui
 struct NoiseScratch {
     uint32_t* counts;  // [4]
     uint32_t* list;    // [256]
-    uint4* data;       // [256], 16-byte aligned
+    uint4* data;       // the parts, 16-byte aligned
 };
 constexpr int kNoiseAliasWords = 256 + 4 * 256;
 
-template <int P> struct NoisePart;
-template <> struct NoisePart<4> { using T = uint32_t; };
-template <> struct NoisePart<2> { using T = uint2; };
-
-// NT: threads of the workgroup (a multiple of 64, at most 256); the list
-// holds NT parts a round.
-template <int P, int NT = kBlock, int NV = 16, class PartFn>
-__device__ __forceinline__ void pool_noise(uint32_t (&v)[NV], uint32_t cf, const NoiseScratch& ns,
-                                           PartFn merged)
+// A workgroup of kBlock threads; the list holds as many parts a round.
+template <int NQ, class PartFn>
+__device__ __forceinline__ void pool_noise(uint32_t (&v)[NQ], uint32_t cf, const NoiseScratch& ns, PartFn merged)
 {
-    constexpr int NQ = NV * P / 4;  // parts per lane
-    using PartT = typename NoisePart<P>::T;
-    constexpr int WPP = 4 / P;  // dwords per part
-    constexpr int C = NT;       // parts per round
-    PartT* data = reinterpret_cast<PartT*>(ns.data);
+    constexpr int C = kBlock;  // parts per round
+    uint32_t* data = reinterpret_cast<uint32_t*>(ns.data);
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
     const uint32_t cnt = __popc(cf);
@@ -96,7 +87,7 @@ __device__ __forceinline__ void pool_noise(uint32_t (&v)[NV], uint32_t cf, const
     __syncthreads();
     int wbase = 0, F = 0;
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
+    for (int w = 0; w < kBlock / 64; ++w) {
         const int c = (int)ns.counts[w];
         wbase += w < wave ? c : 0;
         F += c;
@@ -111,9 +102,8 @@ __device__ __forceinline__ void pool_noise(uint32_t (&v)[NV], uint32_t cf, const
         for (int q = 0; q < NQ; ++q) {
             if ((cf >> q) & 1u) {
                 if (e >= 0 && e < C) {
-                    ns.list[e] = (uint32_t)(q / P << 10 | wave << 8 | lane << 2 | (q % P));
-                    if constexpr (P == 4) data[e] = v[q];
-                    else data[e] = make_uint2(v[WPP * q], v[WPP * q + 1]);
+                    ns.list[e] = (uint32_t)(q / 4 << 10 | wave << 8 | lane << 2 | (q % 4));
+                    data[e] = v[q];
                 }
                 ++e;
             }
@@ -130,15 +120,7 @@ __device__ __forceinline__ void pool_noise(uint32_t (&v)[NV], uint32_t cf, const
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             if ((cf >> q) & 1u) {
-                if (e >= 0 && e < C) {
-                    if constexpr (P == 4) {
-                        v[q] = data[e];
-                    } else {
-                        const uint2 t = data[e];
-                        v[WPP * q] = t.x;
-                        v[WPP * q + 1] = t.y;
-                    }
-                }
+                if (e >= 0 && e < C) v[q] = data[e];
                 ++e;
             }
         }
@@ -155,7 +137,8 @@ __device__ __forceinline__ void group_sync()
     else __syncthreads();
 }
 
-// pool_noise without its first barrier: each wave reserves its slots with
+// pool_noise for int16 (a part is two dwords, two parts to a load slot) and
+// without its first barrier: each wave reserves its slots with
 // one LDS atomic add on ns.counts[0], which the caller has zeroed before a
 // workgroup barrier that precedes the call (the waves' slots then follow
 // in the order of their adds).  The total is read after the barrier that
@@ -165,14 +148,12 @@ __device__ __forceinline__ void group_sync()
 // workgroup may still be reading.  NT = 64: one wave by itself, with no
 // barriers and no counter, whose list may take the place of what the wave
 // no longer needs.  tid: the thread's index among the NT.
-template <int P, int NT, int NV = 16, class PartFn>
+template <int NT, int NV, class PartFn>
 __device__ __forceinline__ void pool_noise_reserved(uint32_t (&v)[NV], uint32_t cf, const NoiseScratch& ns, int tid,
                                                     int wave, PartFn merged)
 {
-    using PartT = typename NoisePart<P>::T;
-    constexpr int WPP = 4 / P;
     constexpr int C = NT;
-    PartT* data = reinterpret_cast<PartT*>(ns.data);
+    uint2* data = reinterpret_cast<uint2*>(ns.data);
     const int lane = lane_id();
     const uint32_t cnt = __popc(cf);
     const uint32_t incl = group_incl_scan<64>(cnt);
@@ -188,12 +169,11 @@ __device__ __forceinline__ void pool_noise_reserved(uint32_t (&v)[NV], uint32_t 
     for (int r0 = 0;; r0 += C) {
         int e = base - r0;
 #pragma unroll
-        for (int q = 0; q < NV * P / 4; ++q) {
+        for (int q = 0; q < NV / 2; ++q) {
             if ((cf >> q) & 1u) {
                 if (e >= 0 && e < C) {
-                    ns.list[e] = (uint32_t)(q / P << 12 | wave << 8 | lane << 2 | (q % P));
-                    if constexpr (P == 4) data[e] = v[q];
-                    else data[e] = make_uint2(v[WPP * q], v[WPP * q + 1]);
+                    ns.list[e] = (uint32_t)(q / 2 << 12 | wave << 8 | lane << 2 | (q % 2));
+                    data[e] = make_uint2(v[2 * q], v[2 * q + 1]);
                 }
                 ++e;
             }
@@ -209,16 +189,12 @@ __device__ __forceinline__ void pool_noise_reserved(uint32_t (&v)[NV], uint32_t 
         group_sync<NT>();
         e = base - r0;
 #pragma unroll
-        for (int q = 0; q < NV * P / 4; ++q) {
+        for (int q = 0; q < NV / 2; ++q) {
             if ((cf >> q) & 1u) {
                 if (e >= 0 && e < C) {
-                    if constexpr (P == 4) {
-                        v[q] = data[e];
-                    } else {
-                        const uint2 t = data[e];
-                        v[WPP * q] = t.x;
-                        v[WPP * q + 1] = t.y;
-                    }
+                    const uint2 t = data[e];
+                    v[2 * q] = t.x;
+                    v[2 * q + 1] = t.y;
                 }
                 ++e;
             }

@@ -401,7 +401,7 @@ __device__ __forceinline__ void i8_replace(const StreamView& d, int64_t first, u
                 const uint32_t nz = noise_quad_i8((uint64_t)(abs0 + off), seed, key1, p.m, p.sq8);
                 return byte_perm(nz, x, flag_sel_i8x4(x, lo_u, hi_u));
             };
-            pool_noise<4>(v, cf, sm.noise(), merged);
+            pool_noise(v, cf, sm.noise(), merged);
         }
     }
 }
@@ -932,7 +932,7 @@ __device__ __forceinline__ void i8_window(const StreamView& d, int64_t w, int64_
         };
         static_assert(sizeof(sm.whist) >= kNoiseAliasWords * 4, "noise list in the histograms");
         // every thread of the workgroup, whatever its window's mode
-        pool_noise<4>(v, cf, sm.noise(), merged);
+        pool_noise(v, cf, sm.noise(), merged);
     }
     if (mode == kModeStats) return;
     uint8_t* yb = static_cast<uint8_t*>(d.y) + base;
@@ -1024,8 +1024,8 @@ __device__ void i8_generic(const StreamView& d, int64_t w, uint64_t seed, Smem& 
 }
 
 // ---------------------------------------------------------------------------
-// Kernels.  All loop over items with a grid stride, so the same kernel
-// serves one-workgroup-per-item launches and persistent launches.
+// Kernels.  Those with a PERSIST parameter serve launches of one workgroup per
+// item and, with a grid-stride loop over the items, persistent ones.
 // ---------------------------------------------------------------------------
 // One or two tiles per workgroup.  With two, the second tile's loads are
 // issued before the first tile is processed, so they are in flight while
@@ -1624,7 +1624,7 @@ __device__ __forceinline__ void mom_apply_item(const LaunchArgs& a, const MomIte
                 atomicAdd(&sm.flagged[rel >> sh], (uint32_t)__popc(sel ^ 0x03020100u));  // one bit per flagged byte
                 return byte_perm(nz, xw, sel);
             };
-            pool_noise<4>(v, cf, sm.noise(), merged);
+            pool_noise(v, cf, sm.noise(), merged);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -1710,7 +1710,7 @@ __device__ __forceinline__ void mom_apply_item(const LaunchArgs& a, const MomIte
                     }
                     return r;
                 };
-                pool_noise<4>(v, cf, sm.noise(), merged);
+                pool_noise(v, cf, sm.noise(), merged);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
