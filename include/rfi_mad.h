@@ -293,7 +293,10 @@ int rfi_plan_execute(rfi_plan* plan, const void* x, void* y, rfi_window_stats* s
  *                         the autotuned value, default 1).
  *   RFI_OPT_WG_PER_CU     at most this many workgroups resident per compute
  *                         unit (1..32, enforced by padding LDS), 0 = no cap,
- *                         -1 = the autotuned value (default; 8 untuned). */
+ *                         -1 = the autotuned value (default; 8 untuned).  For
+ *                         tile, fused and persistent launches; a launch of
+ *                         windows outside tiles that covers every item runs
+ *                         uncapped. */
 typedef enum { RFI_OPT_TILES_PER_WG = 1, RFI_OPT_WG_PER_CU = 2 } rfi_option;
 int rfi_plan_set_option(rfi_plan* plan, int32_t option, int32_t value);
 /* Number of kernel launches one execute makes, and total windows. */

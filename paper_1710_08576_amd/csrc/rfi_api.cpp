@@ -650,10 +650,11 @@ int plan_build(int elem, int32_t n, const int64_t* L, const int32_t* W, const fl
         std::stable_sort(groups[0].begin(), groups[0].end(), [&](const Item& a, const Item& b) {
             return i16_window_threads(W[a.stream], L[a.stream]) < i16_window_threads(W[b.stream], L[b.stream]);
         });
-    if (elem == 1)
-        std::stable_partition(groups[0].begin(), groups[0].end(), [&](const Item& it) {
-            return i8_short_windows(W[it.stream], L[it.stream], p->noise);
-        });
+    if (elem == 1) {  // short windows first
+        auto is_short = [&](const Item& it) { return i8_short_windows(W[it.stream], L[it.stream], p->noise); };
+        if (!std::is_partitioned(groups[0].begin(), groups[0].end(), is_short))
+            std::stable_partition(groups[0].begin(), groups[0].end(), is_short);
+    }
     for (auto& g : groups) p->hitems.insert(p->hitems.end(), g.begin(), g.end());
     for (int m = 0; m < 3; ++m) {  // the statistics-only mode has no fused launch
         for (const Item& it : groups[0])

@@ -508,7 +508,9 @@ __device__ __forceinline__ void wave_sums6(const uint32_t (&e)[6], int (&sum)[6]
 // sums of distances, and added to the histogram's cumulative counts there.
 // False if the result is not among those values; the counts are then taken
 // from all samples.  60 x 2^21 samples: 44 -> 32 us (3.9 TB/s read), 60 x
-// 2^20 23.6 -> 18.
+// 2^20 23.6 -> 18.  Only for W 4096, whose window is one wave's: the narrow
+// classes have other histograms, and the waves of a W 8192 or 16384 window
+// would have to add up their counts twice more between barriers (not tried).
 template <bool NS>
 __device__ __forceinline__ bool i8_stats_select_4096(I8TileSmem<4096, NS>& sm, const uint32_t (&v)[16], int& mb_out,
                                                      int& D_out)
