@@ -205,12 +205,12 @@ int ensure_slot(Slot& sl, size_t bytes)
 // Stages the tables in the slot (the item lists one after another) and copies
 // them to the device on stream s (one copy); returns the device addresses of
 // the three tables and the number of items.
-int upload(Slot& sl, const std::vector<StreamDesc>& descs, const std::vector<const std::vector<Item>*>& items,
+int upload(Slot& sl, const std::vector<StreamDesc>& descs, const std::vector<Item>* const* items, int n_lists,
            const std::vector<CarryItem>& carries, hipStream_t s, StreamDesc** dd, Item** di, CarryItem** dc,
            int64_t* n_items)
 {
     size_t n = 0;
-    for (const auto* v : items) n += v->size();
+    for (int i = 0; i < n_lists; ++i) n += items[i]->size();
     *n_items = (int64_t)n;
     const size_t bd = descs.size() * sizeof(StreamDesc), bi = n * sizeof(Item), bc = carries.size() * sizeof(CarryItem);
     const size_t oi = align256(bd), oc = oi + align256(bi), total = oc + align256(bc);
@@ -218,9 +218,10 @@ int upload(Slot& sl, const std::vector<StreamDesc>& descs, const std::vector<con
     if (rc != RFI_OK) return rc;
     if (bd) std::memcpy(sl.h_stage, descs.data(), bd);
     char* at = sl.h_stage + oi;
-    for (const auto* v : items) {
-        if (!v->empty()) std::memcpy(at, v->data(), v->size() * sizeof(Item));
-        at += v->size() * sizeof(Item);
+    for (int i = 0; i < n_lists; ++i) {
+        const size_t b = items[i]->size() * sizeof(Item);
+        if (b) std::memcpy(at, items[i]->data(), b);
+        at += b;
     }
     if (bc) std::memcpy(sl.h_stage + oc, carries.data(), bc);
     if (total) {
@@ -399,9 +400,10 @@ int dispatch_lane(rfi_server* srv, int li)
     // A carry update reads what no item of the batch writes (input blocks and
     // the stream's other carry buffer), so it is an item like the others.
     for (size_t i = 0; i < L.carries.size(); ++i) L.carry_items.push_back(Item{(int32_t)i, kItemCarry, 0});
-    std::vector<const std::vector<Item>*> items{&L.generic, &L.carry_items};
+    const std::vector<Item>* items[2 + 2 * kI8Classes] = {&L.generic, &L.carry_items};
+    int n_lists = 2;
     for (auto& m : L.tiles)
-        for (auto& v : m) items.push_back(&v);
+        for (auto& v : m) items[n_lists++] = &v;
     Slot& sl = L.slots[si];
     StreamDesc* dd = nullptr;
     Item* di = nullptr;
@@ -409,7 +411,7 @@ int dispatch_lane(rfi_server* srv, int li)
     int64_t n_items = 0;
     int rc = RFI_OK;
     if (++srv->uploads >= srv->fail_from && srv->uploads < srv->fail_from + srv->fail_count) rc = RFI_ERR_NOMEM;
-    if (rc == RFI_OK) rc = upload(sl, L.descs, items, L.carries, L.s, &dd, &di, &dc, &n_items);
+    if (rc == RFI_OK) rc = upload(sl, L.descs, items, n_lists, L.carries, L.s, &dd, &di, &dc, &n_items);
     if (rc != RFI_OK) {
         // Nothing of this batch reached the device: undo it.
         for (int j = 0; j < nm; ++j) {
@@ -742,9 +744,9 @@ int rfi_server_flush(rfi_server* srv, uint32_t stream_id, void* out_dev, rfi_win
     StreamDesc* dd = nullptr;
     Item* di = nullptr;
     CarryItem* dc = nullptr;
-    const std::vector<Item> item{Item{0, kItemGeneric, 0}};
+    const std::vector<Item> item{Item{0, kItemGeneric, 0}}, *items = &item;
     int64_t n_items = 0;
-    rc = upload(L.slots[0], std::vector<StreamDesc>{d}, {&item}, std::vector<CarryItem>{}, L.s, &dd, &di, &dc, &n_items);
+    rc = upload(L.slots[0], std::vector<StreamDesc>{d}, &items, 1, std::vector<CarryItem>{}, L.s, &dd, &di, &dc, &n_items);
     if (rc != RFI_OK) return rc;
     LaunchArgs a;
     std::memset(&a, 0, sizeof(a));
