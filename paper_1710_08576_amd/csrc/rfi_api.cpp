@@ -487,7 +487,7 @@ static void build_launches(rfi_plan* p)
                     const int64_t w = p->W[it.stream];
                     nmax = std::max<int64_t>(nmax, std::min<int64_t>(w, p->L[it.stream] - it.first * w));
                 }
-                l.small = i8_window_threads(nmax, e - b);
+                l.small = i8_window_threads(nmax, e - b, (l.modes & 4) != 0);
             }
             p->launches[RFI_SCHED_SPLIT].push_back(l);
             l.grid = (int)std::min<int64_t>(e - b, persistent_grid(elem, cls, l.modes, false));

@@ -164,13 +164,15 @@ hipError_t launch_i8_tiles(int cls, int modes, int tpw, const LaunchArgs& a, int
 // streams, noise, microseconds, 256 threads against the fewest: 60 windows of
 // 3000 samples 6.8 / 8.3, 480 of 4067 7.2 / 10.0; 128 threads of four chunks
 // against 64 of eight, 960 of 6000 8.7 / 10.3, 3840 16.8 / 17.8, 15360 45.1 /
-// 42.8), and so does one whose chunks nearly fill them (16354 samples, clip,
-// 15360 windows, 256 threads of four against 128 of eight 88 / 101; 12000
-// samples, noise, 79 / 75).  no_scratch: only kernels without private memory
+// 42.8), and so does one whose chunks nearly fill them (15360 windows, 256
+// threads of four against 128 of eight, clip: 9000 samples 54 / 53, 12000 65 /
+// 67, 14001 77 / 86, 16354 88 / 101; noise: 12000 79 / 75, 14001 92 / 89, 15000 95
+// / 93, 16354 99 / 100).  noise: some window of the launch may be in noise
+// mode.  no_scratch: only kernels without private memory
 // (eight chunks of 64 or 128 threads spill in noise mode).
 constexpr int kWideThreads = 1;
 constexpr int kShortWindows = 2;
-inline int i8_window_threads(int64_t n, int64_t count, bool no_scratch = false)
+inline int i8_window_threads(int64_t n, int64_t count, bool noise, bool no_scratch = false)
 {
     if (n > 32738) return 0;
     if (n > 16354) return 256 | kWideThreads;
@@ -178,7 +180,7 @@ inline int i8_window_threads(int64_t n, int64_t count, bool no_scratch = false)
     if (n <= 4066) return 64;
     const bool few = count <= 4096 || no_scratch;
     if (n <= 8162) return few ? 128 : 64 | kWideThreads;
-    return few || n > 14000 ? 256 : 128 | kWideThreads;
+    return few || n > (noise ? 15000 : 11000) ? 256 : 128 | kWideThreads;
 }
 // Whether a stream's windows are short: counting them into one plain
 // histogram by one wave, sample by sample, beats holding 16-byte chunks in

@@ -134,7 +134,7 @@ int multi_build(int32_t n_out, int32_t n, const int64_t* L, const int32_t* W, co
     }
     if (!groups[0].empty()) {
         const int64_t c = (int64_t)groups[0].size();
-        p->gen.push_back({(int64_t)items.size(), c, i8_window_threads(gen_longest, c)});
+        p->gen.push_back({(int64_t)items.size(), c, i8_window_threads(gen_longest, c, false)});
         items.insert(items.end(), groups[0].begin(), groups[0].end());
     }
     hipError_t e = hipSuccess;

@@ -266,7 +266,7 @@ extern "C" int rfi_mad_filter_noalloc(const int8_t* x, int8_t* y, int32_t n_stre
         hipError_t e;
         if (g == 0 || g == kNaShort) {
             const int i = g == 0 ? 0 : 1;
-            const int small = i ? kShortWindows : i8_window_threads(nmax_of[i], count[g], true);
+            const int small = i ? kShortWindows : i8_window_threads(nmax_of[i], count[g], noise, true);
             e = launch_i8_generic(la, modes_of[i], grid, hs, small);
         } else {
             const int cls = (g - 1) / 3, m = (g - 1) % 3;

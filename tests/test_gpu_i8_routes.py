@@ -28,9 +28,9 @@ def _batch(seed, windows, counts, modes):
 
 
 # either side of: short windows, 512 and 4096 windows of a launch, the longest
-# window of 64 and 128 threads, 14000 samples
+# window of 64 and 128 threads, windows that nearly fill 256
 @pytest.mark.parametrize("modes", [(0, 1), (2,), (0, 1, 2)])
-@pytest.mark.parametrize("W", [160, 161, 256, 257, 4066, 4067, 8162, 8163, 14000, 14001, 16354])
+@pytest.mark.parametrize("W", [160, 161, 256, 257, 4066, 4067, 8162, 8163, 11000, 11001, 14000, 14001, 15000, 15001, 16354])
 @pytest.mark.parametrize("count", [512, 513, 4096, 4097])
 def test_window_counts(gpu, W, count, modes):
     x, specs = _batch(W + count, [W] * 3, [count // 3, count // 3, count - 2 * (count // 3)], modes)
